@@ -519,7 +519,7 @@ def bench_bc(args):
 
 
 def bench_cc(args):
-    """Connected components (minimum-label propagation) on the bench graph:
+    """Connected components on the bench graph:
     TEPS as section 5 counts them (every directed edge of the symmetrized
     graph once per run)."""
     import torch
@@ -546,7 +546,7 @@ def bench_cc(args):
     st = tg.tg_last_stats()
     ncomp = int(torch.unique(lab).numel())
     ms = sum(times) / len(times)
-    out = {"metric": "GTEPS, connected components (minimum-label propagation)",
+    out = {"metric": "GTEPS, connected components",
            "value": round(g.nnz / (ms / 1e3) / 1e9, 2), "unit": "GTEPS", "higher_is_better": True, "n_gpus": 1,
            "data": "synthetic", "dtype": "int32 labels",
            "config": {"workload": f"{args.workload_graph}: V={g.n}, E={g.nnz}"},

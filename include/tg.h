@@ -238,10 +238,10 @@ int pagerank(const tg_partition *p, float damping, int32_t iterations,
 int bc(const tg_partition *p, const int32_t *sources, int32_t num_sources,
        float *scores, void *stream);
 
-/* Connected components by minimum-label propagation (the fifth algorithm of
- * section 9.4, run on the undirected graph; labels are reduced by minimum,
- * section 3.4): every vertex starts with its own id and pushes any lower
- * label it receives to its neighbours until no label drops.
+/* Connected components (the fifth algorithm of section 9.4, run on the
+ * undirected graph): a forest of parent links is grown by linking the ends
+ * of a few edges per vertex, then of the remaining edges of the vertices
+ * outside the large component.
  *   labels    device int32 [V]: the smallest original vertex id of the
  *             vertex's component.  On a directed graph the components are
  *             the weak ones (labels cross edges in both directions).

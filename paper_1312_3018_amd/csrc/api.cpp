@@ -1115,8 +1115,7 @@ extern "C" int cc(const tg_partition *pc, int32_t *labels, void *stream) {
   TG_TRY(p->ws.ensure(p->gpu, 0));
   TG_TRY(stat_zero_all(p->ws, s));
   int64_t rounds = 0;
-  TG_TRY(gpu_cc(p, s, &rounds));
-  if (p->gpu.n > 0) TG_TRY(collect_i32(p->gpu, p->ws.state, labels, s));
+  TG_TRY(gpu_cc(p, labels, s, &rounds));
   TG_TRY(stat_fetch(p->ws, 0, s));
   TG_HIP(hipStreamSynchronize(s));
   stats_add("supersteps", (double)rounds);

@@ -544,8 +544,8 @@ int gpu_sssp_roots(tg_partition *p, const int32_t *roots_local, int32_t nr, int3
 int gpu_pagerank(tg_partition *p, double damping, int32_t iters, int mode, float *rank_out,
                  hipStream_t s);
 int gpu_bc_source(tg_partition *p, int32_t src_local, hipStream_t s);
-// cc.hip: component labels (original ids) into ws.state
-int gpu_cc(tg_partition *p, hipStream_t s, int64_t *rounds_out);
+// cc.hip: component labels (original ids) into `labels` (device, V entries)
+int gpu_cc(tg_partition *p, int32_t *labels, hipStream_t s, int64_t *rounds_out);
 // bcb.hip: adds the dependencies of `sources` (original ids) into ws.bc_acc
 int gpu_bc_batched(tg_partition *p, const int32_t *sources, int32_t ns, hipStream_t s);
 void bcb_free(tg_partition *p);

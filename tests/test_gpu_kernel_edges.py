@@ -46,3 +46,54 @@ def test_parents_of_ragged_vertex_counts(gpu, n):
     lev, par = gpu.bfs(load(gpu, g), [0], want_parents=True)
     assert np.array_equal(lev.cpu().numpy()[0], oracle.bfs(g.offsets, g.cols, 0))
     assert np.array_equal(par.cpu().numpy()[0], np.r_[0, up])
+
+
+# ---------------------------------------------------- connected components
+
+@pytest.mark.parametrize("n", [1, 2, 255, 256, 257, 511, 513, 30011])
+@pytest.mark.parametrize("sym", [True, False])
+def test_components_of_ragged_sizes(gpu, n, sym):
+    """Sparse random graphs around the block and sample sizes: isolated
+    vertices, many small components and one large one."""
+    for k, m in enumerate((n // 2, n, 3 * n)):
+        rng = np.random.default_rng(10 * n + k)
+        g = graphgen.from_edges(n, rng.integers(0, n, m), rng.integers(0, n, m), symmetrize=sym)
+        assert np.array_equal(gpu.cc(load(gpu, g)).cpu().numpy(), oracle.cc(g.offsets, g.cols)), (n, m, sym)
+
+
+@pytest.mark.parametrize("sym", [True, False])
+@pytest.mark.parametrize("deg", [4, 5, 12, 13, 76, 511, 512, 5000])
+def test_components_joined_past_the_sampled_edges(gpu, deg, sym):
+    """Stars of equal size joined only through the last edge of each centre's
+    row, so that no sampled edge and no large component hides it: rows just
+    inside and past the sampled four, the one-lane rows, the wave's and the
+    blocks'."""
+    k = 6
+    src, dst = [], []
+    for i in range(k):
+        c = i * (deg + 1)
+        src += [c] * deg
+        dst += list(range(c + 1, c + deg + 1))
+    # the centres' largest neighbour: a leaf of the next star, in pairs
+    for i in range(0, k, 2):
+        src.append(i * (deg + 1))
+        dst.append((i + 2) * (deg + 1) - 1)
+    n = k * (deg + 1) + 3
+    for flip in (False, True):
+        a, b = (dst, src) if flip else (src, dst)
+        g = graphgen.from_edges(n, np.array(a), np.array(b), symmetrize=sym)
+        ref = oracle.cc(g.offsets, g.cols)
+        assert len(np.unique(ref)) == k // 2 + 3
+        assert np.array_equal(gpu.cc(load(gpu, g)).cpu().numpy(), ref), (deg, sym, flip)
+
+
+def test_components_of_long_paths(gpu):
+    """Paths whose parent links form one long chain: vertices in id order, so
+    that every vertex starts under its predecessor, alone and next to a star."""
+    n = 60000
+    for extra in (0, 4000):
+        src = np.r_[np.arange(n - 1), np.full(extra, n)]
+        dst = np.r_[np.arange(1, n), n + 1 + np.arange(extra)]
+        g = graphgen.from_edges(n + 1 + extra, src, dst, symmetrize=True)
+        lab = gpu.cc(load(gpu, g)).cpu().numpy()
+        assert np.array_equal(lab, oracle.cc(g.offsets, g.cols)), extra
