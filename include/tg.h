@@ -308,8 +308,8 @@ void server_destroy(tg_server *s);
 
 /* Batched Brandes betweenness: the same result as bc() (within the stated
  * tolerance), up to 64 sources per chain of supersteps with vertex state laid
- * out [vertex][source] (sigma fp64, delta fp32, level int32: 16 B per vertex
- * and source of scratch).  Many small graphs run in one chain by loading
+ * out [vertex][source] (sigma fp64, delta and (1 + delta) / sigma fp32: 16 B
+ * per vertex and source of scratch).  Many small graphs run in one chain by loading
  * their disjoint union as one graph.  GPU-only partitions.  Same buffers and
  * errors as bc(), plus TG_EUNSUPPORTED on a hybrid partition. */
 int bc_batched(const tg_partition *p, const int32_t *sources, int32_t num_sources,
