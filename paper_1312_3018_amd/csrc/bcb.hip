@@ -26,103 +26,105 @@
 // flight.  Rows take waves by degree: hubs (the HUB bin) several blocks each
 // with partial sums added by a second launch, the BLOCK bin a block, the
 // WAVE bin a wave; below that a wave takes several consecutive queue entries
-// and walks their edges as one list, because the chain of dependent reads
-// (entry, offsets, ids, masks, rows) is otherwise paid per short row.
-// RMAT-20, 64 sources: @BC@.
+// and walks their edges as one list (the walks are in ms.h).
+// RMAT-20, 64 sources: 23.6 ms a call with four edges in flight per wave and
+// three rows (level, sigma, delta) read per edge, 6.9 so, 6.1 with the
+// levels pulled (ms.hip) where 970 us of pushes had been.
 #include <string.h>
 
 #include <algorithm>
 #include <vector>
 
-#include "tg_internal.h"
+#include "ms.h"
 
 using namespace tgk;
 
 namespace tg {
 namespace {
 
-using u64 = unsigned long long;
-constexpr int S = 64;  // sources per chain
+constexpr int S = kSlots;  // sources per chain
 
 inline unsigned nblk(int64_t n) { return (unsigned)std::max<int64_t>((n + BLOCK - 1) / BLOCK, 1); }
-
-__global__ __launch_bounds__(BLOCK) void k_bb_expand(const Plan *__restrict__ Pp, const int32_t *__restrict__ queue,
-                                                     const int64_t *__restrict__ hubpref,
-                                                     const int64_t *__restrict__ off, const int32_t *__restrict__ col,
-                                                     const u64 *front, const u64 *visited, u64 *next,
-                                                     uint32_t *touched, int64_t hub_chunk) {
-  const Plan &P = load_plan(Pp);
-  const int64_t total = P.vb[NBIN];
-  for (int64_t vb = blockIdx.x; vb < total; vb += gridDim.x) {
-    const Assign a = assign_work(vb, P, queue, nullptr, hubpref, off, hub_chunk);
-    if (!a.ok) continue;
-    const u64 m = front[a.v];
-    if (m == 0) continue;
-    for (int64_t e = a.e_begin + a.lane; e < a.e_end; e += a.stride) {
-      const int32_t nb = stream_load(col + e);
-      const u64 x = m & ~visited[nb];
-      if (x && atomicOr(next + nb, x) == 0) atomicOr(touched + (nb >> 5), 1u << (nb & 31));
-    }
-  }
-}
 
 template <typename T>
 __global__ __launch_bounds__(BLOCK) void k_bb_fill(T *p, int64_t n, T v) {
   for (int64_t i = (int64_t)blockIdx.x * BLOCK + threadIdx.x; i < n; i += (int64_t)gridDim.x * BLOCK) p[i] = v;
 }
 
-// Settle level L+1: new bits, visited, the new frontier masks and the mask of
-// each queue entry.
+// Settle level L+1: new bits, visited, the new frontier masks, the mask of
+// each queue entry and the frontier's edges per source.
 __global__ __launch_bounds__(BLOCK) void k_bb_finalize(const Plan *__restrict__ Pp, const int32_t *__restrict__ queue,
                                                        u64 *__restrict__ qmask, u64 *visited, u64 *front_new,
-                                                       u64 *next) {
+                                                       u64 *next, const int64_t *__restrict__ off,
+                                                       u64 (*mf)[kSlots], u64 (*other)[kSlots]) {
   const int32_t count = Pp->count;
-  for (int64_t i = (int64_t)blockIdx.x * BLOCK + threadIdx.x; i < count; i += (int64_t)gridDim.x * BLOCK) {
-    const int32_t v = queue[i];
-    const u64 seen = visited[v];
-    const u64 nb = next[v] & ~seen;
-    next[v] = 0;
-    visited[v] = seen | nb;
-    front_new[v] = nb;
-    qmask[i] = nb;
+  u64 acc = 0;
+  for (int64_t b = (int64_t)blockIdx.x * BLOCK; b < count; b += (int64_t)gridDim.x * BLOCK) {
+    const int64_t i = b + threadIdx.x;
+    u64 nb = 0;
+    uint32_t edges = 0;
+    if (i < count) {
+      const int32_t v = queue[i];
+      const u64 seen = visited[v];
+      nb = next[v] & ~seen;
+      next[v] = 0;
+      visited[v] = seen | nb;
+      front_new[v] = nb;
+      qmask[i] = nb;
+      edges = (uint32_t)(off[v + 1] - off[v]) + 1u;
+    }
+    add_by_slot(nb, edges, acc);
   }
+  publish_by_slot<BLOCK>(acc, mf, other);
 }
-
-__device__ __forceinline__ u64 lane_mask(u64 m, int src) {
-  return (u64)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)m, src) |
-         ((u64)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(m >> 32), src) << 32);
-}
-
-__device__ __forceinline__ int64_t lane_i64(int64_t x, int src) { return (int64_t)lane_mask((u64)x, src); }
 
 // The sigma pull: rows are sigma rows (fp64), a row's sum is the vertex's own.
 struct SigmaOp {
-  using T = double;
+  using X = double;
+  using A = double;
+  using P = double;
+  static constexpr bool WEIGHTS = false;
   double *rows;
   uint32_t *flags;
-  __device__ __forceinline__ double begin(int32_t, u64) const { return 0.0; }
-  __device__ __forceinline__ void end(int32_t v, u64 m, double, double acc) const {
+  __device__ __forceinline__ A zero() const { return 0.0; }
+  __device__ __forceinline__ P begin(int32_t, u64) const { return 0.0; }
+  __device__ __forceinline__ X load(int32_t u, u64 m) const {
+    const int lane = threadIdx.x & 63;
+    return (m >> lane) & 1ull ? rows[(int64_t)u * S + lane] : 0.0;
+  }
+  __device__ __forceinline__ void add(A &acc, X x, int32_t) const { acc += x; }
+  __device__ __forceinline__ void end(int, int32_t v, u64 m, P, A acc) const {
     const int lane = threadIdx.x & 63;
     if ((m >> lane) & 1ull) {
       rows[(int64_t)v * S + lane] = acc;
       if (acc >= 9007199254740992.0) flags[2] = 1u;  // 2^53
     }
   }
+  __device__ __forceinline__ void idle(int32_t, u64, u64) const {}  // (a reached vertex has a parent)
 };
 
 // The dependencies: rows are g rows (fp32).  The vertex's mask at its level
 // becomes the child mask of the next pass.
 struct DeltaOp {
-  using T = float;
+  using X = float;
+  using A = double;
+  using P = double;
+  static constexpr bool WEIGHTS = false;
   float *rows;
   const double *sigma;
   float *delta;
   u64 *mask_out;
-  __device__ __forceinline__ double begin(int32_t v, u64 m) const {
+  __device__ __forceinline__ A zero() const { return 0.0; }
+  __device__ __forceinline__ P begin(int32_t v, u64 m) const {
     const int lane = threadIdx.x & 63;
     return (m >> lane) & 1ull ? sigma[(int64_t)v * S + lane] : 1.0;
   }
-  __device__ __forceinline__ void end(int32_t v, u64 m, double sv, double acc) const {
+  __device__ __forceinline__ X load(int32_t u, u64 m) const {
+    const int lane = threadIdx.x & 63;
+    return (m >> lane) & 1ull ? rows[(int64_t)u * S + lane] : 0.0f;
+  }
+  __device__ __forceinline__ void add(A &acc, X x, int32_t) const { acc += (double)x; }
+  __device__ __forceinline__ void end(int, int32_t v, u64 m, P sv, A acc) const {
     const int lane = threadIdx.x & 63;
     if ((m >> lane) & 1ull) {
       const float d = (float)(sv * acc);
@@ -131,43 +133,16 @@ struct DeltaOp {
     }
     if (lane == 0) mask_out[v] = m;
   }
-};
-
-constexpr int FLY = 8;  // state rows in flight per wave
-
-// Sum, over the tiles of 64 edges first, first + step, ... of [e0, e1), of
-// the neighbours' rows masked by mask[u] & m (lane = source).
-template <typename T>
-__device__ __forceinline__ double masked_rows(const int32_t *__restrict__ col, int64_t e0, int64_t e1, int first,
-                                              int step, const u64 *__restrict__ mask, u64 m, const T *rows) {
-  const int lane = threadIdx.x & 63;
-  const int64_t stride = (int64_t)step * 64;
-  double acc = 0.0;
-  int64_t e = e0 + (int64_t)first * 64;
-  int32_t u = e + lane < e1 ? stream_load(col + e + lane) : -1;
-  while (e < e1) {
-    const u64 mu = u >= 0 ? mask[u] & m : 0ull;
-    const int32_t uc = u;
-    e += stride;
-    u = e + lane < e1 ? stream_load(col + e + lane) : -1;  // the next tile's ids
-    for (u64 todo = __ballot(mu != 0ull); todo;) {
-      T x[FLY];
-#pragma unroll
-      for (int k = 0; k < FLY; ++k) {
-        x[k] = (T)0;
-        if (todo) {
-          const int src = __ffsll((long long)todo) - 1;
-          todo &= todo - 1;
-          if ((lane_mask(mu, src) >> lane) & 1ull)
-            x[k] = rows[(int64_t)__builtin_amdgcn_readlane(uc, src) * S + lane];
-        }
-      }
-#pragma unroll
-      for (int k = 0; k < FLY; ++k) acc += (double)x[k];
+  // no child: delta is 0
+  __device__ __forceinline__ void idle(int32_t v, u64 m, u64 open) const {
+    for (; open; open &= open - 1) {
+      const int j = __ffsll((long long)open) - 1;
+      const int32_t vj = __builtin_amdgcn_readlane(v, j);
+      const u64 mj = lane_mask(m, j);
+      end(j, vj, mj, begin(vj, mj), 0.0);
     }
   }
-  return acc;
-}
+};
 
 // Sum of the block's four waves' per-lane partials (every wave gets it).
 __device__ __forceinline__ double block_lane_sum(double x) {
@@ -190,8 +165,8 @@ __global__ __launch_bounds__(BLOCK) void k_bb_block(const int32_t *__restrict__ 
     const int32_t v = queue[i];
     const u64 m = qmask[i];  // block-uniform, never 0
     const double pre = op.begin(v, m);
-    const double acc = block_lane_sum(masked_rows(col, off[v], off[v + 1], w, BLOCK / 64, mask, m, op.rows));
-    if (w == 0) op.end(v, m, pre, acc);
+    const double acc = block_lane_sum(walk_row(op, col, off[v], off[v + 1], w, BLOCK / 64, mask, m));
+    if (w == 0) op.end(0, v, m, pre, acc);
   }
 }
 
@@ -206,8 +181,8 @@ __global__ __launch_bounds__(BLOCK) void k_bb_hubs(const int32_t *__restrict__ q
   for (int64_t i = blockIdx.x; i < hubs; i += gridDim.x) {
     const int32_t v = queue[i];
     const u64 m = qmask[i];
-    const double acc = block_lane_sum(masked_rows(col, off[v], off[v + 1], (int)blockIdx.y * (BLOCK / 64) + w,
-                                                  (int)gridDim.y * (BLOCK / 64), mask, m, op.rows));
+    const double acc = block_lane_sum(walk_row(op, col, off[v], off[v + 1], (int)blockIdx.y * (BLOCK / 64) + w,
+                                               (int)gridDim.y * (BLOCK / 64), mask, m));
     if (w == 0) part[(i * gridDim.y + blockIdx.y) * S + lane] = acc;
   }
 }
@@ -225,151 +200,21 @@ __global__ __launch_bounds__(BLOCK) void k_bb_hubs_finish(const int32_t *__restr
   const double pre = op.begin(v, m);
   double acc = 0.0;
   for (int y = 0; y < shares; ++y) acc += part[(i * shares + y) * S + lane];
-  op.end(v, m, pre, acc);
+  op.end(0, v, m, pre, acc);
 }
 
-// Queue entries [i0, i0 + k), k <= 64, by one wave.  Lane j holds entry j;
-// the entries' edges are walked as one list, 64 at a time, each lane finding
-// the entry its edge belongs to from the entries' first positions in the
-// list.  Edges stay in order, so a row's sum is finished when the owner of
-// the next contributing edge is another entry.
-template <class Op>
-__device__ __forceinline__ void rows_of_entries(const int32_t *__restrict__ queue, const u64 *__restrict__ qmask,
-                                                int64_t i0, int k, const int64_t *__restrict__ off,
-                                                const int32_t *__restrict__ col, const u64 *__restrict__ mask,
-                                                const Op &op) {
-  using T = typename Op::T;
-  const int lane = threadIdx.x & 63;
-  int32_t v = 0;
-  u64 m = 0;
-  int64_t e0 = 0, d = 0;
-  if (lane < k) {
-    v = queue[i0 + lane];
-    m = qmask[i0 + lane];
-    e0 = off[v];
-    d = off[v + 1] - e0;
-  }
-  // first list position of each entry, and the list's length
-  int64_t inc = d;
-  for (int o = 1; o < 64; o <<= 1) {
-    const int64_t y = __shfl_up((long long)inc, o, 64);
-    if (lane >= o) inc += y;
-  }
-  const int64_t total = lane_i64(inc, 63);
-  if (k == 1 || total >= ((int64_t)1 << 30)) {
-    // one entry (or rows too long for 32-bit positions): row by row
-    for (int j = 0; j < k; ++j) {
-      const int32_t vj = __builtin_amdgcn_readlane(v, j);
-      const u64 mj = lane_mask(m, j);
-      const int64_t ej = lane_i64(e0, j);
-      const double pre = op.begin(vj, mj);
-      op.end(vj, mj, pre, masked_rows(col, ej, ej + lane_i64(d, j), 0, 1, mask, mj, op.rows));
-    }
-    return;
-  }
-  const int32_t start = (int32_t)(inc - d), len = (int32_t)total;
-  int span = 1;  // search steps: the least power of two >= k
-  while (span < k) span <<= 1;
-  int cur = -1;
-  double acc = 0.0, pre = 0.0;
-  u64 open = __ballot(lane < k);
-  const auto finish = [&]() {
-    op.end(__builtin_amdgcn_readlane(v, cur), lane_mask(m, cur), pre, acc);
-    open &= ~(1ull << cur);
-  };
-  for (int32_t t0 = 0; t0 < len; t0 += 64) {
-    const int32_t t = t0 + lane;
-    int own = 0;
-    for (int h = span >> 1; h > 0; h >>= 1) {
-      const int32_t s = __shfl(start, own + h, 64);
-      if (own + h < k && s <= t) own += h;
-    }
-    const int64_t eo = __shfl((long long)e0, own, 64);
-    const int32_t so = __shfl(start, own, 64);
-    const u64 mo = (u64)__shfl((long long)m, own, 64);
-    int32_t u = -1;
-    u64 mu = 0;
-    if (t < len) {
-      u = stream_load(col + eo + (t - so));
-      mu = mask[u] & mo;
-    }
-    for (u64 todo = __ballot(mu != 0ull); todo;) {
-      T x[FLY];
-      double p[FLY];
-      int o[FLY];
-      int prev = cur;
-#pragma unroll
-      for (int q = 0; q < FLY; ++q) {
-        x[q] = (T)0;
-        p[q] = 0.0;
-        o[q] = -1;
-        if (todo) {
-          const int src = __ffsll((long long)todo) - 1;
-          todo &= todo - 1;
-          o[q] = __builtin_amdgcn_readlane(own, src);
-          if (o[q] != prev)
-            p[q] = op.begin(__builtin_amdgcn_readlane(v, o[q]), lane_mask(m, o[q]));
-          prev = o[q];
-          if ((lane_mask(mu, src) >> lane) & 1ull)
-            x[q] = op.rows[(int64_t)__builtin_amdgcn_readlane(u, src) * S + lane];
-        }
-      }
-#pragma unroll
-      for (int q = 0; q < FLY; ++q)
-        if (o[q] >= 0) {
-          if (o[q] != cur) {
-            if (cur >= 0) finish();
-            cur = o[q];
-            pre = p[q];
-            acc = 0.0;
-          }
-          acc += (double)x[q];
-        }
-    }
-  }
-  if (cur >= 0) finish();
-  // entries no neighbour contributes to (the backward pass: no child)
-  while (open) {
-    cur = __ffsll((long long)open) - 1;
-    pre = op.begin(__builtin_amdgcn_readlane(v, cur), lane_mask(m, cur));
-    acc = 0.0;
-    finish();
-  }
-}
-
-// The bins below BLOCK: queue entries [p0, p1) (WAVE bin) one to a wave,
-// [p1, p2) (G16) G16_ROWS to a wave, [p2, p3) (the rest) LOW_ROWS to a wave.
-constexpr int G16_ROWS = 4, LOW_ROWS = 16;
+// The bins below BLOCK: queue entries of the spans R.
 template <class Op>
 __global__ __launch_bounds__(BLOCK) void k_bb_rows(const int32_t *__restrict__ queue, const u64 *__restrict__ qmask,
-                                                   int64_t p0, int64_t p1, int64_t p2, int64_t p3,
-                                                   const int64_t *__restrict__ off, const int32_t *__restrict__ col,
-                                                   const u64 *__restrict__ mask, Op op) {
-  const int64_t w1 = p1 - p0, w2 = w1 + (p2 - p1 + G16_ROWS - 1) / G16_ROWS,
-                w3 = w2 + (p3 - p2 + LOW_ROWS - 1) / LOW_ROWS;
-  const int64_t nw = ((int64_t)gridDim.x * BLOCK) >> 6;
-  const int64_t mine = ((int64_t)blockIdx.x * BLOCK + threadIdx.x) >> 6;
-  for (int64_t x = mine; x < w3; x += nw) {
-    // wave-uniform: entries [i, i + k)
-    const int64_t w = lane_i64(x, 0);
-    int64_t i, end;
-    int k;
-    if (w < w1) {
-      i = p0 + w;
-      k = 1;
-      end = p1;
-    } else if (w < w2) {
-      i = p1 + (w - w1) * G16_ROWS;
-      k = G16_ROWS;
-      end = p2;
-    } else {
-      i = p2 + (w - w2) * LOW_ROWS;
-      k = LOW_ROWS;
-      end = p3;
-    }
-    if (i + k > end) k = (int)(end - i);
-    rows_of_entries(queue, qmask, i, k, off, col, mask, op);
-  }
+                                                   RowSpans R, const int64_t *__restrict__ off,
+                                                   const int32_t *__restrict__ col, const u64 *__restrict__ mask,
+                                                   Op op) {
+  for_row_spans(R, ((int64_t)blockIdx.x * BLOCK + threadIdx.x) >> 6, ((int64_t)gridDim.x * BLOCK) >> 6,
+                [&](int64_t i, int k) {
+                  Entries E;
+                  E.load([&](int64_t x) { return queue[x]; }, [&](int64_t x, int32_t) { return qmask[x]; }, i, k, off);
+                  walk_list(op, E, col, mask);
+                });
 }
 
 // The deepest level: delta is 0, so g = 1 / sigma; its masks start the
@@ -380,7 +225,7 @@ __global__ __launch_bounds__(BLOCK) void k_bb_deepest(const int32_t *__restrict_
   for (int64_t i = ((int64_t)blockIdx.x * BLOCK + threadIdx.x) >> 6; i < count; i += nw) {
     const int32_t v = queue[i];
     const u64 m = qmask[i];
-    op.end(v, m, op.begin(v, m), 0.0);
+    op.end(0, v, m, op.begin(v, m), 0.0);
   }
 }
 
@@ -398,12 +243,12 @@ __global__ __launch_bounds__(BLOCK) void k_bb_score(const float4 *__restrict__ d
   if (v < n && (t & 15) == 0 && x != 0.0) score[v] += x;
 }
 
-struct Roots {
+struct Sources {
   int32_t v[S];
 };
 
 // The sources join: their bit on the next masks, sigma 1.
-__global__ __launch_bounds__(S) void k_bb_join(u64 *next, uint32_t *touched, double *sigma, Roots roots, int count) {
+__global__ __launch_bounds__(S) void k_bb_join(u64 *next, uint32_t *touched, double *sigma, Sources roots, int count) {
   const int k = threadIdx.x;
   if (k >= count) return;
   const int32_t r = roots.v[k];
@@ -434,10 +279,9 @@ int launch_rows(const Plan &P, const int32_t *queue, const u64 *qmask, const int
     hipLaunchKernelGGL(k_bb_block<Op>, dim3((unsigned)std::min<int32_t>(split - hubs, 16384)), dim3(BLOCK), 0, s,
                        queue, qmask, hubs, split, off, col, mask, op);
   if (count > split) {
-    const int64_t p1 = P.pos[BIN_G16], p2 = P.pos[BIN_G4];
-    const int64_t waves = (p1 - split) + (p2 - p1 + G16_ROWS - 1) / G16_ROWS + (count - p2 + LOW_ROWS - 1) / LOW_ROWS;
-    hipLaunchKernelGGL(k_bb_rows<Op>, dim3((unsigned)std::min<int64_t>((waves + 3) / 4, 32768)), dim3(BLOCK), 0, s,
-                       queue, qmask, (int64_t)split, p1, p2, (int64_t)count, off, col, mask, op);
+    const RowSpans R{split, P.pos[BIN_G16], P.pos[BIN_G4], count};
+    hipLaunchKernelGGL(k_bb_rows<Op>, dim3((unsigned)std::min<int64_t>((R.waves() + 3) / 4, 32768)), dim3(BLOCK), 0, s,
+                       queue, qmask, R, off, col, mask, op);
   }
   TG_HIP(hipGetLastError());
   return TG_OK;
@@ -449,6 +293,7 @@ int launch_rows(const Plan &P, const int32_t *queue, const u64 *qmask, const int
 struct BcBatchState {
   DevArena arena;
   Workspace ws;
+  MsState *state = nullptr, *h_state = nullptr;  // device (its plan takes the place of ws.plan) and pinned copy
   int64_t n = -1;
   u64 *masks = nullptr;                // visited, front[0], front[1], next back to back
   u64 *visited = nullptr, *front[2] = {nullptr, nullptr}, *next = nullptr;
@@ -460,6 +305,9 @@ struct BcBatchState {
   double *hub_part = nullptr;    // hubs' partial sums, a row of S each
   int64_t part_rows = 0;
 
+  ~BcBatchState() {
+    if (h_state) TG_QUIET(hipHostFree(h_state));
+  }
   // Room for `need` queue entries, keeping the first `used`.
   int grow(int64_t need, int64_t used, hipStream_t s) {
     if (need <= qcap) return TG_OK;
@@ -505,6 +353,8 @@ int gpu_bc_batched(tg_partition *p, const int32_t *sources, int32_t ns, hipStrea
     B.queue_all = nullptr;
     B.qmask = nullptr;
     B.qcap = 0;
+    TG_TRY(dalloc(B.arena, &B.state, 1));
+    if (!B.h_state) TG_HIP(hipHostMalloc((void **)&B.h_state, sizeof(MsState), hipHostMallocDefault));
     TG_TRY(dalloc(B.arena, &B.masks, (size_t)n * 4));
     B.visited = B.masks;
     B.front[0] = B.masks + n;
@@ -522,15 +372,17 @@ int gpu_bc_batched(tg_partition *p, const int32_t *sources, int32_t ns, hipStrea
     B.n = g.n;
   }
   Workspace &ws = B.ws;
+  ws.plan = &B.state->plan;
   const unsigned fill_grid = 4096;
   TG_HIP(hipMemsetAsync(ws.counters, 0, 4 * sizeof(uint32_t), s));  // an earlier call's overflow flag
   for (int32_t c0 = 0; c0 < ns; c0 += S) {
     const int32_t cn = std::min<int32_t>(S, ns - c0);
     TG_HIP(hipMemsetAsync(B.masks, 0, (size_t)n * 4 * sizeof(u64), s));
     TG_HIP(hipMemsetAsync(ws.bits_a, 0, ws.nwords * sizeof(uint32_t), s));
+    TG_HIP(hipMemsetAsync(B.state, 0, sizeof(MsState), s));
     hipLaunchKernelGGL(k_bb_fill<float4>, dim3(fill_grid), dim3(BLOCK), 0, s, reinterpret_cast<float4 *>(B.delta),
                        n * S / 4, make_float4(0.f, 0.f, 0.f, 0.f));
-    Roots roots;
+    Sources roots;
     for (int32_t k = 0; k < cn; ++k) roots.v[k] = p->h_l_of_g[sources[c0 + k]];
     hipLaunchKernelGGL(k_bb_join, dim3(1), dim3(S), 0, s, B.next, ws.bits_a, B.sigma, roots, (int)cn);
     TG_HIP(hipGetLastError());
@@ -541,32 +393,44 @@ int gpu_bc_batched(tg_partition *p, const int32_t *sources, int32_t ns, hipStrea
     int cur = 0;
     TG_TRY(frontier_compact(g, ws, 1, ws.bits_a, nullptr, B.queue_all, nullptr, 0, s));
     TG_TRY(frontier_plan(g, ws, B.queue_all, t, s, false));
-    hipLaunchKernelGGL(k_bb_finalize, dim3(1), dim3(BLOCK), 0, s, ws.plan, B.queue_all, B.qmask, B.visited,
-                       B.front[cur], B.next);
-    TG_HIP(hipMemcpyAsync(ws.h_plan, ws.plan, sizeof(Plan), hipMemcpyDeviceToHost, s));
-    TG_HIP(hipStreamSynchronize(s));
     int32_t L = 0;
+    int64_t mu[S];
+    for (int64_t &x : mu) x = g.m;
+    // the level of the queue at noff: its masks, its edges per source, and
+    // the plan on the host
+    const auto settle = [&](int64_t noff, u64 *front_new, int32_t level) -> int {
+      // few blocks: each ends with an atomic per source
+      hipLaunchKernelGGL(k_bb_finalize, dim3((unsigned)std::min<int64_t>(nblk(n), 512)), dim3(BLOCK), 0, s, ws.plan,
+                         B.queue_all + noff, B.qmask + noff, B.visited, front_new, B.next, g.out.off,
+                         B.state->mf[level & 1], B.state->mf[(level + 1) & 1]);
+      TG_HIP(hipMemcpyAsync(B.h_state, B.state, sizeof(MsState), hipMemcpyDeviceToHost, s));
+      TG_HIP(hipStreamSynchronize(s));
+      return TG_OK;
+    };
+    TG_TRY(settle(0, B.front[cur], 0));
     for (;;) {
       if (L > g.n) return set_error(TG_EDEVICE, "bc_batched: more supersteps than vertices");
-      const Plan P = *ws.h_plan;
+      const Plan P = B.h_state->plan;
       plans.push_back(P);
       segoff.push_back(off);
       const int64_t noff = off + P.count;
       TG_TRY(B.grow(noff + n, noff, s));
-      if (P.vb[NBIN] > 0)
-        hipLaunchKernelGGL(k_bb_expand, dim3(launch_grid(P.vb[NBIN])), dim3(BLOCK), 0, s, ws.plan, B.queue_all + off,
-                           ws.hubpref, g.out.off, g.out.col, B.front[cur], B.visited, B.next, ws.bits_a,
-                           t.hub_chunk);
+      u64 mf[S] = {}, alive = 0;
+      for (int c = 0; c < MF_COPIES; ++c)
+        for (int k = 0; k < S; ++k) mf[k] += B.h_state->mf[L & 1][c][k];
+      for (int k = 0; k < S; ++k) {
+        if (mf[k]) alive |= 1ull << k;
+        mu[k] -= (int64_t)mf[k];
+      }
+      TG_TRY(ms_expand(g, ws, t, P, B.queue_all + off, B.front[cur], B.visited, B.next, alive,
+                       ms_pull_slots(mf, mu, alive, t), s));
       TG_TRY(frontier_compact(g, ws, 1, ws.bits_a, nullptr, B.queue_all + noff, nullptr, 0, s));
       TG_TRY(frontier_plan(g, ws, B.queue_all + noff, t, s, false));
-      hipLaunchKernelGGL(k_bb_finalize, dim3(nblk(std::min<int64_t>(n, 1 << 20))), dim3(BLOCK), 0, s, ws.plan,
-                         B.queue_all + noff, B.qmask + noff, B.visited, B.front[cur ^ 1], B.next);
-      TG_HIP(hipMemcpyAsync(ws.h_plan, ws.plan, sizeof(Plan), hipMemcpyDeviceToHost, s));
-      TG_HIP(hipStreamSynchronize(s));
+      TG_TRY(settle(noff, B.front[cur ^ 1], L + 1));
       TG_HIP(hipGetLastError());
-      if (ws.h_plan->count == 0) break;
+      if (B.h_state->plan.count == 0) break;
       const int tk = ktimer_start(s);
-      TG_TRY(launch_rows(*ws.h_plan, B.queue_all + noff, B.qmask + noff, g.in.off, g.in.col, B.front[cur],
+      TG_TRY(launch_rows(B.h_state->plan, B.queue_all + noff, B.qmask + noff, g.in.off, g.in.col, B.front[cur],
                          SigmaOp{B.sigma, ws.counters}, B.hub_part, B.part_rows, s));
       ktimer_stop(tk, s, "bcb_sigma");
       TG_HIP(hipMemsetAsync(B.front[cur], 0, (size_t)n * sizeof(u64), s));

@@ -218,7 +218,8 @@ void tg_server::run() {
         L.waiting.pop_front();
         admit(this, q);
         L.slot_q[slot] = q;
-        int rc = L.eng->join(slot, L.p->h_l_of_g[q->root], L.kind == kSlotBfs ? q->out : nullptr);
+        const int32_t root = L.p->h_l_of_g[q->root];
+        int rc = L.eng->join(slot, 1, &root);
         if (rc != TG_OK) {
           L.slot_q[slot] = nullptr;
           L.eng->busy &= ~(1ull << slot);
@@ -256,9 +257,8 @@ void tg_server::run() {
       progressed = true;
       unsigned long long f = 0;
       if (L.eng->finish_step(&f) == TG_OK && f) {
-        if (L.kind == kSlotSssp)
-          for (int k = 0; k < kSlots; ++k)
-            if ((f >> k) & 1ull) L.eng->tab.out[k] = L.slot_q[k]->out;
+        for (int k = 0; k < kSlots; ++k)
+          if ((f >> k) & 1ull) L.eng->tab.out[k] = L.slot_q[k]->out;
         unsigned long long ovf = 0;
         const int rc = L.eng->retire(f, &ovf);
         fin.emplace_back(&L, f);

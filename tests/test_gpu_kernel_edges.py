@@ -97,3 +97,120 @@ def test_components_of_long_paths(gpu):
         g = graphgen.from_edges(n + 1 + extra, src, dst, symmetrize=True)
         lab = gpu.cc(load(gpu, g)).cpu().numpy()
         assert np.array_equal(lab, oracle.cc(g.offsets, g.cols)), extra
+
+
+# ------------------------------------------------- multi-source supersteps
+
+def core_and_tail(scale, tail, hub=0, seed=3):
+    """An R-MAT core (large frontiers: pulled) with a path hung on its largest
+    vertex (small frontiers for `tail` more levels) and `hub` leaves on the
+    path's end (one row past the block sizes, far from the core)."""
+    core = graphgen.rmat(scale, seed=seed)
+    deg = np.diff(core.offsets)
+    src = np.repeat(np.arange(core.n), deg)
+    c = graphgen.max_degree_vertex(core)
+    path = np.r_[c, core.n + np.arange(tail)]
+    end = path[-1]
+    leaves = core.n + tail + np.arange(hub)
+    n = core.n + tail + hub
+    a = np.r_[src, path[:-1], np.full(hub, end)]
+    b = np.r_[core.cols, path[1:], leaves]
+    return graphgen.from_edges(n, a, b, symmetrize=True), c, int(end)
+
+
+@pytest.mark.parametrize("tail,hub", [(3, 0), (40, 700), (252, 0), (253, 0), (254, 3), (300, 9000)])
+def test_batched_levels_and_distances_past_one_byte(gpu, tail, hub):
+    """Pulled, mixed and pushed supersteps in one run, frontiers that grow
+    again after shrinking, and levels on both sides of the one-byte limit;
+    a second run on the same engine starts from its kept buffers."""
+    g, c, end = core_and_tail(9, tail, hub)
+    w = graphgen.weights(g, seed=4)
+    for tuning in (None, {"bfs_do": 0}, {"hub_min_deg": 64, "block_min_deg": 32, "wave_min_deg": 16,
+                                         "g16_min_deg": 6, "g4_min_deg": 2, "hub_chunk": 256}):
+        P = load(gpu, g, w, tuning)
+        for k, count in enumerate((64, 5, 1)):
+            roots = ([end, c] + graphgen.sample_roots(g, 62, seed=k).tolist())[:count]
+            lev = gpu.bfs_batched(P, roots).cpu().numpy()
+            dist = gpu.sssp_batched(P, roots).cpu().numpy()
+            for i in sorted({0, 1, count // 2, count - 1} & set(range(count))):
+                assert np.array_equal(lev[i], oracle.bfs(g.offsets, g.cols, roots[i])), (tuning, count, i)
+                assert np.array_equal(dist[i], oracle.sssp(g.offsets, g.cols, w, roots[i])), (tuning, count, i)
+
+
+@pytest.mark.parametrize("n", [1, 2, 63, 64, 65, 1023, 1025])
+@pytest.mark.parametrize("sym", [True, False])
+def test_batched_on_ragged_vertex_counts(gpu, n, sym):
+    rng = np.random.default_rng(n)
+    m = 5 * n
+    g = graphgen.from_edges(n, rng.integers(0, n, m), rng.integers(0, n, m), symmetrize=sym)
+    w = graphgen.weights(g, seed=5)
+    P = load(gpu, g, w)
+    roots = rng.integers(0, n, 64).tolist()
+    lev, dist = gpu.bfs_batched(P, roots).cpu().numpy(), gpu.sssp_batched(P, roots).cpu().numpy()
+    for i in range(0, 64, 7):
+        assert np.array_equal(lev[i], oracle.bfs(g.offsets, g.cols, roots[i]))
+        assert np.array_equal(dist[i], oracle.sssp(g.offsets, g.cols, w, roots[i]))
+
+
+@pytest.mark.parametrize("leaves", [3, 600])
+def test_pulled_distances_that_do_not_fit(gpu, leaves):
+    """Overflowing candidates in the pulled supersteps of a symmetric graph,
+    from rows of both splits: the verdict names the root whose distances do
+    not fit, and a candidate that overflows beside one that fits is no error."""
+    big = 2**31 - 10
+    # a clique carries the frontier; vertex 9 hangs on leaf rows by edges too
+    # heavy for anything but a direct start
+    a, b = np.triu_indices(8, 1)
+    src = np.r_[a, np.full(leaves, 8), 0, 8]
+    dst = np.r_[b, 9 + np.arange(leaves), 8, 9 + leaves]
+    g = graphgen.from_edges(10 + leaves, src, dst, symmetrize=True)
+    row = np.repeat(np.arange(g.n), np.diff(g.offsets))
+    heavy = (row == 9 + leaves) | (g.cols == 9 + leaves)
+    w = np.where(heavy, big, 1000).astype(np.int32)
+    P = load(gpu, g, w)
+    far = 9 + leaves
+    with pytest.raises(gpu.TGError) as ei:
+        gpu.sssp_batched(P, [8, 3])
+    assert ei.value.code == gpu.TG_ERANGE and "root 3" in str(ei.value)
+    ok = gpu.sssp_batched(P, [8]).cpu().numpy()[0]
+    assert ok[far] == big and ok[0] == 1000
+    # a lighter way round: the overflowing candidate no longer matters
+    g2 = graphgen.from_edges(g.n, np.r_[src, 3], np.r_[dst, far], symmetrize=True)
+    row2 = np.repeat(np.arange(g2.n), np.diff(g2.offsets))
+    pair = ((row2 == far) & (g2.cols == 8)) | ((row2 == 8) & (g2.cols == far))
+    w2 = np.where(pair, big, 1000).astype(np.int32)
+    got = gpu.sssp_batched(load(gpu, g2, w2), [8, 3, far]).cpu().numpy()
+    for i, r in enumerate((8, 3, far)):
+        assert np.array_equal(got[i], oracle.sssp(g2.offsets, g2.cols, w2, r))
+
+
+@pytest.mark.parametrize("deg", [1, 63, 64, 65, 511, 513, 2049])
+def test_batched_betweenness_rows_of_each_split(gpu, deg):
+    """Two hubs sharing `deg` middle vertices (every row sum a multiple of the
+    tile, or one off), a tail behind each, and isolated vertices."""
+    mid = 2 + np.arange(deg)
+    t = deg + 2
+    src = np.r_[np.zeros(deg, int), np.ones(deg, int), 0, t, 1, t + 2]
+    dst = np.r_[mid, mid, t, t + 1, t + 2, t + 3]
+    n = t + 6
+    for sym in (True, False):
+        g = graphgen.from_edges(n, src, dst, symmetrize=sym)
+        srcs = [0, 1, 2, t + 1, t + 3, deg + 1, n - 1] + list(range(2, min(2 + deg, 70)))
+        ref = oracle.bc(g.offsets, g.cols, srcs)
+        for tuning in (None, {"hub_min_deg": 50, "block_min_deg": 20, "wave_min_deg": 8, "g16_min_deg": 4,
+                              "g4_min_deg": 2, "hub_chunk": 256}):
+            got = gpu.bc_batched(load(gpu, g, None, tuning), srcs).cpu().numpy().astype(np.float64)
+            assert np.all(np.abs(got - ref) <= 1e-5 * np.abs(ref) + 1e-6 * max(ref.max(), 1.0)), (sym, tuning)
+
+
+def test_batched_betweenness_deep_graph_grows_its_queue(gpu):
+    """A path: every source reaches each vertex at its own level, far more
+    queue entries than vertices."""
+    n = 700
+    g = graphgen.from_edges(n, np.arange(n - 1), np.arange(1, n), symmetrize=True)
+    srcs = list(range(0, n, 11))
+    ref = oracle.bc(g.offsets, g.cols, srcs)
+    P = load(gpu, g)
+    for _ in range(2):
+        got = gpu.bc_batched(P, srcs).cpu().numpy().astype(np.float64)
+        assert np.all(np.abs(got - ref) <= 1e-5 * np.abs(ref) + 1e-6 * ref.max())
