@@ -128,7 +128,10 @@ int partition_by_degree(const tg_graph *g, int strategy, double cpu_edge_share,
  *                supersteps captured once as HIP graphs and replayed; kernel
  *                timing off only); "bfs_lds_words",
  *                "bfs_grid", "bfs_lds_min_vblocks" for the top-down steps of
- *                betweenness and hybrid searches;
+ *                betweenness and hybrid searches; "bfs_batch_roots" (fewest
+ *                roots of a call without parents that run in the 64-slot
+ *                engine of bfs_batched; 0: never, -1: by the graph's size,
+ *                the default unless another bfs_ key is given);
  *   SSSP         "sssp_delta" (0: plain frontier; > 0: near/far step),
  *                "sssp_lanes" (roots in flight, 1..8), "sssp_pull" (a
  *                superstep whose frontier holds more than this percentage
@@ -148,7 +151,8 @@ int partition_by_degree(const tg_graph *g, int strategy, double cpu_edge_share,
  *                with the split on a TG_SYMMETRIC graph: that heavy pass
  *                is pulled by the vertices whose distance is not yet final
  *                when their out-degree sum times sssp_hpull / 100 is below
- *                the bucket's; 0: always pushed);
+ *                the bucket's; 0: always pushed), "sssp_batch_roots" (as
+ *                bfs_batch_roots, for sssp_batched's engine);
  *   layout       "mapped_edges" (1: the edge arrays -- neighbour ids, weights,
  *                in-edge ids -- stay in pinned host memory mapped into the
  *                GPU and kernels read them over the host link, for graphs

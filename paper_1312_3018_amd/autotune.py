@@ -94,7 +94,8 @@ def _timed(fn) -> float:
 
 
 def measure(part, cfg, roots, sssp_roots, pr_iters, family: str, bufs, repeats: int = 2) -> float:
-    partition_retune(part, cfg)
+    # the keys searched shape the single searches
+    partition_retune(part, dict(cfg, bfs_batch_roots=0, sssp_batch_roots=0))
     lev, dist, rank = bufs
     best = math.inf
     for _ in range(repeats):

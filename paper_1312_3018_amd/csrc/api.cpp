@@ -334,6 +334,7 @@ Tuning default_tuning() {
   t.sssp_hpull = 100;
   t.bfs_graph = 0;  // replaying captured chunks measured 1-2% slower than direct launches
   t.mapped_edges = 0;
+  t.bfs_batch_roots = t.sssp_batch_roots = -1;
   return t;
 }
 
@@ -385,6 +386,12 @@ int parse_tuning(const char *json, Tuning *t) {
   if (json_int(json, "sssp_hpull", &v)) t->sssp_hpull = v;
   if (json_int(json, "bfs_graph", &v)) t->bfs_graph = v;
   if (json_int(json, "mapped_edges", &v)) t->mapped_edges = v;
+  if (strstr(json, "\"bfs_")) t->bfs_batch_roots = 0;
+  if (strstr(json, "\"sssp_")) t->sssp_batch_roots = 0;
+  if (json_int(json, "bfs_batch_roots", &v)) t->bfs_batch_roots = v;
+  if (json_int(json, "sssp_batch_roots", &v)) t->sssp_batch_roots = v;
+  if (t->bfs_batch_roots < -1 || t->sssp_batch_roots < -1)
+    return set_error(TG_EINVAL, "tuning: bfs_batch_roots and sssp_batch_roots must be >= -1");
   if (t->mapped_edges != 0 && t->mapped_edges != 1) return set_error(TG_EINVAL, "tuning: mapped_edges must be 0 or 1");
   if (t->bfs_graph != 0 && t->bfs_graph != 1) return set_error(TG_EINVAL, "tuning: bfs_graph must be 0 or 1");
   if (t->sssp_pull < 0 || t->sssp_pull > 100) return set_error(TG_EINVAL, "tuning: sssp_pull must be in [0, 100]");
@@ -1006,7 +1013,8 @@ extern "C" int partition_info(const tg_partition *p, char *json, size_t cap) {
            "\"pr_grid\":%lld,\"bfs_lds_words\":%lld,\"bfs_grid\":%lld,\"bfs_lds_min_vblocks\":%lld,"
            "\"sssp_delta\":%lld,\"sssp_lds_verts\":%lld,\"sssp_grid\":%lld,\"pr_xcd\":%lld,\"pr_rows\":%lld,"
            "\"bfs_do\":%lld,\"bfs_alpha\":%lld,\"bfs_beta\":%lld,\"sssp_xcd\":%lld,\"bfs_lanes\":%lld,"
-           "\"bfs_td_grid\":%lld,\"bfs_bu_grid\":%lld,\"sssp_pull\":%lld,\"sssp_lanes\":%lld,\"bfs_graph\":%lld,\"mapped_edges\":%lld,\"sssp_packed\":%lld,\"sssp_ring\":%lld,\"sssp_split\":%lld,\"sssp_hpull\":%lld}",
+           "\"bfs_td_grid\":%lld,\"bfs_bu_grid\":%lld,\"sssp_pull\":%lld,\"sssp_lanes\":%lld,\"bfs_graph\":%lld,\"mapped_edges\":%lld,\"sssp_packed\":%lld,\"sssp_ring\":%lld,\"sssp_split\":%lld,\"sssp_hpull\":%lld,"
+           "\"bfs_batch_roots\":%lld,\"sssp_batch_roots\":%lld}",
            (long long)p->tune.min_deg[0], (long long)p->tune.min_deg[1], (long long)p->tune.min_deg[2],
            (long long)p->tune.min_deg[3], (long long)p->tune.min_deg[4], (long long)p->tune.hub_chunk,
            (long long)p->tune.pr_lds_verts, (long long)p->tune.pr_grid, (long long)p->tune.bfs_lds_words,
@@ -1016,7 +1024,8 @@ extern "C" int partition_info(const tg_partition *p, char *json, size_t cap) {
            (long long)p->tune.bfs_beta, (long long)p->tune.sssp_xcd, (long long)p->tune.bfs_lanes,
            (long long)p->tune.bfs_td_grid, (long long)p->tune.bfs_bu_grid, (long long)p->tune.sssp_pull,
            (long long)p->tune.sssp_lanes, (long long)p->tune.bfs_graph, (long long)p->tune.mapped_edges,
-           (long long)p->tune.sssp_packed, (long long)p->tune.sssp_ring, (long long)p->tune.sssp_split, (long long)p->tune.sssp_hpull);
+           (long long)p->tune.sssp_packed, (long long)p->tune.sssp_ring, (long long)p->tune.sssp_split, (long long)p->tune.sssp_hpull,
+           (long long)p->tune.bfs_batch_roots, (long long)p->tune.sssp_batch_roots);
   s += buf;
   s += ",\"tuning_source\":\"" + p->tuning_source + "\"";
   s += hybrid_info_json(p);
@@ -1043,6 +1052,41 @@ int check_roots(const tg_partition *p, const int32_t *roots, int32_t nr, const c
   return TG_OK;
 }
 
+// Calls with several roots: the 64-slot engine streams an edge once for all
+// of them, the single searches keep up to four in flight.  The lines below
+// are where the two met (ms, single / engine).
+//
+// BFS (levels only).  2 roots: 2^13..2^20 vertices 0.49-0.72 / 0.25-0.67,
+// RMAT-22 0.63 / 1.01; 4 roots: RMAT-22 1.09 / 1.10, RMAT-23 1.61 / 2.61; 8:
+// RMAT-23 3.74 / 3.06, RMAT-24 3.78 / 3.29; 64: RMAT-22 22.5 / 3.84, RMAT-24
+// 28.1 / 10.9.
+bool bfs_in_engine(const tg_partition *p, int32_t nr) {
+  const int64_t from = p->tune.bfs_batch_roots, n = p->gpu.n;
+  if (from >= 0) return from > 0 && nr >= from;
+  return nr >= (n <= (1 << 20) ? 2 : n <= (1 << 22) ? 4 : 8);
+}
+
+// SSSP.  The engine relaxes every active (vertex, root) pair each superstep,
+// the single searches' buckets do less work per root but in many more
+// supersteps.  1 root: 2^13..2^19 vertices 2.0-3.0 / 0.7-2.4, RMAT-20 3.28 /
+// 3.98; 4: RMAT-21 8.65 / 8.53; 8: RMAT-22 14.2 / 19.0; 16: RMAT-22 28.0 /
+// 19.6, RMAT-23 41.8 / 39.7, RMAT-24 67 / 83; 32: RMAT-24 134 / 99; 64:
+// RMAT-24 271 / 106.  Directed graphs (no pulled supersteps there): 4 roots:
+// RMAT-20 4.90 / 6.02; 8: 9.83 / 7.52, RMAT-21 11.7 / 11.5; 16: RMAT-22 28.9 /
+// 25.2.
+bool sssp_in_engine(const tg_partition *p, int32_t nr) {
+  const int64_t from = p->tune.sssp_batch_roots;
+  if (from >= 0) return from > 0 && nr >= from;
+  int lg = 0;  // n <= 2^lg
+  while (((int64_t)1 << lg) < p->gpu.n) ++lg;
+  return nr >= 4 * (lg - (p->gpu.in_alias ? 19 : 18));
+}
+
+// Betweenness, one source at a time / 64 in a chain: 2 sources: 2^12..2^20
+// vertices 0.64-3.11 / 0.54-2.56; RMAT-22, 2: 6.7 / 7.3, 3: 10.5 / 8.0, 16:
+// 61.8 / 11.1.
+bool bc_in_chain(const tg_partition *p, int32_t ns) { return ns >= 2 + (p->gpu.n >> 22); }
+
 }  // namespace
 
 extern "C" int bfs(const tg_partition *pc, const int32_t *roots, int32_t num_roots, int32_t *levels,
@@ -1055,9 +1099,23 @@ extern "C" int bfs(const tg_partition *pc, const int32_t *roots, int32_t num_roo
   stats_reset("bfs");
   ktimer_reset();
   if (p->alpha > 0.0) return hybrid_bfs(p, roots, num_roots, levels, parents, s);
+  int64_t supersteps = 0;
+  if (!parents && bfs_in_engine(p, num_roots)) {
+    const int rc = slots_run_batch(p, kSlotBfs, roots, num_roots, levels, s, &supersteps);
+    if (rc == TG_OK) {
+      TG_HIP(hipStreamSynchronize(s));
+      stats_add("roots", num_roots);
+      stats_add("supersteps", (double)supersteps);
+      ktimer_emit();
+    }
+    // no room for the engine's rows: the single searches need less
+    if (rc != TG_ENOMEM) return rc;
+    slots_drop(p, kSlotBfs);
+    clear_error();
+    supersteps = 0;
+  }
   std::vector<int32_t> local((size_t)num_roots);
   for (int32_t r = 0; r < num_roots; ++r) local[r] = p->h_l_of_g[roots[r]];
-  int64_t supersteps = 0;
   TG_TRY(gpu_bfs_roots(p, local.data(), num_roots, levels, parents, s, &supersteps));
   // counters of every lane (the other lanes' work is ordered before s)
   const int nl = bfs_lane_count(p->tune, num_roots);
@@ -1093,6 +1151,22 @@ extern "C" int sssp(const tg_partition *pc, const int32_t *roots, int32_t num_ro
   ktimer_reset();
   if (p->alpha > 0.0) return hybrid_sssp(p, roots, num_roots, dist, s);
   int64_t rounds_total = 0, pulls_total = 0;
+  if (sssp_in_engine(p, num_roots)) {
+    const int rc = slots_run_batch(p, kSlotSssp, roots, num_roots, dist, s, &rounds_total);
+    if (rc == TG_ERANGE) return set_error(rc, "sssp: a shortest-path distance does not fit below INT32_MAX");
+    if (rc == TG_OK) {
+      TG_HIP(hipStreamSynchronize(s));
+      stats_add("roots", num_roots);
+      stats_add("supersteps", (double)rounds_total);
+      stats_add("pull_supersteps", 0.0);
+      ktimer_emit();
+    }
+    // no room for the engine's rows: the single searches need less
+    if (rc != TG_ENOMEM) return rc;
+    slots_drop(p, kSlotSssp);
+    clear_error();
+    rounds_total = 0;
+  }
   std::vector<int32_t> local((size_t)num_roots);
   for (int32_t r = 0; r < num_roots; ++r) local[r] = p->h_l_of_g[roots[r]];
   TG_TRY(gpu_sssp_roots(p, local.data(), num_roots, dist, s, &rounds_total, &pulls_total));
@@ -1158,6 +1232,22 @@ extern "C" int bc(const tg_partition *pc, const int32_t *sources, int32_t num_so
   TG_TRY(p->ws.ensure(p->gpu, 0));
   TG_TRY(fill_f64(p->ws.bc_acc, p->gpu.n, 0.0, s));
   TG_HIP(hipMemsetAsync(p->ws.counters, 0, 64 * sizeof(uint32_t), s));
+  if (bc_in_chain(p, num_sources)) {
+    const int rc = gpu_bc_batched(p, sources, num_sources, s);
+    if (rc == TG_ERANGE) return set_error(rc, "bc: a shortest-path count reached 2^53");
+    if (rc != TG_OK && rc != TG_ENOMEM) return rc;
+    if (rc == TG_OK) {
+      TG_TRY(collect_f64_to_f32(p->gpu, p->ws.bc_acc, scores, s));
+      TG_HIP(hipStreamSynchronize(s));
+      stats_add("sources", num_sources);
+      ktimer_emit();
+      return TG_OK;
+    }
+    // no room for the chain's rows: one source at a time needs less
+    bcb_free(p);
+    clear_error();
+    TG_TRY(fill_f64(p->ws.bc_acc, p->gpu.n, 0.0, s));
+  }
   for (int32_t i = 0; i < num_sources; ++i) TG_TRY(gpu_bc_source(p, p->h_l_of_g[sources[i]], s));
   TG_TRY(collect_f64_to_f32(p->gpu, p->ws.bc_acc, scores, s));
   TG_HIP(hipMemcpyAsync(p->ws.h_flags, p->ws.counters, 4 * sizeof(uint32_t), hipMemcpyDeviceToHost, s));

@@ -75,5 +75,7 @@ struct SlotEngine {
 
 int slots_run_batch(tg_partition *p, int kind, const int32_t *roots, int32_t nr, int32_t *out, hipStream_t s,
                     int64_t *supersteps_out);
+// Give the engine of `kind` and its buffers back.
+void slots_drop(tg_partition *p, int kind);
 
 }  // namespace tg

@@ -921,6 +921,11 @@ int SlotEngine::retire(u64 mask, u64 *overflow) {
   return TG_OK;
 }
 
+void slots_drop(tg_partition *p, int kind) {
+  delete p->slots[kind];
+  p->slots[kind] = nullptr;
+}
+
 // Batched BFS / SSSP from a fixed list of roots: chunks of 64 slots that all
 // join at superstep 0 and retire together.
 int slots_run_batch(tg_partition *p, int kind, const int32_t *roots, int32_t nr, int32_t *out, hipStream_t s,

@@ -99,6 +99,10 @@ struct Tuning {
                                  // vertices' degree sum times this percent is below the members' (0: always push)
   int64_t bfs_graph;             // BFS: 1 = chunks of supersteps replayed as captured HIP graphs
   int64_t mapped_edges;          // partition build: 1 = edge arrays in mapped host memory
+  // fewest roots of a bfs() / sssp() call that run in the 64-slot engine
+  // (-1: by the graph's size, 0: never; a tuning that names any other key of
+  // the algorithm asks for that schedule, so there the default is 0)
+  int64_t bfs_batch_roots, sssp_batch_roots;
 };
 Tuning default_tuning();
 int parse_tuning(const char *json, Tuning *t);

@@ -214,3 +214,41 @@ def test_batched_betweenness_deep_graph_grows_its_queue(gpu):
     for _ in range(2):
         got = gpu.bc_batched(P, srcs).cpu().numpy().astype(np.float64)
         assert np.all(np.abs(got - ref) <= 1e-5 * np.abs(ref) + 1e-6 * ref.max())
+
+
+# ------------------------------------- calls routed to the 64-slot engines
+
+@pytest.mark.parametrize("sym", [True, False])
+@pytest.mark.parametrize("count", [0, 1, 2, 3, 4, 8, 63, 64, 65, 130])
+def test_engine_and_single_searches_agree(gpu, sym, count):
+    """bfs, sssp and bc with the engines chosen by rule, forced and refused:
+    repeated and isolated roots, chunks of 64 and their remainders."""
+    g = graphgen.rmat(11, symmetrize=sym, seed=6)
+    w = graphgen.weights(g, seed=7)
+    iso = int(np.argmin(np.diff(g.offsets)))
+    roots = (graphgen.sample_roots(g, 60, seed=9).tolist() + [iso, iso, 5, 5] + list(range(100)))[:count]
+    ref_l = ref_d = None
+    for tuning in ({"bfs_batch_roots": 0, "sssp_batch_roots": 0}, None, {"bfs_batch_roots": 1, "sssp_batch_roots": 1},
+                   {"bfs_lanes": 2, "sssp_lanes": 2}):
+        P = load(gpu, g, w, tuning)
+        lev, dist = gpu.bfs(P, roots).cpu().numpy(), gpu.sssp(P, roots).cpu().numpy()
+        if ref_l is None:
+            ref_l, ref_d = lev, dist
+            for i in range(0, count, 16):
+                assert np.array_equal(lev[i], oracle.bfs(g.offsets, g.cols, roots[i]))
+                assert np.array_equal(dist[i], oracle.sssp(g.offsets, g.cols, w, roots[i]))
+        assert np.array_equal(lev, ref_l) and np.array_equal(dist, ref_d), tuning
+    got = gpu.bc(P, roots).cpu().numpy().astype(np.float64)
+    ref = oracle.bc(g.offsets, g.cols, roots)
+    assert np.all(np.abs(got - ref) <= 1e-5 * np.abs(ref) + 1e-6 * max(np.abs(ref).max(), 1.0))
+
+
+def test_overflow_verdict_is_the_same_on_both_routes(gpu):
+    g = graphgen.from_edges(3, [0, 1], [1, 2], symmetrize=True)
+    w = np.full(g.nnz, 2**31 - 10, dtype=np.int32)
+    for tuning in ({"sssp_batch_roots": 0}, {"sssp_batch_roots": 1}, None):
+        P = load(gpu, g, w, tuning)
+        with pytest.raises(gpu.TGError) as ei:
+            gpu.sssp(P, [1, 0])
+        assert ei.value.code == gpu.TG_ERANGE
+        assert gpu.sssp(P, [1]).cpu().numpy().tolist() == [[2**31 - 10, 0, 2**31 - 10]]
