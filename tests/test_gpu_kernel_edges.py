@@ -231,6 +231,13 @@ def test_engine_and_single_searches_agree(gpu, sym, count):
     for tuning in ({"bfs_batch_roots": 0, "sssp_batch_roots": 0}, None, {"bfs_batch_roots": 1, "sssp_batch_roots": 1},
                    {"bfs_lanes": 2, "sssp_lanes": 2}):
         P = load(gpu, g, w, tuning)
+        if count == 0:
+            # an empty output has no address: refused on either route
+            for call in (gpu.bfs, gpu.sssp):
+                with pytest.raises(gpu.TGError) as ei:
+                    call(P, roots)
+                assert ei.value.code == gpu.TG_EINVAL
+            continue
         lev, dist = gpu.bfs(P, roots).cpu().numpy(), gpu.sssp(P, roots).cpu().numpy()
         if ref_l is None:
             ref_l, ref_d = lev, dist
