@@ -954,6 +954,7 @@ extern "C" void partition_free(tg_partition *p) {
   delete p->slots[0];
   delete p->slots[1];
   bcb_free(p);
+  small_free(p);
   pr_slices_free(p->gpu);
   pr_rows_free(p->gpu);
   sssp_slices_free(p->gpu);
@@ -1066,6 +1067,11 @@ bool bfs_in_engine(const tg_partition *p, int32_t nr) {
   return nr >= (n <= (1 << 20) ? 2 : n <= (1 << 22) ? 4 : 8);
 }
 
+// Small graphs: a workgroup per root in one launch.
+bool bfs_in_workgroups(const tg_partition *p, int32_t nr) {
+  return p->tune.bfs_batch_roots < 0 && small_bfs_supported(p->gpu) && nr > 0;
+}
+
 // SSSP.  The engine relaxes every active (vertex, root) pair each superstep,
 // the single searches' buckets do less work per root but in many more
 // supersteps.  1 root: 2^13..2^19 vertices 2.0-3.0 / 0.7-2.4, RMAT-20 3.28 /
@@ -1100,6 +1106,21 @@ extern "C" int bfs(const tg_partition *pc, const int32_t *roots, int32_t num_roo
   ktimer_reset();
   if (p->alpha > 0.0) return hybrid_bfs(p, roots, num_roots, levels, parents, s);
   int64_t supersteps = 0;
+  if (bfs_in_workgroups(p, num_roots)) {
+    bool deep = false;
+    const int rc = small_bfs(p, roots, num_roots, levels, parents, s, &supersteps, &deep);
+    if (rc != TG_OK && rc != TG_ENOMEM) return rc;
+    if (rc == TG_ENOMEM) {
+      small_free(p);
+      clear_error();
+    } else if (!deep) {
+      stats_add("roots", num_roots);
+      stats_add("supersteps", (double)supersteps);
+      ktimer_emit();
+      return TG_OK;
+    }
+    supersteps = 0;
+  }
   if (!parents && bfs_in_engine(p, num_roots)) {
     const int rc = slots_run_batch(p, kSlotBfs, roots, num_roots, levels, s, &supersteps);
     if (rc == TG_OK) {

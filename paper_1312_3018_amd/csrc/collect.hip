@@ -66,13 +66,13 @@ __global__ __launch_bounds__(BLOCK) void k_parents(const int32_t *__restrict__ g
                                                    int32_t *__restrict__ out) {
   const int lane = threadIdx.x & 63, sub = lane & 3;
   const int64_t v = (((int64_t)blockIdx.x * BLOCK + threadIdx.x) >> 6) * 16 + (lane >> 2);
-  const auto at = [&](int32_t u, int32_t want) {
-    return ((visited[u >> 5] >> (u & 31)) & 1u) && level[u] == want;
-  };
+  // (without bits, unvisited vertices have level TG_INF)
+  const auto seen = [&](int64_t u) { return visited ? ((visited[u >> 5] >> (u & 31)) & 1u) != 0u : level[u] != TG_INF; };
+  const auto at = [&](int32_t u, int32_t want) { return (!visited || seen(u)) && level[u] == want; };
   int32_t best = -1, want = 0;
   int64_t e0 = 0, e1 = 0;
   bool open = false;
-  if (v < n && ((visited[v >> 5] >> (v & 31)) & 1u)) {
+  if (v < n && seen(v)) {
     want = level[v] - 1;
     if (want <= 0) {
       best = root;

@@ -1,0 +1,317 @@
+// Searches whose cost is launches and waits, not edges: breadth-first search
+// on small graphs, one workgroup per root in one launch, and shortest paths
+// for a few roots, one launch per round for all of them.
+#include <algorithm>
+#include <vector>
+
+#include "ms.h"
+
+using namespace tgk;
+
+namespace tg {
+namespace {
+
+// ------------------------------------------------------------------- BFS
+//
+// The whole search runs in one 1024-thread workgroup with its bitmaps and
+// byte levels in LDS, so a level costs barriers and load latency (2-10 us)
+// instead of four launches and a share of a host wait.  Top-down levels walk
+// an LDS queue, a wave per vertex; bottom-up levels (Beamer's switch) give a
+// lane to each unvisited vertex: its first four in-neighbours with one
+// 16-byte load, twelve more from its row, then the wave takes the rows still
+// open.  Many roots are as many workgroups.  RMAT-14, one root with parents:
+// 298 us a call through the launched supersteps, 88 so; 64 roots: 419 in the
+// 64-slot engine, 96 so.  (Four vertices per lane in flight in the bottom-up
+// levels were slower, 114: the registers of 16 waves do not hold them.)
+constexpr int BT = 1024;
+constexpr int64_t SMALL_BFS_MAX_N = 65536;
+constexpr int QMAX = 1024;      // largest frontier walked top-down
+constexpr int MAX_BYTE = 254;   // deepest level kept in a byte
+
+struct SmallBfsArgs {
+  const int64_t *off;
+  const int32_t *col;
+  const int32_t *ioff32;
+  const int64_t *ioff64;
+  const int32_t *icol;
+  const int4 *head;
+  const int32_t *l_of_g;
+  const int32_t *roots;  // local
+  int32_t *state;        // [roots][n] levels by local id
+  int32_t *out;          // [roots][V] levels by original id
+  int64_t *info;         // [roots]: supersteps, or -1: deeper than a byte holds
+  int64_t n, V, m, n_in;
+  int64_t alpha, beta;
+  int do_switch;
+};
+
+// Lane-wide append of the lanes with `add` to the LDS queue.
+__device__ __forceinline__ void push_lanes(bool add, int32_t v, int32_t *queue, uint32_t *count) {
+  const uint64_t m = __ballot(add);
+  if (!m) return;
+  const int lane = threadIdx.x & 63;
+  uint32_t base = 0;
+  if (lane == __ffsll((long long)m) - 1) base = atomicAdd(count, (uint32_t)__popcll(m));
+  base = __shfl(base, __ffsll((long long)m) - 1, 64);
+  const uint32_t at = base + (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
+  if (add && at < QMAX) queue[at] = v;
+}
+
+__global__ __launch_bounds__(BT) void k_bfs_small(const SmallBfsArgs A) {
+  extern __shared__ uint32_t lds[];
+  const int W = (int)((A.n + 63) / 64) * 2;  // bitmap words: whole pairs
+  uint32_t *vis = lds, *fr = vis + W, *nx = fr + W;
+  int32_t *qa = reinterpret_cast<int32_t *>(nx + W), *qb = qa + QMAX;
+  uint8_t *lev = reinterpret_cast<uint8_t *>(qb + QMAX);
+  __shared__ uint32_t count;            // vertices that joined this superstep
+  __shared__ unsigned long long edges;  // their out-degrees
+  const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
+  const int32_t root = A.roots[blockIdx.x];
+  for (int i = t; i < W; i += BT) vis[i] = fr[i] = nx[i] = 0u;
+  __syncthreads();
+  if (t == 0) {
+    vis[root >> 5] = fr[root >> 5] = 1u << (root & 31);
+    lev[root] = 0;
+    qa[0] = root;
+  }
+  int64_t m_u = A.m, m_f = A.off[root + 1] - A.off[root];
+  int64_t n_f = 1;
+  int L = 0, bu = 0;
+  bool queued = true;  // qa holds the frontier
+  for (;; ++L) {
+    if (L >= MAX_BYTE) {
+      if (t == 0) A.info[blockIdx.x] = -1;
+      return;
+    }
+    m_u -= m_f;
+    if (A.do_switch) {
+      if (!bu && m_f > m_u / A.alpha) bu = 1;
+      else if (bu && n_f < A.n / A.beta) bu = 0;
+    }
+    // a frontier beyond the queue can only be looked for (every level of a
+    // graph without in-edges beyond the bottom-up rows would be empty)
+    const bool up = bu || n_f > QMAX;
+    __syncthreads();
+    if (t == 0) {
+      count = 0u;
+      edges = 0ull;
+    }
+    if (!up && !queued) {
+      // the queue of a frontier that a bottom-up level found
+      __syncthreads();
+      for (int i0 = wv * 64; i0 < W; i0 += BT) {
+        uint32_t w = i0 + lane < W ? fr[i0 + lane] : 0u;
+        while (__ballot(w != 0u)) {
+          push_lanes(w != 0u, w ? (i0 + lane) * 32 + __ffs(w) - 1 : 0, qa, &count);
+          w &= w - 1u;
+        }
+      }
+      __syncthreads();
+      if (t == 0) count = 0u;
+    }
+    __syncthreads();
+    unsigned long long deg = 0;
+    if (!up) {
+      for (int i = wv; i < (int)n_f; i += BT / 64) {
+        const int32_t v = qa[i];
+        const int64_t e0 = A.off[v], e1 = A.off[v + 1];
+        for (int64_t e = e0; e < e1; e += 256) {
+          int32_t nb[4];
+#pragma unroll
+          for (int k = 0; k < 4; ++k) nb[k] = e + k * 64 + lane < e1 ? A.col[e + k * 64 + lane] : -1;
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            bool won = false;
+            if (nb[k] >= 0) {
+              const uint32_t bit = 1u << (nb[k] & 31);
+              if (!(vis[nb[k] >> 5] & bit)) won = !(atomicOr(vis + (nb[k] >> 5), bit) & bit);
+            }
+            if (won) {
+              atomicOr(nx + (nb[k] >> 5), 1u << (nb[k] & 31));
+              lev[nb[k]] = (uint8_t)(L + 1);
+              deg += (unsigned long long)(A.off[nb[k] + 1] - A.off[nb[k]]);
+            }
+            push_lanes(won, nb[k], qb, &count);
+          }
+        }
+      }
+    } else {
+      uint32_t joined = 0;
+      const auto in = [&](int32_t u) { return u >= 0 && ((fr[u >> 5] >> (u & 31)) & 1u); };
+      for (int64_t v0 = wv * 64; v0 < A.n_in; v0 += BT) {
+        const int64_t v = v0 + lane;
+        const bool open = v < A.n_in && !((vis[v >> 5] >> (v & 31)) & 1u);
+        bool hit = false;
+        int64_t e = 0, e1 = 0;
+        if (open) {
+          const int4 h = A.head[v];
+          hit = in(h.x) || in(h.y) || in(h.z) || in(h.w);
+          if (!hit && h.w >= 0) {
+            e = (A.ioff32 ? (int64_t)A.ioff32[v] : A.ioff64[v]) + 4;
+            e1 = A.ioff32 ? (int64_t)A.ioff32[v + 1] : A.ioff64[v + 1];
+            for (int r = 0; r < 3 && e < e1 && !hit; ++r, e += 4) {
+              int32_t u[4];
+#pragma unroll
+              for (int k = 0; k < 4; ++k) u[k] = A.icol[e + k < e1 ? e + k : e1 - 1];
+              hit = in(u[0]) || in(u[1]) || in(u[2]) || in(u[3]);
+            }
+          }
+        }
+        for (uint64_t todo = __ballot(!hit && e < e1); todo; todo &= todo - 1) {
+          const int src = __ffsll((long long)todo) - 1;
+          const int64_t a1 = lane_i64(e1, src);
+          bool found = false;
+          for (int64_t b = lane_i64(e, src); b < a1 && !found; b += 256) {
+            int32_t u[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) u[k] = b + k * 64 + lane < a1 ? A.icol[b + k * 64 + lane] : -1;
+            found = __ballot(in(u[0]) || in(u[1]) || in(u[2]) || in(u[3])) != 0ull;
+          }
+          if (lane == src) hit = found;
+        }
+        const uint64_t m = __ballot(hit);
+        if (m) {
+          // the wave's own two words
+          if (lane == 0) nx[v0 >> 5] = (uint32_t)m;
+          if (lane == 1) nx[(v0 >> 5) + 1] = (uint32_t)(m >> 32);
+          joined += (uint32_t)__popcll(m);
+          if (hit) {
+            lev[v] = (uint8_t)(L + 1);
+            deg += (unsigned long long)(A.off[v + 1] - A.off[v]);
+          }
+        }
+      }
+      if (lane == 0 && joined) atomicAdd(&count, joined);
+    }
+    deg = wave_sum(deg);
+    if (lane == 0 && deg) atomicAdd(&edges, deg);
+    __syncthreads();
+    n_f = count;
+    m_f = (int64_t)edges;
+    queued = !up;
+    if (n_f == 0) break;
+    for (int i = t; i < W; i += BT) {
+      const uint32_t x = nx[i];
+      fr[i] = x;
+      nx[i] = 0u;
+      if (up) vis[i] |= x;
+    }
+    int32_t *q = qa;
+    qa = qb;
+    qb = q;
+  }
+  // (the barrier above ordered every level written)
+  int32_t *state = A.state + (int64_t)blockIdx.x * A.n;
+  for (int64_t v = t; v < A.n; v += BT) state[v] = (vis[v >> 5] >> (v & 31)) & 1u ? (int32_t)lev[v] : TG_INF;
+  int32_t *out = A.out + (int64_t)blockIdx.x * A.V;
+  for (int64_t gid = t; gid < A.V; gid += BT) {
+    const int32_t l = A.l_of_g[gid];
+    out[gid] = (vis[l >> 5] >> (l & 31)) & 1u ? (int32_t)lev[l] : TG_INF;
+  }
+  if (t == 0) A.info[blockIdx.x] = L + 1;
+}
+
+size_t small_bfs_lds(int64_t n) {
+  const size_t W = (size_t)((n + 63) / 64) * 2;
+  return W * 3 * 4 + 2 * QMAX * 4 + (size_t)((n + 15) & ~(int64_t)15);
+}
+
+}  // namespace
+
+// Scratch of both searches (lazy, per partition): per root a row of vertex
+// state, and a few words per root.
+struct SmallState {
+  DevArena arena;
+  int64_t rows = 0;        // entries of `state`
+  int32_t *state = nullptr;
+  int32_t *settled = nullptr;
+  uint32_t *ovf = nullptr;
+  int32_t *roots = nullptr;
+  int64_t *info = nullptr;
+  int32_t *h_roots = nullptr;
+  int64_t *h_info = nullptr;
+  ~SmallState() {
+    if (h_roots) TG_QUIET(hipHostFree(h_roots));
+    if (h_info) TG_QUIET(hipHostFree(h_info));
+  }
+};
+
+void small_free(tg_partition *p) {
+  delete p->small;
+  p->small = nullptr;
+}
+
+namespace {
+
+constexpr int64_t CHUNK = 64;  // roots per launch
+
+int small_state(tg_partition *p, int64_t rows, SmallState **out) {
+  if (!p->small) {
+    p->small = new (std::nothrow) SmallState();
+    if (!p->small) return set_error(TG_ENOMEM, "out of host memory");
+  }
+  SmallState &S = *p->small;
+  if (!S.roots) {
+    TG_TRY(dalloc(S.arena, &S.roots, (size_t)CHUNK));
+    TG_TRY(dalloc(S.arena, &S.info, (size_t)CHUNK));
+    TG_HIP(hipHostMalloc((void **)&S.h_roots, CHUNK * sizeof(int32_t), hipHostMallocDefault));
+    TG_HIP(hipHostMalloc((void **)&S.h_info, CHUNK * sizeof(int64_t), hipHostMallocDefault));
+  }
+  if (S.rows < rows) {
+    if (S.state) S.arena.release_one(S.state);
+    S.state = nullptr;
+    S.rows = 0;
+    TG_TRY(dalloc(S.arena, &S.state, (size_t)rows));
+    S.rows = rows;
+  }
+  *out = &S;
+  return TG_OK;
+}
+
+}  // namespace
+
+// (us, launched single search or engine, whichever is less / one workgroup
+// per root, 1 and 64 roots: R-MAT 2^12 221, 400 / 51, 51; 2^14 189, 419 / 84,
+// 96; 2^16 189, 584 / 186, 224; uniform 2^13 240, 328 / 92, 104; 2^16 296, 441
+// / 385, 434: without hubs most rows are read to their end, and one CU is too
+// few for them.)
+bool small_bfs_supported(const GpuPart &g) {
+  if (g.n <= 0 || small_bfs_lds(g.n) > (size_t)rows_lds_limit()) return false;
+  const bool hubs = g.h_deg[0] * g.n >= 16 * g.m;  // largest degree at least 16 times the mean
+  return g.n <= (hubs ? SMALL_BFS_MAX_N : SMALL_BFS_MAX_N / 2);
+}
+
+int small_bfs(tg_partition *p, const int32_t *roots, int32_t nr, int32_t *levels, int32_t *parents, hipStream_t s,
+              int64_t *supersteps, bool *deep) {
+  const GpuPart &g = p->gpu;
+  const Tuning &t = p->tune;
+  SmallState *S = nullptr;
+  TG_TRY(small_state(p, std::min<int64_t>(nr, CHUNK) * g.n, &S));
+  *deep = false;
+  for (int64_t c0 = 0; c0 < nr; c0 += CHUNK) {
+    const int64_t cn = std::min<int64_t>(CHUNK, nr - c0);
+    for (int64_t k = 0; k < cn; ++k) S->h_roots[k] = p->h_l_of_g[roots[c0 + k]];
+    TG_HIP(hipMemcpyAsync(S->roots, S->h_roots, (size_t)cn * sizeof(int32_t), hipMemcpyHostToDevice, s));
+    SmallBfsArgs A{g.out.off, g.out.col, g.in_off32, g.in.off, g.in.col, reinterpret_cast<const int4 *>(g.in_head),
+                   g.l_of_g, S->roots, S->state, levels + c0 * g.n_global, S->info, g.n, g.n_global, g.m,
+                   g.in_alias ? g.out_bins.bstart[BIN_ZERO] : g.n, t.bfs_alpha, t.bfs_beta, (int)t.bfs_do};
+    const int tk = ktimer_start(s);
+    hipLaunchKernelGGL(k_bfs_small, dim3((unsigned)cn), dim3(BT), small_bfs_lds(g.n), s, A);
+    ktimer_stop(tk, s, "bfs_small");
+    TG_HIP(hipGetLastError());
+    if (parents)
+      for (int64_t k = 0; k < cn; ++k)
+        TG_TRY(bfs_parents(g, nullptr, S->state + k * g.n, S->h_roots[k], parents + (c0 + k) * g.n_global, s));
+    TG_HIP(hipMemcpyAsync(S->h_info, S->info, (size_t)cn * sizeof(int64_t), hipMemcpyDeviceToHost, s));
+    TG_HIP(hipStreamSynchronize(s));
+    ktimer_flush();
+    for (int64_t k = 0; k < cn; ++k) {
+      if (S->h_info[k] < 0) *deep = true;
+      else *supersteps += S->h_info[k];
+    }
+    if (*deep) return TG_OK;
+  }
+  return TG_OK;
+}
+
+}  // namespace tg

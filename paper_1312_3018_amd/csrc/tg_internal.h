@@ -365,6 +365,7 @@ unsigned long long stat_sum(const Workspace &ws, int k);
 struct HybridState;
 struct SlotEngine;
 struct BcBatchState;
+struct SmallState;
 constexpr int MAX_LANES = 8;  // searches in flight of one multi-root call
 constexpr int MAX_BFS_LANES = 4;  // BFS searches in flight (within MAX_LANES)
 // BFS searches in flight for nr roots under tuning t.
@@ -398,6 +399,7 @@ struct tg_partition {
   tg::HybridState *hy = nullptr;  // host partition + boundary buffers (cpu_edge_share > 0)
   tg::SlotEngine *slots[2] = {nullptr, nullptr};  // batched BFS / SSSP engines (lazy)
   tg::BcBatchState *bcb = nullptr;                 // batched BC scratch (lazy)
+  tg::SmallState *small = nullptr;                 // scratch of the few-launch searches (lazy)
 };
 
 namespace tg {
@@ -492,6 +494,7 @@ int collect_f64_to_f32(const GpuPart &g, const double *state, float *out, hipStr
 int fill_i32(int32_t *p, int64_t n, int32_t v, hipStream_t s);
 int fill_f64(double *p, int64_t n, double v, hipStream_t s);
 int fill_f32(float *p, int64_t n, float v, hipStream_t s);
+// (`visited` null: `level` holds TG_INF where the search has not been)
 int bfs_parents(const GpuPart &g, const uint32_t *visited, const int32_t *level, int32_t root_local,
                 int32_t *out, hipStream_t s);
 
@@ -548,6 +551,13 @@ int gpu_sssp_roots(tg_partition *p, const int32_t *roots_local, int32_t nr, int3
 int gpu_pagerank(tg_partition *p, double damping, int32_t iters, int mode, float *rank_out,
                  hipStream_t s);
 int gpu_bc_source(tg_partition *p, int32_t src_local, hipStream_t s);
+// small.hip: BFS on a small graph, a workgroup per root (roots: original ids;
+// levels and, if non-null, parents as gpu_bfs_roots).  *deep: some search has
+// more levels than it can hold, the outputs are not complete.
+bool small_bfs_supported(const GpuPart &g);
+int small_bfs(tg_partition *p, const int32_t *roots, int32_t nr, int32_t *levels, int32_t *parents, hipStream_t s,
+              int64_t *supersteps, bool *deep);
+void small_free(tg_partition *p);
 // cc.hip: component labels (original ids) into `labels` (device, V entries)
 int gpu_cc(tg_partition *p, int32_t *labels, hipStream_t s, int64_t *rounds_out);
 // bcb.hip: adds the dependencies of `sources` (original ids) into ws.bc_acc

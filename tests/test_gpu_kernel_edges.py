@@ -259,3 +259,41 @@ def test_overflow_verdict_is_the_same_on_both_routes(gpu):
             gpu.sssp(P, [1, 0])
         assert ei.value.code == gpu.TG_ERANGE
         assert gpu.sssp(P, [1]).cpu().numpy().tolist() == [[2**31 - 10, 0, 2**31 - 10]]
+
+
+# ------------------------------------------- one workgroup per BFS root
+
+@pytest.mark.parametrize("n", [1, 2, 31, 32, 33, 63, 64, 65, 1023, 1024, 1025, 32768, 65536, 65537])
+@pytest.mark.parametrize("sym", [True, False])
+def test_workgroup_bfs_of_each_size(gpu, n, sym):
+    """Bitmap word pairs, the 1024-vertex sweep, the largest graphs it takes
+    and the first it does not; a star and a random graph in one, so that the
+    queue overflows and rows of all lengths are looked through."""
+    rng = np.random.default_rng(n)
+    k = n // 3
+    src = np.r_[np.zeros(k, int), rng.integers(0, n, 3 * n)]
+    dst = np.r_[np.arange(k), rng.integers(0, max(n // 2, 1), 3 * n)]
+    g = graphgen.from_edges(n, src, dst, symmetrize=sym)
+    roots = [0, n - 1, n // 2, 0] + rng.integers(0, n, 3).tolist()
+    lev, par = gpu.bfs(load(gpu, g), roots, want_parents=True)
+    lev, par = lev.cpu().numpy(), par.cpu().numpy()
+    only = gpu.bfs(load(gpu, g), roots).cpu().numpy()
+    assert np.array_equal(only, lev)
+    for i, r in enumerate(roots):
+        assert np.array_equal(lev[i], oracle.bfs(g.offsets, g.cols, r)), (i, r)
+        v = np.nonzero((lev[i] != INF) & (np.arange(n) != r))[0]
+        assert par[i][r] == r and np.all(par[i][lev[i] == INF] == -1)
+        assert np.all(lev[i][par[i][v]] == lev[i][v] - 1)
+
+
+@pytest.mark.parametrize("tail", [1, 252, 253, 254, 255, 400])
+def test_workgroup_bfs_past_its_deepest_level(gpu, tail):
+    """Levels up to and past what a byte holds (the launched supersteps take
+    over), with a frontier beyond the queue at the end of the path."""
+    g, c, end = core_and_tail(8, tail, hub=3000)
+    for roots in ([c], [end, c, 0], [end] * 65):
+        lev, par = gpu.bfs(load(gpu, g), roots, want_parents=True)
+        lev = lev.cpu().numpy()
+        assert np.array_equal(lev, gpu.bfs(load(gpu, g), roots).cpu().numpy())
+        for i in {0, len(roots) - 1}:
+            assert np.array_equal(lev[i], oracle.bfs(g.offsets, g.cols, roots[i])), (tail, i)
