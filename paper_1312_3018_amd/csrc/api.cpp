@@ -1088,6 +1088,22 @@ bool sssp_in_engine(const tg_partition *p, int32_t nr) {
   return nr >= 4 * (lg - (p->gpu.in_alias ? 19 : 18));
 }
 
+// Few roots on small graphs: a launch per round for all of them.  The most
+// roots by log2 of the vertex count (ms, rounds / engine; the single searches
+// are slower than both here).  Symmetric: 2^12, 32 roots 0.50 / 0.78; 2^14,
+// 16: 0.68 / 1.00, 32: 1.16 / 1.03; 2^15, 8: 1.07 / 1.21, 16: 1.81 / 1.14;
+// 2^18, 2: 1.33 / 1.99, 4: 2.58 / 2.22; 2^20, 1: 1.96 / 3.97, 2: 4.00 / 5.20.
+// Directed (the engine pushes only): 50,021 vertices, 1: 0.27 / 0.93, 32: 3.59
+// / 5.35; 2^18, 4: 2.8 / 4.6, 8: 5.6 / 4.9; 2^20, 1: 1.75 / 2.50, 2: 2.99 /
+// 2.86.
+bool sssp_in_rounds(const tg_partition *p, int32_t nr) {
+  static const int sym[] = {32, 20, 16, 8, 6, 4, 3, 2, 2}, dir[] = {32, 32, 32, 32, 32, 12, 6, 3, 1};  // 2^12 .. 2^20
+  if (p->tune.sssp_batch_roots >= 0 || nr <= 0 || p->gpu.n <= 0 || p->gpu.n > (1 << 20)) return false;
+  int lg = 12;  // n <= 2^lg
+  while (((int64_t)1 << lg) < p->gpu.n) ++lg;
+  return nr <= (p->gpu.in_alias ? sym : dir)[lg - 12];
+}
+
 // Betweenness, one source at a time / 64 in a chain: 2 sources: 2^12..2^20
 // vertices 0.64-3.11 / 0.54-2.56; RMAT-22, 2: 6.7 / 7.3, 3: 10.5 / 8.0, 16:
 // 61.8 / 11.1.
@@ -1172,6 +1188,19 @@ extern "C" int sssp(const tg_partition *pc, const int32_t *roots, int32_t num_ro
   ktimer_reset();
   if (p->alpha > 0.0) return hybrid_sssp(p, roots, num_roots, dist, s);
   int64_t rounds_total = 0, pulls_total = 0;
+  if (sssp_in_rounds(p, num_roots)) {
+    const int rc = round_sssp(p, roots, num_roots, dist, s, &rounds_total);
+    if (rc == TG_OK) {
+      stats_add("roots", num_roots);
+      stats_add("supersteps", (double)rounds_total);
+      stats_add("pull_supersteps", 0.0);
+      ktimer_emit();
+    }
+    if (rc != TG_ENOMEM) return rc;
+    small_free(p);
+    clear_error();
+    rounds_total = 0;
+  }
   if (sssp_in_engine(p, num_roots)) {
     const int rc = slots_run_batch(p, kSlotSssp, roots, num_roots, dist, s, &rounds_total);
     if (rc == TG_ERANGE) return set_error(rc, "sssp: a shortest-path distance does not fit below INT32_MAX");

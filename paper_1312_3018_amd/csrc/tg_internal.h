@@ -557,6 +557,8 @@ int gpu_bc_source(tg_partition *p, int32_t src_local, hipStream_t s);
 bool small_bfs_supported(const GpuPart &g);
 int small_bfs(tg_partition *p, const int32_t *roots, int32_t nr, int32_t *levels, int32_t *parents, hipStream_t s,
               int64_t *supersteps, bool *deep);
+// SSSP for a few roots (original ids), a launch per round for all of them.
+int round_sssp(tg_partition *p, const int32_t *roots, int32_t nr, int32_t *dist, hipStream_t s, int64_t *rounds);
 void small_free(tg_partition *p);
 // cc.hip: component labels (original ids) into `labels` (device, V entries)
 int gpu_cc(tg_partition *p, int32_t *labels, hipStream_t s, int64_t *rounds_out);

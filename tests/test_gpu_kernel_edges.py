@@ -297,3 +297,63 @@ def test_workgroup_bfs_past_its_deepest_level(gpu, tail):
         assert np.array_equal(lev, gpu.bfs(load(gpu, g), roots).cpu().numpy())
         for i in {0, len(roots) - 1}:
             assert np.array_equal(lev[i], oracle.bfs(g.offsets, g.cols, roots[i])), (tail, i)
+
+
+# ------------------------------------- SSSP for a few roots, in rounds
+
+@pytest.mark.parametrize("n", [1, 2, 16, 17, 64, 65, 1025, 5000])
+@pytest.mark.parametrize("sym", [True, False])
+@pytest.mark.parametrize("top", [1, 255, 100000])
+def test_round_sssp_of_each_size(gpu, n, sym, top):
+    """Packed and two-array edges, ragged spans of 1, 4 and 16 vertices, a row
+    past the 1024-thread block's turn, several roots per launch."""
+    rng = np.random.default_rng(n)
+    src = np.r_[np.zeros(n, int), rng.integers(0, n, 4 * n)]
+    dst = np.r_[np.arange(n), rng.integers(0, max(n // 2, 1), 4 * n)]
+    g = graphgen.from_edges(n, src, dst, symmetrize=sym)
+    w = graphgen.weights(g, seed=n, lo=1, hi=top)
+    for tuning in (None, {"hub_min_deg": 64, "block_min_deg": 32, "wave_min_deg": 16, "g16_min_deg": 6,
+                          "g4_min_deg": 2, "hub_chunk": 256}):
+        P = load(gpu, g, w, tuning)
+        for roots in ([n - 1], [0, n // 2, 0, n - 1, n // 3]):
+            dist = gpu.sssp(P, roots).cpu().numpy()
+            for i, r in enumerate(roots):
+                assert np.array_equal(dist[i], oracle.sssp(g.offsets, g.cols, w, r)), (tuning, roots, i)
+
+
+@pytest.mark.parametrize("n", [12, 13, 14, 17, 40, 130, 3000])
+def test_round_sssp_chunks_end_anywhere(gpu, n):
+    """Paths whose number of rounds is on either side of a chunk's end, and a
+    root without edges (no round relaxes anything)."""
+    g = graphgen.from_edges(n + 1, np.arange(n - 1), np.arange(1, n), symmetrize=True)
+    w = graphgen.weights(g, seed=n)
+    P = load(gpu, g, w)
+    for _ in range(2):
+        dist = gpu.sssp(P, [0, n]).cpu().numpy()
+        for i, r in enumerate((0, n)):
+            assert np.array_equal(dist[i], oracle.sssp(g.offsets, g.cols, w, r)), r
+        assert gpu.sssp(P, [n]).cpu().numpy()[0].tolist() == [INF] * n + [0]
+
+
+@pytest.mark.parametrize("leaves", [2, 600])
+@pytest.mark.parametrize("sym", [True, False])
+def test_round_sssp_overflow(gpu, leaves, sym):
+    """Overflowing candidates from short rows and from a block's row: an error
+    only where the vertex stays unreached."""
+    big = 2**31 - 10
+    far = leaves + 2
+    src = np.r_[0, np.full(leaves, 1), 1]
+    dst = np.r_[1, 2 + np.arange(leaves), far]
+    g = graphgen.from_edges(far + 1, src, dst, symmetrize=sym)
+    row = np.repeat(np.arange(g.n), np.diff(g.offsets))
+    w = np.where((row == far) | (g.cols == far), big, 50).astype(np.int32)
+    P = load(gpu, g, w)
+    with pytest.raises(gpu.TGError) as ei:
+        gpu.sssp(P, [0])
+    assert ei.value.code == gpu.TG_ERANGE
+    assert np.array_equal(gpu.sssp(P, [1]).cpu().numpy()[0], oracle.sssp(g.offsets, g.cols, w, 1))
+    g2 = graphgen.from_edges(g.n, np.r_[src, 0], np.r_[dst, far], symmetrize=sym)
+    row2 = np.repeat(np.arange(g2.n), np.diff(g2.offsets))
+    pair = ((row2 == 1) & (g2.cols == far)) | ((row2 == far) & (g2.cols == 1))
+    w2 = np.where(pair, big, 50).astype(np.int32)
+    assert np.array_equal(gpu.sssp(load(gpu, g2, w2), [0]).cpu().numpy()[0], oracle.sssp(g2.offsets, g2.cols, w2, 0))
