@@ -43,7 +43,7 @@ def kernel_sources_digest(files):
 # Sources each timed kernel is built from, plus the tuning cache that sets its
 # launch shapes (a traffic figure is only reused while these are unchanged).
 KERNEL_FILES = {
-    "pr_gather": ["pagerank.hip", "pr_sliced.hip", "pr_rows.hip", "kcommon.h", "../tuning_cache.json"],
+    "pr_gather": ["pagerank.hip", "pr_sell.hip", "pr_rows.hip", "kcommon.h", "../tuning_cache.json"],
     "bfs_step": ["bfs.hip", "frontier.hip", "kcommon.h", "../tuning_cache.json"],
     "sssp_relax": ["sssp.hip", "kcommon.h", "../tuning_cache.json"],
     "sssp_pull": ["sssp.hip", "frontier.hip", "kcommon.h", "../tuning_cache.json"],
@@ -74,7 +74,9 @@ def load_traffic(kernel: str, workload: str):
 TRAFFIC_ROWS = {
     "sssp_relax": ("sssp", ["k_sssp_relax<true, 1>", "k_sssp_relax<true, 2>"], "pool"),
     "sssp_pull": ("ssspp", ["k_sssp_pull_heavy"], "sum"),
-    "pr_gather": ("pr", ["k_pr_rows<true, int, 8>", "k_pr_long<true>", "k_pr_combine", "k_pr_dsum"], "sum"),
+    # (sliced columns, then row blocks by class: a run has the kernels of one)
+    "pr_gather": ("pr", ["k_pr_sell<true>", "k_pr_sell_long", "k_pr_combine", "k_pr_rows<true, int, 8>",
+                         "k_pr_long<true>", "k_pr_dsum"], "sum"),
     "bfs_step": ("bfs", ["k_bfs_step<int>"], "sum"),
 }
 # A 1 GiB device-to-device copy (--copy-calibration) reads FETCH_SIZE =

@@ -335,6 +335,7 @@ Tuning default_tuning() {
   t.bfs_graph = 0;  // replaying captured chunks measured 1-2% slower than direct launches
   t.mapped_edges = 0;
   t.bfs_batch_roots = t.sssp_batch_roots = -1;
+  t.pr_auto = true;
   return t;
 }
 
@@ -388,6 +389,7 @@ int parse_tuning(const char *json, Tuning *t) {
   if (json_int(json, "mapped_edges", &v)) t->mapped_edges = v;
   if (strstr(json, "\"bfs_")) t->bfs_batch_roots = 0;
   if (strstr(json, "\"sssp_")) t->sssp_batch_roots = 0;
+  if (strstr(json, "\"pr_")) t->pr_auto = false;
   if (json_int(json, "bfs_batch_roots", &v)) t->bfs_batch_roots = v;
   if (json_int(json, "sssp_batch_roots", &v)) t->sssp_batch_roots = v;
   if (t->bfs_batch_roots < -1 || t->sssp_batch_roots < -1)

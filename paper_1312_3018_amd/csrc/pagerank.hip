@@ -3,8 +3,8 @@
 //   r'(v) = (1 - d)/N + d * (sum c(u) + D/N),
 // where D is the rank held by out-degree-0 vertices (uniform mode) or 0 (drop
 // mode).  Pull needs no atomics on vertex state (the reason Figure 14 pulls).
-// The gather itself is in pr_rows.hip (whole CSR) and pr_sliced.hip (per-XCD
-// source classes).
+// The gather itself is in pr_sell.hip (sliced columns) and pr_rows.hip (the
+// CSR in row blocks: hybrid partitions, edges in host memory).
 #include <algorithm>
 
 #include "tg_internal.h"
@@ -72,15 +72,18 @@ int gpu_pagerank(tg_partition *p, double damping, int32_t iters, int mode, float
   GpuPart &g = p->gpu;
   if (g.n == 0) return TG_OK;
   const double N = (double)g.n_global;
+  if (iters == 0) return pr_write_initial(g, rank_out, N, s);
+  if (p->tune.pr_xcd && pr_slices_supported(g)) {
+    const int rc = gpu_pagerank_slices(p, damping, iters, mode, rank_out, s);
+    if (rc != TG_ENOMEM && rc != TG_EUNSUPPORTED) return rc;
+    // no room for the sliced columns: walk the in-edges as they are
+    pr_slices_free(g);
+    clear_error();
+  }
   // r_0 = 1/N, so c_0(u) = 1/(N outdeg(u)) and D_0 = (#dangling)/N
   TG_TRY(gpu_pagerank_setup(p, damping, mode, s, nullptr, (double)g.n_dangling / N));
-  if (iters == 0) return pr_write_initial(g, rank_out, N, s);
-  for (int32_t k = 0; k < iters; ++k) {
-    if (p->tune.pr_xcd)
-      TG_TRY(gpu_pagerank_sliced_step(p, damping, mode, k, k == iters - 1, rank_out, s));
-    else
-      TG_TRY(gpu_pagerank_step(p, damping, mode, k, k == iters - 1, rank_out, s, nullptr, nullptr));
-  }
+  for (int32_t k = 0; k < iters; ++k)
+    TG_TRY(gpu_pagerank_step(p, damping, mode, k, k == iters - 1, rank_out, s, nullptr, nullptr));
   return TG_OK;
 }
 

@@ -12,9 +12,8 @@
 // of its edges over its rows -- the latency chain (offsets, then ids, then
 // gathers) is what bounds a degree-bin walk on low-degree rows.
 //
-// The same kernel serves the per-XCD source classes: there every class has
-// its own CSR and row blocks, workgroup i takes class i mod 8, and rows yield
-// partial sums that a combine pass adds (see pr_sliced.hip).
+// (pr_sell.hip is the faster layout for whole graphs on the GPU; this kernel
+// also takes boundary contributions, and needs no copy of the edges.)
 //
 // Blocks never wait on each other.  A chunk block stores its partial sum; a
 // second launch finishes the long rows (one wave per row, a fixed reduction
@@ -89,30 +88,20 @@ void build_row_blocks(int64_t nrows, const int64_t *off64, const int32_t *off32,
 
 namespace {
 
-constexpr int NS = 8;     // source classes (XCDs)
-constexpr int LINE = 32;  // contributions per 128-byte line
 constexpr int WB = 1024;  // threads per workgroup of the row-block gather
-
-template <bool CLASSES>
-__device__ __forceinline__ const float *contrib_ptr(const float *hot, const float *c_in, int64_t H, int32_t u) {
-  // generic pointer: one load instruction for the LDS or the global case
-  if (CLASSES) return u < H ? hot + (((u >> 8) << 5) | (u & 31)) : c_in + u;
-  return u < H ? hot + u : c_in + u;
-}
 
 // Loads of one row block (its row offsets, out-degrees when staged, and
 // source ids) by one wave, issued without a branch: lanes past an end re-read
 // the last element, and a chunk block re-reads its row's offset.
-template <typename OffT, int U>
+template <int U>
 struct BlockLoads {
-  OffT o[U];
+  int64_t o[U];
   int32_t od[U];
   int32_t u[U];
 };
 
-template <typename OffT, int U>
-__device__ __forceinline__ void issue_loads(BlockLoads<OffT, U> &L, const RowBlk &me, const RowBlk &nx,
-                                            const OffT *off, const int32_t *col, const int32_t *od32,
+template <int U>
+__device__ __forceinline__ void issue_loads(BlockLoads<U> &L, const RowBlk &me, const RowBlk &nx, const int64_t *off, const int32_t *col, const int32_t *od32,
                                             bool stage_od, int lane) {
   const bool chunk = me.lr >= 0;
   const int32_t R = chunk ? 1 : nx.r0 - me.r0;
@@ -137,61 +126,52 @@ __device__ __forceinline__ void wave_lds_sync() {
 }
 
 // One workgroup of WB threads per CU.  Its waves share one table of hot
-// contributions in LDS (in class mode every workgroup of an XCD serves the
-// same class, so the table covers 8x as many sources) and each wave walks its
-// own row blocks of at most 64*U edges and 64*U - 1 rows, with no workgroup
-// barrier.  Per wave the loads of block j+1 are issued right after the
+// contributions in LDS and each wave walks its own row blocks of at most 64*U
+// edges and 64*U - 1 rows, with no workgroup barrier.  Per wave the loads of block j+1 are issued right after the
 // gathers of block j, so one memory round trip covers both.
-template <bool CLASSES, typename OffT, int U>
+template <int U>
 __global__ __launch_bounds__(WB) void k_pr_rows(const RowsArgs A) {
   constexpr int NNZ = 64 * U;
   // all LDS is dynamic (sized by rows_lds_bytes): hot table, then one
-  // region per wave, then (single mode) the waves' dangling partials
+  // region per wave, then the waves' dangling partials
   extern __shared__ float lds[];
   const int t = threadIdx.x, w = t >> 6, lane = t & 63;
-  const bool stage_od = !CLASSES && !A.od_rows;
+  const bool stage_od = !A.od_rows;
   float *hot = lds;
   double *s_dang = reinterpret_cast<double *>(lds + A.lds_verts + (int64_t)(WB / 64) * NNZ * (stage_od ? 3 : 2));
   float *vals = lds + A.lds_verts + (int64_t)w * NNZ * (stage_od ? 3 : 2);
   int32_t *loff = reinterpret_cast<int32_t *>(vals + NNZ);
-  int32_t *lod = loff + NNZ;  // out-degrees of the rows (single mode, unless they equal the row lengths)
-  const int k = CLASSES ? (int)(blockIdx.x & (NS - 1)) : 0;
-  const int64_t nwg = CLASSES ? (int64_t)(gridDim.x >> 3) : (int64_t)gridDim.x;
-  const int64_t j0 = (CLASSES ? (int64_t)(blockIdx.x >> 3) : (int64_t)blockIdx.x) * (WB / 64) + w;
-  const int64_t js = nwg * (WB / 64);
-  // hottest contributions: sources [0, lds_verts); in class mode the first
-  // lds_verts/32 lines of class k (lines k, k+8, ...), so that every source
-  // below H has its line in LDS
-  for (int32_t i = t; i < A.lds_verts; i += WB) {
-    const int64_t u = CLASSES ? ((int64_t)(i / LINE) * NS + k) * LINE + (i % LINE) : (int64_t)i;
-    hot[i] = u < A.n ? A.c_in[u] : 0.0f;
-  }
-  const int64_t H = CLASSES ? (int64_t)A.lds_verts * NS : (int64_t)A.lds_verts;
+  int32_t *lod = loff + NNZ;  // out-degrees of the rows (unless they equal the row lengths)
+  const int64_t j0 = (int64_t)blockIdx.x * (WB / 64) + w;
+  const int64_t js = (int64_t)gridDim.x * (WB / 64);
+  // hottest contributions: sources [0, lds_verts)
+  for (int32_t i = t; i < A.lds_verts; i += WB) hot[i] = i < A.n ? A.c_in[i] : 0.0f;
   __syncthreads();
-  const RowBlk *rb = A.rb + A.rb_base[k];
-  const OffT *off = static_cast<const OffT *>(A.off) + (int64_t)k * A.off_stride;
-  const int32_t *col = A.col + A.ebase[k];
-  float *psk = CLASSES ? A.ps + (int64_t)k * A.n : nullptr;
-  const double add = CLASSES ? 0.0 : A.base + A.d * (A.drop ? 0.0 : *A.dsum_in) * A.inv_n;
+  const RowBlk *rb = A.rb;
+  const double add = A.base + A.d * (A.drop ? 0.0 : *A.dsum_in) * A.inv_n;
   double dang = 0.0;
 
-  const int64_t nbk = A.nb[k];
+  const int64_t nbk = A.nb;
   if (j0 < nbk) {
     // descriptors of the current and the next block (past the end the last
     // block's is re-read: its loads are issued but never used)
     RowBlk cur = rb[j0], cur_nx = rb[j0 + 1];
     const int64_t i1 = min(j0 + js, nbk - 1);
     RowBlk nxt = rb[i1], nxt_nx = rb[i1 + 1];
-    BlockLoads<OffT, U> L;
-    issue_loads<OffT, U>(L, cur, cur_nx, off, col, A.od32, stage_od, lane);
+    BlockLoads<U> L;
+    issue_loads<U>(L, cur, cur_nx, A.off, A.col, A.od32, stage_od, lane);
     for (int64_t j = j0; j < nbk; j += js) {
       const int64_t i2 = min(j + 2 * js, nbk - 1);
       const RowBlk nn = rb[i2], nn_nx = rb[i2 + 1];
       float x[U];
 #pragma unroll
-      for (int q = 0; q < U; ++q) x[q] = *contrib_ptr<CLASSES>(hot, A.c_in, H, L.u[q]);
-      BlockLoads<OffT, U> L2;
-      issue_loads<OffT, U>(L2, nxt, nxt_nx, off, col, A.od32, stage_od, lane);
+      for (int q = 0; q < U; ++q) {
+        // generic pointer: one load instruction for the LDS or the global case
+        const float *from = L.u[q] < A.lds_verts ? hot + L.u[q] : A.c_in + L.u[q];
+        x[q] = *from;
+      }
+      BlockLoads<U> L2;
+      issue_loads<U>(L2, nxt, nxt_nx, A.off, A.col, A.od32, stage_od, lane);
 
       const int32_t ne = (int32_t)(cur_nx.e0 - cur.e0);
       const bool chunk = cur.lr >= 0;
@@ -201,7 +181,7 @@ __global__ __launch_bounds__(WB) void k_pr_rows(const RowsArgs A) {
 #pragma unroll
         for (int q = 0; q < U; ++q) cs += (q * 64 + lane < ne) ? (double)x[q] : 0.0;
         cs = wave_sum(cs);
-        if (lane == 0) A.chunk_part[A.rb_base[k] + j] = cs;
+        if (lane == 0) A.chunk_part[j] = cs;
       } else {
         const int32_t R = cur_nx.r0 - cur.r0;
 #pragma unroll
@@ -229,15 +209,11 @@ __global__ __launch_bounds__(WB) void k_pr_rows(const RowsArgs A) {
           sm = group_sum(sm, Lw);
           if (r < R && sub == 0) {
             const int32_t v = cur.r0 + r;
-            if (CLASSES) {
-              __builtin_nontemporal_store((float)sm, psk + v);
-            } else {
-              const double rv = add + A.d * (sm + (A.ghost ? A.ghost[v] : 0.0));
-              const int32_t od = stage_od ? lod[r] : hi - lo;
-              if (A.last) A.rank_out[A.g_of_l[v]] = (float)rv;
-              else if (od > 0) __builtin_nontemporal_store((float)(rv / (double)od), A.c_out + v);
-              if (od == 0) dang += rv;
-            }
+            const double rv = add + A.d * (sm + (A.ghost ? A.ghost[v] : 0.0));
+            const int32_t od = stage_od ? lod[r] : hi - lo;
+            if (A.last) A.rank_out[A.g_of_l[v]] = (float)rv;
+            else if (od > 0) __builtin_nontemporal_store((float)(rv / (double)od), A.c_out + v);
+            if (od == 0) dang += rv;
           }
         }
         wave_lds_sync();
@@ -249,7 +225,6 @@ __global__ __launch_bounds__(WB) void k_pr_rows(const RowsArgs A) {
       L = L2;
     }
   }
-  if (CLASSES) return;
   // dangling partial of this workgroup, waves added in order
   dang = wave_sum(dang);
   if (lane == 0) s_dang[w] = dang;
@@ -262,14 +237,13 @@ __global__ __launch_bounds__(WB) void k_pr_rows(const RowsArgs A) {
 }
 
 // Long rows: one wave per row sums the row's chunk partials (lane-strided,
-// then a fixed butterfly) and finishes the row like k_pr_rows does.  Single
-// mode leaves one dangling partial per block in long_part.
-template <bool CLASSES>
+// then a fixed butterfly) and finishes the row like k_pr_rows does, leaving one
+// dangling partial per block in long_part.
 __global__ __launch_bounds__(BLOCK) void k_pr_long(const RowsArgs A) {
   const int lane = threadIdx.x & 63;
   const int64_t w0 = ((int64_t)blockIdx.x * BLOCK + threadIdx.x) >> 6;
   const int64_t nw = ((int64_t)gridDim.x * BLOCK) >> 6;
-  const double add = CLASSES ? 0.0 : A.base + A.d * (A.drop ? 0.0 : *A.dsum_in) * A.inv_n;
+  const double add = A.base + A.d * (A.drop ? 0.0 : *A.dsum_in) * A.inv_n;
   double dang = 0.0;
   for (int64_t lr = w0; lr < A.nlr; lr += nw) {
     const int64_t b0 = A.lr_b0[lr];
@@ -278,20 +252,14 @@ __global__ __launch_bounds__(BLOCK) void k_pr_long(const RowsArgs A) {
     for (int32_t c = lane; c < nch; c += 64) s += A.chunk_part[b0 + c];
     s = wave_sum(s);
     if (lane == 0) {
-      const int64_t pos = A.lr_pos[lr];
-      if (CLASSES) {
-        A.ps[pos] = (float)s;
-      } else {
-        const int64_t v = pos;
-        const double r = add + A.d * (s + (A.ghost ? A.ghost[v] : 0.0));
-        const int64_t od = A.od_rows ? A.out_off[v + 1] - A.out_off[v] : A.od32[v];
-        if (A.last) A.rank_out[A.g_of_l[v]] = (float)r;
-        else if (od > 0) A.c_out[v] = (float)(r / (double)od);
-        if (od == 0) dang += r;
-      }
+      const int64_t v = A.lr_pos[lr];
+      const double r = add + A.d * (s + (A.ghost ? A.ghost[v] : 0.0));
+      const int64_t od = A.od_rows ? A.out_off[v + 1] - A.out_off[v] : A.od32[v];
+      if (A.last) A.rank_out[A.g_of_l[v]] = (float)r;
+      else if (od > 0) A.c_out[v] = (float)(r / (double)od);
+      if (od == 0) dang += r;
     }
   }
-  if (CLASSES) return;
   dang = block_sum(dang);
   if (threadIdx.x == 0) A.long_part[blockIdx.x] = dang;
 }
@@ -371,32 +339,20 @@ int rows_lds_limit() {
   return limit[dev];
 }
 
-int rows_launch(const RowsArgs &A, bool classes, bool off32, int grid, hipStream_t s) {
-  const size_t lds = rows_lds_bytes(A.lds_verts, A.nnz, !classes && !A.od_rows);
+static int rows_launch(const RowsArgs &A, int grid, hipStream_t s) {
+  const size_t lds = rows_lds_bytes(A.lds_verts, A.nnz, !A.od_rows);
   if (lds > (size_t)rows_lds_limit())
     return set_error(TG_EINVAL, "pagerank: row blocks need %zu bytes of LDS (limit %d)", lds, rows_lds_limit());
-  if (classes != (bool)off32) return set_error(TG_EINVAL, "pagerank: row offset width does not match the mode");
   if (A.nnz != 256 && A.nnz != 512) return set_error(TG_EINVAL, "pagerank: row blocks of %d edges (256 or 512)", A.nnz);
   if (A.lds_verts % 2) return set_error(TG_EINVAL, "pagerank: odd hot-table size");
-#define TG_ROWS_LAUNCH(C, T, UU) hipLaunchKernelGGL((k_pr_rows<C, T, UU>), dim3(grid), dim3(WB), lds, s, A)
-  if (classes) {
-    if (A.nnz == 256) TG_ROWS_LAUNCH(true, int32_t, 4);
-    else TG_ROWS_LAUNCH(true, int32_t, 8);
-  } else {
-    if (A.nnz == 256) TG_ROWS_LAUNCH(false, int64_t, 4);
-    else TG_ROWS_LAUNCH(false, int64_t, 8);
-  }
-#undef TG_ROWS_LAUNCH
+  if (A.nnz == 256)
+    hipLaunchKernelGGL(k_pr_rows<4>, dim3(grid), dim3(WB), lds, s, A);
+  else
+    hipLaunchKernelGGL(k_pr_rows<8>, dim3(grid), dim3(WB), lds, s, A);
   TG_HIP(hipGetLastError());
-  if (A.nlr > 0 || !classes) {
-    // single mode always runs it: it writes the long rows' dangling partials
-    const int lg = long_grid(A.nlr);
-    if (classes)
-      hipLaunchKernelGGL((k_pr_long<true>), dim3(lg), dim3(BLOCK), 0, s, A);
-    else
-      hipLaunchKernelGGL((k_pr_long<false>), dim3(lg), dim3(BLOCK), 0, s, A);
-    TG_HIP(hipGetLastError());
-  }
+  // also without long rows: it writes their dangling partials
+  hipLaunchKernelGGL(k_pr_long, dim3(long_grid(A.nlr)), dim3(BLOCK), 0, s, A);
+  TG_HIP(hipGetLastError());
   return TG_OK;
 }
 
@@ -455,7 +411,7 @@ int gpu_pagerank_rows_step(tg_partition *p, double damping, int mode, int32_t k,
   RowsArgs A;
   memset(&A, 0, sizeof(A));
   A.rb = R.dev.rb;
-  A.nb[0] = R.dev.nb_total - 1;  // without the sentinel
+  A.nb = R.dev.nb_total - 1;  // without the sentinel
   A.off = g.in.off;
   A.col = g.in.col;
   A.lr_b0 = R.dev.lr_b0;
@@ -495,9 +451,9 @@ int gpu_pagerank_rows_step(tg_partition *p, double damping, int mode, int32_t k,
   A.ghost = ghost;
   A.extra_deg = extra_deg;
   // workgroups: enough for every wave to get a block, at most pr_grid
-  const int grid = (int)std::max<int64_t>(1, std::min<int64_t>((A.nb[0] + 15) / 16, p->tune.pr_grid));
+  const int grid = (int)std::max<int64_t>(1, std::min<int64_t>((A.nb + 15) / 16, p->tune.pr_grid));
   const int tk = ktimer_start(s);
-  TG_TRY(rows_launch(A, false, false, grid, s));
+  TG_TRY(rows_launch(A, grid, s));
   TG_TRY(pr_dsum_launch(ws.partials, grid, R.dev.long_part, long_grid(A.nlr), A.iso_count, A.base, A.d, A.inv_n,
                         A.drop, A.dsum_in, A.dsum_out, s));
   ktimer_stop(tk, s, "pr_rows");

@@ -103,6 +103,7 @@ struct Tuning {
   // (-1: by the graph's size, 0: never; a tuning that names any other key of
   // the algorithm asks for that schedule, so there the default is 0)
   int64_t bfs_batch_roots, sssp_batch_roots;
+  bool pr_auto;  // PageRank: no key of it was given (small graphs may be walked whole)
 };
 Tuning default_tuning();
 int parse_tuning(const char *json, Tuning *t);
@@ -221,18 +222,12 @@ int long_grid(int64_t nlr);
 // One block: *dsum_out = sum(pa[0..na)) + sum(pb[0..nb)) + iso_count * ((1-d)/N + d D/N)
 int pr_dsum_launch(const double *pa, int32_t na, const double *pb, int32_t nb, double iso_count, double base,
                    double d, double inv_n, int32_t drop, const double *dsum_in, double *dsum_out, hipStream_t s);
-// Kernel arguments.  Class mode: class k's blocks are rb[rb_base[k] ..
-// rb_base[k] + nb[k]] (sentinel included), its rows' offsets are
-// off + k * off_stride (int32, relative) and its edges col + ebase[k]; rows
-// write partial sums into ps[k * n + v].  Single mode: class 0 only, and rows
-// are finished as in the degree-bin gather.
+// Kernel arguments: blocks rb[0 .. nb] (sentinel included) over the rows'
+// offsets `off` and edges `col`.
 struct RowsArgs {
   const RowBlk *rb;
-  int64_t rb_base[8];
-  int64_t nb[8];
-  const void *off;
-  int64_t off_stride;
-  int64_t ebase[8];
+  int64_t nb;
+  const int64_t *off;
   const int32_t *col;
   const int32_t *lr_b0, *lr_nch;
   const int64_t *lr_pos;
@@ -243,15 +238,14 @@ struct RowsArgs {
   int32_t lds_verts;
   const float *c_in;
   int64_t n;
-  float *ps;
   double base, d, inv_n, iso_count;
   int32_t drop, last;
-  int32_t od_rows;  // single mode: out-degree of a row = its length (symmetric whole graph)
+  int32_t od_rows;  // out-degree of a row = its length (symmetric whole graph)
   const double *dsum_in;
   double *dsum_out;
   double *partials;
   const int64_t *out_off;
-  const int32_t *od32;      // single mode, od_rows == 0: out-degree of each row
+  const int32_t *od32;      // od_rows == 0: out-degree of each row
   float *c_out;
   const int32_t *g_of_l;
   float *rank_out;
@@ -260,7 +254,6 @@ struct RowsArgs {
 };
 size_t rows_lds_bytes(int32_t lds_verts, int32_t nnz, bool stage_od);
 int rows_lds_limit();  // LDS bytes a workgroup may use on the current device
-int rows_launch(const RowsArgs &A, bool classes, bool off32, int grid, hipStream_t s);
 
 // The GPU partition: local ids 0..n-1 in decreasing out-degree order.
 struct GpuPart {
@@ -507,9 +500,10 @@ int gpu_pagerank_setup(tg_partition *p, double damping, int mode, hipStream_t s,
                        double d0);
 int gpu_pagerank_step(tg_partition *p, double damping, int mode, int32_t k, bool last, float *rank_out,
                       hipStream_t s, const double *ghost, const int32_t *extra_deg);
-// pr_sliced.hip: the same step through the per-XCD source classes
-int gpu_pagerank_sliced_step(tg_partition *p, double damping, int mode, int32_t k, bool last, float *rank_out,
-                             hipStream_t s);
+// pr_sell.hip: all iterations (at least one) over sliced columns of the
+// in-edges, where supported
+bool pr_slices_supported(const GpuPart &g);
+int gpu_pagerank_slices(tg_partition *p, double damping, int32_t iters, int mode, float *rank_out, hipStream_t s);
 void pr_slices_free(GpuPart &g);
 // pr_rows.hip: the step over row blocks of the in-edges
 int gpu_pagerank_rows_step(tg_partition *p, double damping, int mode, int32_t k, bool last, float *rank_out,

@@ -357,3 +357,66 @@ def test_round_sssp_overflow(gpu, leaves, sym):
     pair = ((row2 == 1) & (g2.cols == far)) | ((row2 == far) & (g2.cols == 1))
     w2 = np.where(pair, big, 50).astype(np.int32)
     assert np.array_equal(gpu.sssp(load(gpu, g2, w2), [0]).cpu().numpy()[0], oracle.sssp(g2.offsets, g2.cols, w2, 0))
+
+
+# ------------------------------------------ PageRank over sliced columns
+
+# None: rows walked whole; the others name a schedule, which takes the classes:
+# as they are, without a table of hot contributions, with one line of it per
+# class, and with one workgroup per class.
+PR_TUNINGS = [None, {"pr_xcd": 1}, {"pr_lds_verts": 0}, {"pr_lds_verts": 32}, {"pr_grid": 8}]
+
+
+def check_pagerank(tg, g, tuning, iters=4):
+    """All terms are positive; per iteration a rank carries at most the
+    rounding of its contributions and of its partial sums, and one more when it
+    is written: (2 iters + 1) 2^-24, and one 2^-24 for the sums in 64 bits."""
+    P = load(tg, g, tuning=tuning)
+    for dangling in ("uniform", "drop"):
+        want = oracle.pagerank(g.offsets, g.cols, iterations=iters, dangling=dangling)
+        for _ in range(2):
+            r = tg.pagerank(P, iterations=iters, dangling=dangling).cpu().numpy().astype(np.float64)
+            assert np.all(np.abs(r - want) <= (2 * iters + 2) * 2.0**-24 * want), (tuning, dangling)
+
+
+@pytest.mark.parametrize("n", [1, 2, 63, 64, 65, 255, 257, 511, 512, 513, 1025, 30011])
+@pytest.mark.parametrize("sym", [True, False])
+def test_pagerank_slices_of_ragged_sizes(gpu, n, sym):
+    """Windows, slices and classes that end anywhere; isolated vertices."""
+    rng = np.random.default_rng(n)
+    for m in (0, n // 2, 9 * n):
+        g = graphgen.from_edges(n, rng.integers(0, n, m), rng.integers(0, n, m), symmetrize=sym)
+        for tuning in PR_TUNINGS:
+            check_pagerank(gpu, g, tuning)
+
+
+@pytest.mark.parametrize("around", [32, 128, 1024, 2048, 9 * 1024])
+@pytest.mark.parametrize("sym", [True, False])
+def test_pagerank_rows_around_each_split(gpu, around, sym):
+    """Rows just below and above the longest of a slice, one piece and several
+    (whole rows, and their eighths in the classes)."""
+    rng = np.random.default_rng(around)
+    pool = 24000
+    if around * 8 <= pool:
+        lens = np.r_[around + np.arange(-2, 3), 8 * around + np.arange(-48, 49, 8)]
+    else:
+        lens = around + np.arange(-64, 65, 16)
+    src = np.concatenate([rng.choice(pool, k, replace=False) for k in lens])
+    dst = pool + np.repeat(np.arange(lens.size), lens)
+    back = rng.integers(0, pool, 40000)
+    src, dst = np.r_[src, back], np.r_[dst, rng.integers(0, pool + lens.size, 40000)]
+    g = graphgen.from_edges(pool + lens.size, src, dst, symmetrize=sym)
+    for tuning in PR_TUNINGS:
+        check_pagerank(gpu, g, tuning)
+
+
+def test_pagerank_rows_of_one_class(gpu):
+    """Symmetric, so that ids follow degrees: 128 hubs of equal degree hold
+    four classes, rows of only those leave the other classes empty."""
+    n, hubs = 6000, 128
+    src = np.tile(np.arange(hubs), n - hubs)
+    dst = np.repeat(np.arange(hubs, n), hubs)
+    keep = (src + dst) % 3 > 0
+    g = graphgen.from_edges(n, src[keep], dst[keep], symmetrize=True)
+    for tuning in PR_TUNINGS:
+        check_pagerank(gpu, g, tuning)
