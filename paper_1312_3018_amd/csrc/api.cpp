@@ -957,6 +957,7 @@ extern "C" void partition_free(tg_partition *p) {
   delete p->slots[1];
   bcb_free(p);
   small_free(p);
+  buckets_free(p);
   pr_slices_free(p->gpu);
   pr_rows_free(p->gpu);
   sssp_slices_free(p->gpu);
@@ -1075,31 +1076,45 @@ bool bfs_in_workgroups(const tg_partition *p, int32_t nr) {
 }
 
 // SSSP.  The engine relaxes every active (vertex, root) pair each superstep,
-// the single searches' buckets do less work per root but in many more
-// supersteps.  1 root: 2^13..2^19 vertices 2.0-3.0 / 0.7-2.4, RMAT-20 3.28 /
-// 3.98; 4: RMAT-21 8.65 / 8.53; 8: RMAT-22 14.2 / 19.0; 16: RMAT-22 28.0 /
-// 19.6, RMAT-23 41.8 / 39.7, RMAT-24 67 / 83; 32: RMAT-24 134 / 99; 64:
-// RMAT-24 271 / 106.  Directed graphs (no pulled supersteps there): 4 roots:
-// RMAT-20 4.90 / 6.02; 8: 9.83 / 7.52, RMAT-21 11.7 / 11.5; 16: RMAT-22 28.9 /
-// 25.2.
+// the bucket schedule does less work per root but in many more supersteps,
+// which up to eight roots share (buckets.hip).  Engine / buckets, symmetric:
+// 2^17 vertices, 8 roots 2.06 / 2.20; 2^18, 8: 3.33 / 2.58, 16: 2.98 / 5.10;
+// 2^20, 8: 5.82 / 3.95, 10: 5.75 / 6.32; 2^21, 16: 10.9 / 9.95, 20: 11.0 /
+// 13.7; 2^22, 16: 20.3 / 16.0, 24: 20.8 / 23.9; 2^23, 16: 45.9 / 28.6, 32: 56.3
+// / 57.2; 2^24, 32: 102 / 105.  Directed (the engine has no pulled supersteps
+// there): 2^18, 12: 5.56 / 5.18, 16: 5.55 / 5.53; 2^20, 8: 7.60 / 4.50, 16:
+// 8.23 / 8.91; 2^21, 16: 14.6 / 12.9, 24: 15.6 / 19.2; 2^22, 16: 27.0 / 21.0,
+// 32: 32.8 / 41.9.  Single searches in four lanes (weights past a byte, where
+// the bucket schedule does not apply) / engine: 4 roots: RMAT-21 8.65 / 8.53;
+// 16: RMAT-23 41.8 / 39.7; directed, 8: RMAT-21 11.7 / 11.5.
 bool sssp_in_engine(const tg_partition *p, int32_t nr) {
+  static const int sym[] = {1, 9, 9, 9, 17, 20, 32, 32}, dir[] = {1, 16, 16, 13, 17, 24, 32, 32};  // 2^17 .. 2^24
   const int64_t from = p->tune.sssp_batch_roots;
   if (from >= 0) return from > 0 && nr >= from;
-  int lg = 0;  // n <= 2^lg
+  int lg = 17;  // n <= 2^lg
   while (((int64_t)1 << lg) < p->gpu.n) ++lg;
+  if (buckets_supported(p)) return nr >= (p->gpu.in_alias ? sym : dir)[std::min(lg, 24) - 17];
   return nr >= 4 * (lg - (p->gpu.in_alias ? 19 : 18));
 }
 
+// The bucket schedule with its supersteps shared and driven on the device,
+// wherever it applies and no schedule is named.  Lanes / buckets: 2^18, 1
+// root: 2.94 / 1.54; RMAT-22, 1: 4.01 / 2.48, 2: 5.25 / 3.44, 8: 17.4 / 7.9;
+// RMAT-24, 1: 6.59 / 4.37, 8: 34.8 / 25.9; uniform of 2^22, 1: 7.88 / 4.77.
+bool sssp_in_buckets(const tg_partition *p, int32_t nr) {
+  return p->tune.sssp_batch_roots != 0 && nr > 0 && buckets_supported(p);
+}
+
 // Few roots on small graphs: a launch per round for all of them.  The most
-// roots by log2 of the vertex count (ms, rounds / engine; the single searches
-// are slower than both here).  Symmetric: 2^12, 32 roots 0.50 / 0.78; 2^14,
-// 16: 0.68 / 1.00, 32: 1.16 / 1.03; 2^15, 8: 1.07 / 1.21, 16: 1.81 / 1.14;
-// 2^18, 2: 1.33 / 1.99, 4: 2.58 / 2.22; 2^20, 1: 1.96 / 3.97, 2: 4.00 / 5.20.
-// Directed (the engine pushes only): 50,021 vertices, 1: 0.27 / 0.93, 32: 3.59
-// / 5.35; 2^18, 4: 2.8 / 4.6, 8: 5.6 / 4.9; 2^20, 1: 1.75 / 2.50, 2: 2.99 /
-// 2.86.
+// roots by log2 of the vertex count (ms, rounds / the better of the others).
+// Symmetric: 2^12, 32 roots 0.50 / 0.78; 2^14, 16: 0.68 / 1.00, 32: 1.16 / 1.03;
+// 2^15, 8: 1.07 / 1.21, 16: 1.81 / 1.14; 2^17, 4: 1.60 / 1.86; 2^18, 2: 1.29 /
+// 1.95, 4: 2.58 / 2.32; 2^19, 1: 1.29 / 1.75, 2: 2.17 / 1.90; 2^20, 1: 1.88 /
+// 1.90, 2: 3.76 / 2.19.  Directed: 50,021 vertices, 1: 0.27 / 0.93, 32: 3.59 /
+// 5.35; 2^17, 12: 3.53 / 4.57; 2^18, 5: 2.51 / 2.52; 2^19, 3: 2.47 / 2.58; 2^20,
+// 1: 1.27 / 2.00, 2: 2.99 / 2.63.
 bool sssp_in_rounds(const tg_partition *p, int32_t nr) {
-  static const int sym[] = {32, 20, 16, 8, 6, 4, 3, 2, 2}, dir[] = {32, 32, 32, 32, 32, 12, 6, 3, 1};  // 2^12 .. 2^20
+  static const int sym[] = {32, 20, 16, 8, 6, 4, 3, 1, 1}, dir[] = {32, 32, 32, 32, 32, 12, 5, 3, 1};  // 2^12 .. 2^20
   if (p->tune.sssp_batch_roots >= 0 || nr <= 0 || p->gpu.n <= 0 || p->gpu.n > (1 << 20)) return false;
   int lg = 12;  // n <= 2^lg
   while (((int64_t)1 << lg) < p->gpu.n) ++lg;
@@ -1221,7 +1236,18 @@ extern "C" int sssp(const tg_partition *pc, const int32_t *roots, int32_t num_ro
   }
   std::vector<int32_t> local((size_t)num_roots);
   for (int32_t r = 0; r < num_roots; ++r) local[r] = p->h_l_of_g[roots[r]];
-  TG_TRY(gpu_sssp_roots(p, local.data(), num_roots, dist, s, &rounds_total, &pulls_total));
+  int rc = TG_ENOMEM;
+  if (sssp_in_buckets(p, num_roots)) {
+    rc = bucket_sssp(p, local.data(), num_roots, dist, s, &rounds_total, &pulls_total);
+    if (rc != TG_OK && rc != TG_ENOMEM) return rc;
+    if (rc == TG_ENOMEM) {
+      // no room for several searches' rows
+      buckets_free(p);
+      clear_error();
+      rounds_total = pulls_total = 0;
+    }
+  }
+  if (rc != TG_OK) TG_TRY(gpu_sssp_roots(p, local.data(), num_roots, dist, s, &rounds_total, &pulls_total));
   TG_HIP(hipStreamSynchronize(s));
   stats_add("roots", num_roots);
   stats_add("supersteps", (double)rounds_total);

@@ -359,6 +359,7 @@ struct HybridState;
 struct SlotEngine;
 struct BcBatchState;
 struct SmallState;
+struct BucketState;
 constexpr int MAX_LANES = 8;  // searches in flight of one multi-root call
 constexpr int MAX_BFS_LANES = 4;  // BFS searches in flight (within MAX_LANES)
 // BFS searches in flight for nr roots under tuning t.
@@ -392,6 +393,7 @@ struct tg_partition {
   tg::HybridState *hy = nullptr;  // host partition + boundary buffers (cpu_edge_share > 0)
   tg::SlotEngine *slots[2] = {nullptr, nullptr};  // batched BFS / SSSP engines (lazy)
   tg::BcBatchState *bcb = nullptr;                 // batched BC scratch (lazy)
+  tg::BucketState *buckets = nullptr;              // scratch of bucket_sssp (lazy)
   tg::SmallState *small = nullptr;                 // scratch of the few-launch searches (lazy)
 };
 
@@ -554,6 +556,11 @@ int small_bfs(tg_partition *p, const int32_t *roots, int32_t nr, int32_t *levels
 // SSSP for a few roots (original ids), a launch per round for all of them.
 int round_sssp(tg_partition *p, const int32_t *roots, int32_t nr, int32_t *dist, hipStream_t s, int64_t *rounds);
 void small_free(tg_partition *p);
+// SSSP by buckets for several roots at once (buckets.hip).
+bool buckets_supported(const tg_partition *p);
+int bucket_sssp(tg_partition *p, const int32_t *roots_local, int32_t nr, int32_t *dist, hipStream_t s, int64_t *rounds,
+                int64_t *pulls);
+void buckets_free(tg_partition *p);
 // cc.hip: component labels (original ids) into `labels` (device, V entries)
 int gpu_cc(tg_partition *p, int32_t *labels, hipStream_t s, int64_t *rounds_out);
 // bcb.hip: adds the dependencies of `sources` (original ids) into ws.bc_acc

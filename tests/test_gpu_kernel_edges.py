@@ -420,3 +420,61 @@ def test_pagerank_rows_of_one_class(gpu):
     g = graphgen.from_edges(n, src[keep], dst[keep], symmetrize=True)
     for tuning in PR_TUNINGS:
         check_pagerank(gpu, g, tuning)
+
+
+# -------------------------- SSSP by buckets for several roots at once
+
+BUCKETS = {"sssp_batch_roots": 1 << 20}  # never the engine: the bucket schedule
+
+
+@pytest.mark.parametrize("n", [1, 2, 31, 32, 33, 1025, 16383, 16384, 16385, 32768])
+@pytest.mark.parametrize("sym", [True, False])
+def test_bucket_sssp_of_ragged_sizes(gpu, n, sym):
+    """Words and collecting blocks (16384 vertices) that end anywhere, bins
+    that begin and end inside a block, full and partial groups of roots."""
+    rng = np.random.default_rng(n)
+    m = 5 * n
+    g = graphgen.from_edges(n, np.r_[np.zeros(n, int), rng.integers(0, n, m)],
+                            np.r_[np.arange(n), rng.integers(0, max(n // 2, 1), m)], symmetrize=sym)
+    w = graphgen.weights(g, seed=n)
+    bins = {"hub_min_deg": 64, "block_min_deg": 32, "wave_min_deg": 16, "g16_min_deg": 6, "g4_min_deg": 2}
+    want = {r: oracle.sssp(g.offsets, g.cols, w, r) for r in (0, n // 3, n // 2, n - 1)}
+    for tuning in (BUCKETS, {**BUCKETS, **bins}, {**BUCKETS, "sssp_delta": 255, "sssp_hpull": 0},
+                   {**BUCKETS, "sssp_delta": 24, "sssp_hpull": 100000}):
+        P = load(gpu, g, w, tuning)
+        for roots in ([n - 1], [0, n // 2, 0, n - 1, n // 3, 0, 0, n // 2], [n // 3, 0, n - 1] * 6):
+            dist = gpu.sssp(P, roots).cpu().numpy()
+            for i, r in enumerate(roots):
+                assert np.array_equal(dist[i], want[r]), (tuning, roots, i)
+
+
+@pytest.mark.parametrize("leaves", [2047, 2048, 2049, 4096, 4097, 40000])
+@pytest.mark.parametrize("top", [1, 8, 255])
+def test_bucket_sssp_hub_chunks(gpu, leaves, top):
+    """Two hubs whose rows end around a chunk's end, all light, some light,
+    and few light edges; leaves joined in a ring give longer ways round."""
+    a, b = 0, 1
+    leaf = 2 + np.arange(leaves)
+    src = np.r_[np.full(leaves, a), np.full(leaves - 1, b), leaf]
+    dst = np.r_[leaf, leaf[1:], np.roll(leaf, 1)]
+    g = graphgen.from_edges(leaves + 2, src, dst, symmetrize=True)
+    w = graphgen.weights(g, seed=leaves, lo=1, hi=top)
+    roots = [0, 1, 2, leaves // 2, leaves + 1]
+    for tuning in ({**BUCKETS, "hub_min_deg": 1024, "block_min_deg": 512}, {**BUCKETS, "sssp_delta": 2}):
+        dist = gpu.sssp(load(gpu, g, w, tuning), roots).cpu().numpy()
+        for i, r in enumerate(roots):
+            assert np.array_equal(dist[i], oracle.sssp(g.offsets, g.cols, w, r)), (tuning, r)
+
+
+def test_bucket_sssp_same_partition_again(gpu):
+    """More roots than the scratch was made for, then fewer."""
+    rng = np.random.default_rng(5)
+    n = 3000
+    g = graphgen.from_edges(n, rng.integers(0, n, 4 * n), rng.integers(0, n, 4 * n), symmetrize=True)
+    w = graphgen.weights(g, seed=1)
+    P = load(gpu, g, w, BUCKETS)
+    for count in (1, 3, 8, 20, 2):
+        roots = rng.integers(0, n, count).tolist()
+        dist = gpu.sssp(P, roots).cpu().numpy()
+        for i, r in enumerate(roots):
+            assert np.array_equal(dist[i], oracle.sssp(g.offsets, g.cols, w, r)), (count, i)
