@@ -59,8 +59,19 @@ __global__ __launch_bounds__(BLOCK) void k_gather(const Plan *__restrict__ Pp, c
     T s = op.identity();
     if (a.ok) {
       const auto vs = op.vstate(a.v);
-      if (op.live(vs))
-        for (int64_t e = a.e_begin + a.lane; e < a.e_end; e += a.stride) s = op.combine(s, op.term(vs, e));
+      if (op.live(vs)) {
+        // four terms' loads in flight, combined in the order of the edges (the
+        // gathers of a hybrid search, mean: 12.0 us one at a time, 10.3 so)
+        int64_t e = a.e_begin + a.lane;
+        for (; e + 3 * a.stride < a.e_end; e += 4 * (int64_t)a.stride) {
+          T x[4];
+#pragma unroll
+          for (int j = 0; j < 4; ++j) x[j] = op.term(vs, e + j * (int64_t)a.stride);
+#pragma unroll
+          for (int j = 0; j < 4; ++j) s = op.combine(s, x[j]);
+        }
+        for (; e < a.e_end; e += a.stride) s = op.combine(s, op.term(vs, e));
+      }
     }
     if (a.bin == BIN_HUB) {
       s = block_reduce(s, op);

@@ -103,7 +103,9 @@ struct HybridState {
   int32_t *d_cpu_g_of_l = nullptr;
   int32_t *d_stage = nullptr;   // host-partition results on their way to the output
   int32_t *h_stage = nullptr;
-  double *h_scalar = nullptr;   // pinned: dangling mass on its way to the GPU
+  long long *h_clock = nullptr;  // pinned: clocks around the small messages, [direction][parity][2]
+  bool by_kernel[2][2] = {};     // whether the last one of [direction][parity] crossed so
+  int clock_khz = 100000;
   Box out, in;                  // GPU-to-host and host-to-GPU messages
   hipStream_t cs_d2h = nullptr, cs_h2d = nullptr;  // copy streams (default priority)
   hipEvent_t ev_ready[2] = {}, ev_d2h[2][2] = {}, ev_h2d[2][2] = {}, ev_step = nullptr;

@@ -409,7 +409,9 @@ int build_hybrid(tg_partition *p, uint64_t seed) {
   TG_TRY(up(A, &hy->d_cpu_g_of_l, C.g_of_l.data(), (size_t)C.n));
   TG_TRY(dalloc(A, &hy->d_stage, (size_t)C.n));
   TG_HIP(hipHostMalloc((void **)&hy->h_stage, (size_t)C.n * sizeof(int32_t), hipHostMallocDefault));
-  TG_HIP(hipHostMalloc((void **)&hy->h_scalar, 64, hipHostMallocDefault));
+  TG_HIP(hipHostMalloc((void **)&hy->h_clock, 8 * sizeof(long long), hipHostMallocDefault));
+  TG_HIP(hipDeviceGetAttribute(&hy->clock_khz, hipDeviceAttributeWallClockRate, p->device));
+  if (hy->clock_khz <= 0) hy->clock_khz = 100000;
   TG_HIP(hipStreamCreateWithFlags(&hy->cs_d2h, hipStreamNonBlocking));
   TG_HIP(hipStreamCreateWithFlags(&hy->cs_h2d, hipStreamNonBlocking));
   for (int b = 0; b < 2; ++b) {
@@ -432,7 +434,7 @@ HybridState::~HybridState() {
       if (b->h[k]) TG_QUIET(hipHostFree(b->h[k]));
     }
   if (h_stage) TG_QUIET(hipHostFree(h_stage));
-  if (h_scalar) TG_QUIET(hipHostFree(h_scalar));
+  if (h_clock) TG_QUIET(hipHostFree(h_clock));
   if (cs_d2h) TG_QUIET(hipStreamDestroy(cs_d2h));
   if (cs_h2d) TG_QUIET(hipStreamDestroy(cs_h2d));
   for (int b = 0; b < 2; ++b) {

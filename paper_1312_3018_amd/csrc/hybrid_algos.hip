@@ -448,6 +448,24 @@ __global__ void k_set_f64h(double *p, int64_t i, double v) {
   if (threadIdx.x == 0) p[i] = v;
 }
 
+// Small messages cross by a kernel on the GPU's own stream, which reads or
+// writes the pinned host memory itself (16 bytes per lane, the tail in words).
+// Block 0 leaves its first and last clock.
+constexpr int COPY_THREADS = 1024;
+constexpr size_t COPY_BLOCK_BYTES = (size_t)COPY_THREADS * 16;
+__global__ __launch_bounds__(COPY_THREADS) void k_message(char *dst, const char *src, int64_t bytes,
+                                                          long long *clock2) {
+  if (clock2 && blockIdx.x == 0 && threadIdx.x == 0) clock2[0] = wall_clock64();
+  const int64_t n16 = bytes / 16, n4 = (bytes - n16 * 16) / 4;
+  for (int64_t i = (int64_t)blockIdx.x * COPY_THREADS + threadIdx.x; i < n16; i += (int64_t)gridDim.x * COPY_THREADS)
+    reinterpret_cast<uint4 *>(dst)[i] = reinterpret_cast<const uint4 *>(src)[i];
+  if (blockIdx.x == 0 && (int64_t)threadIdx.x < n4)
+    reinterpret_cast<uint32_t *>(dst + n16 * 16)[threadIdx.x] =
+        reinterpret_cast<const uint32_t *>(src + n16 * 16)[threadIdx.x];
+  __syncthreads();
+  if (clock2 && blockIdx.x == 0 && threadIdx.x == 0) clock2[1] = wall_clock64();
+}
+
 inline unsigned nblk(int64_t n) { return (unsigned)std::max<int64_t>((n + BLOCK - 1) / BLOCK, 1); }
 inline unsigned select_grid(int64_t n) { return (unsigned)std::min<int64_t>(nblk(n), 8192); }
 
@@ -474,8 +492,7 @@ int launch_select(Sel sel, int64_t n, char *box, hipStream_t s) {
 }
 
 int clear_words(uint32_t *w, int64_t n, hipStream_t s) {
-  if (n > 0) TG_HIP(hipMemsetAsync(w, 0, (size_t)n * sizeof(uint32_t), s));
-  return TG_OK;
+  return n > 0 ? fill_i32(reinterpret_cast<int32_t *>(w), n, 0, s) : TG_OK;
 }
 
 // ---------------------------------------------------------------- exchange
@@ -483,8 +500,35 @@ int clear_words(uint32_t *w, int64_t n, hipStream_t s) {
 // frontier plan is read back), so a buffer of parity b is free again when
 // superstep b + 2 fills it.
 
+// Messages up to this cross by a kernel: one launch, where the copy streams
+// take five calls (event, wait, event, copy, event) of which the GPU's stream
+// waits for two.  R-MAT of 2^20 vertices, directed, hubs with 2, 10, 30 and 60 %
+// of the edges on the host (messages of up to 72 KB), ms by copies / kernels:
+// 10 PageRank iterations 1.82, 2.00, 4.00, 8.75 / 1.54, 1.62, 3.66, 8.33; four
+// searches 2.40, 2.90, 3.49 / 2.36, 2.60, 3.14.  Beyond, a copy engine moves
+// the bytes beside the kernels.
+constexpr size_t SMALL_MESSAGE = (size_t)1 << 17;
+
+int launch_message(void *dst, const void *src, size_t bytes, long long *clock2, hipStream_t s) {
+  const unsigned grid = (unsigned)std::max<size_t>(1, (bytes + COPY_BLOCK_BYTES - 1) / COPY_BLOCK_BYTES);
+  hipLaunchKernelGGL(k_message, dim3(grid), dim3(COPY_THREADS), 0, s, static_cast<char *>(dst),
+                     static_cast<const char *>(src), (int64_t)bytes, clock2);
+  TG_HIP(hipGetLastError());
+  return TG_OK;
+}
+
+double clock_ms(const HybridState &h, const long long *clock2) {
+  return (double)(clock2[1] - clock2[0]) / (double)h.clock_khz;
+}
+
 // GPU -> host: once the GPU stream has produced box b, copy `bytes` of it.
 int post_d2h(HybridState &h, int b, size_t bytes, hipStream_t s) {
+  h.by_kernel[0][b] = bytes > 0 && bytes <= SMALL_MESSAGE;
+  if (h.by_kernel[0][b]) {
+    TG_TRY(launch_message(h.out.h[b], h.out.d[b], bytes, h.h_clock + 2 * b, s));
+    TG_HIP(hipEventRecord(h.ev_d2h[b][1], s));
+    return TG_OK;
+  }
   TG_HIP(hipEventRecord(h.ev_ready[b], s));
   TG_HIP(hipStreamWaitEvent(h.cs_d2h, h.ev_ready[b], 0));
   TG_HIP(hipEventRecord(h.ev_d2h[b][0], h.cs_d2h));
@@ -496,6 +540,10 @@ int post_d2h(HybridState &h, int b, size_t bytes, hipStream_t s) {
 // Waits for it; adds the copy's time.
 int wait_d2h(HybridState &h, int b, double *ms) {
   TG_HIP(hipEventSynchronize(h.ev_d2h[b][1]));
+  if (h.by_kernel[0][b]) {
+    *ms += clock_ms(h, h.h_clock + 2 * b);
+    return TG_OK;
+  }
   float t = 0.0f;
   TG_QUIET(hipEventElapsedTime(&t, h.ev_d2h[b][0], h.ev_d2h[b][1]));
   *ms += t;
@@ -531,6 +579,9 @@ size_t list_prefix_bytes(int64_t nslots) {
 // host -> GPU: copy `bytes` from offset `off` of host box b to the same
 // offset of the device box; the GPU stream waits for it.
 int post_h2d(HybridState &h, int b, size_t off, size_t bytes, hipStream_t s) {
+  h.by_kernel[1][b] = bytes > 0 && bytes <= SMALL_MESSAGE;
+  if (h.by_kernel[1][b])
+    return launch_message(h.in.d[b] + off, h.in.h[b] + off, bytes, h.h_clock + 4 + 2 * b, s);
   TG_HIP(hipEventRecord(h.ev_h2d[b][0], h.cs_h2d));
   if (bytes) TG_HIP(hipMemcpyAsync(h.in.d[b] + off, h.in.h[b] + off, bytes, hipMemcpyHostToDevice, h.cs_h2d));
   TG_HIP(hipEventRecord(h.ev_h2d[b][1], h.cs_h2d));
@@ -541,6 +592,7 @@ int post_h2d(HybridState &h, int b, size_t off, size_t bytes, hipStream_t s) {
 // Time of the last host-to-GPU copy of parity b (complete once the GPU
 // stream has passed it).
 double h2d_ms(HybridState &h, int b) {
+  if (h.by_kernel[1][b]) return clock_ms(h, h.h_clock + 4 + 2 * b);
   float t = 0.0f;
   TG_QUIET(hipEventElapsedTime(&t, h.ev_h2d[b][0], h.ev_h2d[b][1]));
   return t;
@@ -679,7 +731,7 @@ int hybrid_bfs(tg_partition *p, const int32_t *roots, int32_t nr, int32_t *level
     }
     TG_TRY(bfs_dev_start(g, ws, gl, s));  // gl < 0: no GPU root
     TG_TRY(frontier_compact_bfs_dev(g, ws, t, s));
-    TG_HIP(hipMemcpyAsync(ws.h_plan, ws.plan, sizeof(Plan), hipMemcpyDeviceToHost, s));
+    TG_TRY(launch_message(ws.h_plan, ws.plan, sizeof(Plan), nullptr, s));
     TG_HIP(hipStreamSynchronize(s));
     for (int32_t L = 0;; ++L) {
       const bool gpu_front = ws.h_plan->count > 0, host_front = !cfront.empty();
@@ -716,7 +768,7 @@ int hybrid_bfs(tg_partition *p, const int32_t *roots, int32_t nr, int32_t *level
       TG_TRY(bfs_dev_resume(ws, L, s));
       TG_TRY(frontier_compact_bfs_dev(g, ws, t, s));
       TG_HIP(hipEventRecord(ev.e[1], s));
-      TG_HIP(hipMemcpyAsync(ws.h_plan, ws.plan, sizeof(Plan), hipMemcpyDeviceToHost, s));
+      TG_TRY(launch_message(ws.h_plan, ws.plan, sizeof(Plan), nullptr, s));
       // host: expand its frontier over its local edges while the GPU runs
       const auto tc = clk::now();
 #pragma omp parallel
@@ -976,7 +1028,7 @@ int hybrid_pagerank(tg_partition *p, double damping, int32_t iters, int mode, fl
                          h.din.partials_f));
     // GPU gather with the ghost sums; its dangling mass lands in scalars[(k+1)&1]
     TG_TRY(gpu_pagerank_step(p, damping, mode, k, last, rank, s, h.d_ghost, h.d_bdeg));
-    TG_HIP(hipMemcpyAsync(&ws.h_work[2], ws.scalars + ((k + 1) & 1), sizeof(double), hipMemcpyDeviceToHost, s));
+    TG_TRY(launch_message(&ws.h_work[2], ws.scalars + ((k + 1) & 1), sizeof(double), nullptr, s));
     TG_HIP(hipEventRecord(ev.e[3], s));
     // host gather, beside the GPU step
     TG_TRY(wait_d2h(h, b, &ph.exchange_ms));
@@ -1005,8 +1057,7 @@ int hybrid_pagerank(tg_partition *p, double damping, int32_t iters, int mode, fl
     ph.h2d_bytes += (double)C.n * sizeof(float);
     ph.cpu_edges += (double)C.m;
     D = d_gpu + d_cpu;
-    h.h_scalar[0] = D;
-    TG_HIP(hipMemcpyAsync(ws.scalars + ((k + 1) & 1), h.h_scalar, sizeof(double), hipMemcpyHostToDevice, s));
+    if (!last) hipLaunchKernelGGL(k_set_f64h, dim3(1), dim3(64), 0, s, ws.scalars, (int64_t)((k + 1) & 1), D);
   }
   TG_TRY(stage_host_f32(h, crank, rank, s));
   TG_HIP(hipStreamSynchronize(s));
@@ -1208,6 +1259,7 @@ int hybrid_bc_source(tg_partition *p, int32_t src, hipStream_t s, std::vector<do
       sig_i[k] = H.sig[h.g2c.dst[k]];
       lev_i[k] = H.lev[h.g2c.dst[k]];
     }
+    h.by_kernel[1][0] = false;
     TG_HIP(hipEventRecord(h.ev_h2d[0][0], h.cs_h2d));
     TG_HIP(hipMemcpyAsync(h.d_gh_sig, sig_i, (size_t)no * sizeof(double), hipMemcpyHostToDevice, h.cs_h2d));
     TG_HIP(hipMemcpyAsync(h.d_gh_lev, lev_i, (size_t)no * sizeof(int32_t), hipMemcpyHostToDevice, h.cs_h2d));

@@ -478,3 +478,27 @@ def test_bucket_sssp_same_partition_again(gpu):
         dist = gpu.sssp(P, roots).cpu().numpy()
         for i, r in enumerate(roots):
             assert np.array_equal(dist[i], oracle.sssp(g.offsets, g.cols, w, r)), (count, i)
+
+
+# ---------------------------------------- messages of the hybrid split
+
+@pytest.mark.parametrize("n,alpha", [(40, 0.3), (300, 0.5), (4001, 0.5), (120000, 0.7)])
+def test_hybrid_messages_of_each_size(gpu, n, alpha):
+    """Messages of a few words, with a tail past their last 16 bytes, of more
+    than one block, and (the largest: over 2^15 host vertices) by copies."""
+    rng = np.random.default_rng(n)
+    g = graphgen.from_edges(n, rng.integers(0, n, 4 * n), rng.integers(0, n, 4 * n), symmetrize=True)
+    G = gpu.graph_load_csr(g.n, g.offsets, g.cols, None, symmetric=True)
+    P = gpu.partition_by_degree(G, "high", alpha, seed=3)
+    if n == 120000:
+        assert gpu.partition_info(P)["cpu_vertices"] * 4 > 1 << 17
+    roots = [0, n // 2, n - 1]
+    lev = gpu.bfs(P, roots).cpu().numpy()
+    for i, r in enumerate(roots):
+        assert np.array_equal(lev[i], oracle.bfs(g.offsets, g.cols, r)), r
+    # per iteration the rounding of a rank's contributions, and of what the
+    # sums of one side become on the way to the other
+    iters = 5
+    want = oracle.pagerank(g.offsets, g.cols, iterations=iters)
+    r = gpu.pagerank(P, iterations=iters).cpu().numpy().astype(np.float64)
+    assert np.all(np.abs(r - want) <= (2 * iters + 2) * 2.0**-24 * want)
