@@ -25,11 +25,13 @@
 // drops those with no source in common, and keeps eight state rows in
 // flight.  Rows take waves by degree: hubs (the HUB bin) several blocks each
 // with partial sums added by a second launch, the BLOCK bin a block, the
-// WAVE bin a wave; below that a wave takes several consecutive queue entries
-// and walks their edges as one list (the walks are in ms.h).
+// WAVE bin a wave, and these two bins several blocks too where a level has
+// few of them; below that a wave takes several consecutive queue entries and
+// walks their edges as one list (the walks are in ms.h).
 // RMAT-20, 64 sources: 23.6 ms a call with four edges in flight per wave and
 // three rows (level, sigma, delta) read per edge, 6.9 so, 6.1 with the
-// levels pulled (ms.hip) where 970 us of pushes had been.
+// levels pulled (ms.hip) where 970 us of pushes had been, 5.9 with few rows
+// shared.
 #include <string.h>
 
 #include <algorithm>
@@ -170,15 +172,15 @@ __global__ __launch_bounds__(BLOCK) void k_bb_block(const int32_t *__restrict__ 
   }
 }
 
-// The HUB bin: queue entries [0, hubs), gridDim.y blocks each; block y of
-// entry i leaves its share in part[i * gridDim.y + y].
+// Rows of queue entries [0, rows), gridDim.y blocks each; block y of entry i
+// leaves its share in part[i * gridDim.y + y].
 template <class Op>
-__global__ __launch_bounds__(BLOCK) void k_bb_hubs(const int32_t *__restrict__ queue, const u64 *__restrict__ qmask,
-                                                   int32_t hubs, const int64_t *__restrict__ off,
+__global__ __launch_bounds__(BLOCK) void k_bb_shared(const int32_t *__restrict__ queue, const u64 *__restrict__ qmask,
+                                                   int32_t rows, const int64_t *__restrict__ off,
                                                    const int32_t *__restrict__ col, const u64 *__restrict__ mask,
                                                    Op op, double *__restrict__ part) {
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  for (int64_t i = blockIdx.x; i < hubs; i += gridDim.x) {
+  for (int64_t i = blockIdx.x; i < rows; i += gridDim.x) {
     const int32_t v = queue[i];
     const u64 m = qmask[i];
     const double acc = block_lane_sum(walk_row(op, col, off[v], off[v + 1], (int)blockIdx.y * (BLOCK / 64) + w,
@@ -187,19 +189,26 @@ __global__ __launch_bounds__(BLOCK) void k_bb_hubs(const int32_t *__restrict__ q
   }
 }
 
-// One wave per hub adds its shares in order and finishes the row.
+// One wave per row adds its shares in order, eight reads in flight, and
+// finishes the row.
 template <class Op>
-__global__ __launch_bounds__(BLOCK) void k_bb_hubs_finish(const int32_t *__restrict__ queue,
-                                                          const u64 *__restrict__ qmask, int32_t hubs, int shares,
+__global__ __launch_bounds__(BLOCK) void k_bb_shared_finish(const int32_t *__restrict__ queue,
+                                                          const u64 *__restrict__ qmask, int32_t rows, int shares,
                                                           const double *__restrict__ part, Op op) {
   const int lane = threadIdx.x & 63;
   const int64_t i = ((int64_t)blockIdx.x * BLOCK + threadIdx.x) >> 6;
-  if (i >= hubs) return;
+  if (i >= rows) return;
   const int32_t v = queue[i];
   const u64 m = qmask[i];
   const double pre = op.begin(v, m);
   double acc = 0.0;
-  for (int y = 0; y < shares; ++y) acc += part[(i * shares + y) * S + lane];
+  for (int y = 0; y < shares; y += 8) {
+    double x[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) x[q] = y + q < shares ? part[(i * shares + y + q) * S + lane] : 0.0;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) acc += x[q];
+  }
   op.end(0, v, m, pre, acc);
 }
 
@@ -257,29 +266,65 @@ __global__ __launch_bounds__(S) void k_bb_join(u64 *next, uint32_t *touched, dou
   sigma[(int64_t)r * S + k] = 1.0;
 }
 
-// Blocks that share a hub's row: as many as the partial sums' room allows
-// (part_rows of them), 16 at most.
-int hub_shares(int64_t part_rows, int32_t hubs) {
-  return (int)std::max<int64_t>(1, std::min<int64_t>(part_rows / hubs, 16));
+// Blocks that share each of `rows` rows: enough for the chip, as many as
+// `most` (a wave's tile of 64 edges each, 16 in any case for hubs) and as the
+// partial sums have room for.
+int row_shares(int64_t part_rows, int32_t rows, int least, int most) {
+  const int64_t want = std::max<int64_t>(least, std::min<int64_t>(2048 / rows, most));
+  return (int)std::max<int64_t>(1, std::min<int64_t>(part_rows / rows, want));
+}
+
+// Rows of queue entries [lo, hi), `shares` blocks each.
+template <class Op>
+int launch_shared(int32_t lo, int32_t hi, int shares, int64_t part_rows, const int32_t *queue, const u64 *qmask,
+                  const int64_t *off, const int32_t *col, const u64 *mask, const Op &op, double *part, hipStream_t s) {
+  const int32_t rows = hi - lo;
+  if ((int64_t)rows * shares > part_rows)
+    return set_error(TG_EDEVICE, "bc_batched: %d rows in %d shares, room for %lld", rows, shares, (long long)part_rows);
+  hipLaunchKernelGGL(k_bb_shared<Op>, dim3((unsigned)std::min<int32_t>(rows, 16384), (unsigned)shares), dim3(BLOCK), 0,
+                     s, queue + lo, qmask + lo, rows, off, col, mask, op, part);
+  hipLaunchKernelGGL(k_bb_shared_finish<Op>, dim3((unsigned)((rows + 3) / 4)), dim3(BLOCK), 0, s, queue + lo,
+                     qmask + lo, rows, shares, part, op);
+  return TG_OK;
 }
 
 // One pass over a level's queue (plan P): rows of off / col, masks `mask`.
+// The rows of a bin whose level holds few are shared by several blocks like
+// the hubs', as a wave's edges are a chain of dependent reads.  RMAT-18, 4
+// sources: 10 hubs 53 us in 16 shares, 19 in 64; 113 rows of the BLOCK bin 122
+// us a block each, 19 in 18 shares with their second launch; 78 rows of the
+// WAVE bin 50 us a wave each, 14 so; the call 1.64 -> 1.44 ms (lines at half
+// or twice the rows: the same).  RMAT-20, 64 sources: 6.44 -> 6.18 ms.
+constexpr int32_t SHARED_BLOCK_ROWS = 512, SHARED_WAVE_ROWS = 1024;
+
 template <class Op>
 int launch_rows(const Plan &P, const int32_t *queue, const u64 *qmask, const int64_t *off, const int32_t *col,
                 const u64 *mask, const Op &op, double *part, int64_t part_rows, hipStream_t s) {
   const int32_t hubs = P.pos[1], split = P.pos[BIN_WAVE], count = P.count;
-  if (hubs > 0) {
-    const int shares = hub_shares(part_rows, hubs);
-    hipLaunchKernelGGL(k_bb_hubs<Op>, dim3((unsigned)std::min<int32_t>(hubs, 16384), (unsigned)shares), dim3(BLOCK), 0,
-                       s, queue, qmask, hubs, off, col, mask, op, part);
-    hipLaunchKernelGGL(k_bb_hubs_finish<Op>, dim3((unsigned)((hubs + 3) / 4)), dim3(BLOCK), 0, s, queue, qmask, hubs,
-                       shares, part, op);
+  int32_t done = 0;
+  const auto shared = [&](int32_t hi, int least, int most) -> int {
+    const int shares = row_shares(part_rows, hi - done, least, most);
+    TG_TRY(launch_shared(done, hi, shares, part_rows, queue, qmask, off, col, mask, op, part, s));
+    done = hi;
+    return TG_OK;
+  };
+  // (the partial sums have room for the hubs, but not for any bin's rows)
+  const auto few = [&](int32_t rows, int32_t most) {
+    return rows > 0 && rows <= most && 2 * (int64_t)rows <= part_rows;
+  };
+  if (hubs > 0) TG_TRY(shared(hubs, 16, 64));
+  if (split > hubs) {
+    if (few(split - hubs, SHARED_BLOCK_ROWS)) {
+      TG_TRY(shared(split, 1, 32));
+    } else {
+      hipLaunchKernelGGL(k_bb_block<Op>, dim3((unsigned)std::min<int32_t>(split - hubs, 16384)), dim3(BLOCK), 0, s,
+                         queue, qmask, hubs, split, off, col, mask, op);
+      done = split;
+    }
   }
-  if (split > hubs)
-    hipLaunchKernelGGL(k_bb_block<Op>, dim3((unsigned)std::min<int32_t>(split - hubs, 16384)), dim3(BLOCK), 0, s,
-                       queue, qmask, hubs, split, off, col, mask, op);
-  if (count > split) {
-    const RowSpans R{split, P.pos[BIN_G16], P.pos[BIN_G4], count};
+  if (few(P.pos[BIN_G16] - split, SHARED_WAVE_ROWS)) TG_TRY(shared(P.pos[BIN_G16], 1, 2));
+  if (count > done) {
+    const RowSpans R{done, P.pos[BIN_G16], P.pos[BIN_G4], count};
     hipLaunchKernelGGL(k_bb_rows<Op>, dim3((unsigned)std::min<int64_t>((R.waves() + 3) / 4, 32768)), dim3(BLOCK), 0, s,
                        queue, qmask, R, off, col, mask, op);
   }

@@ -502,3 +502,26 @@ def test_hybrid_messages_of_each_size(gpu, n, alpha):
     want = oracle.pagerank(g.offsets, g.cols, iterations=iters)
     r = gpu.pagerank(P, iterations=iters).cpu().numpy().astype(np.float64)
     assert np.all(np.abs(r - want) <= (2 * iters + 2) * 2.0**-24 * want)
+
+
+# ---------------------- betweenness rows shared by several blocks
+
+@pytest.mark.parametrize("rows", [1, 511, 512, 513, 1024, 1025])
+@pytest.mark.parametrize("deg", [16, 64, 300])
+def test_betweenness_rows_shared_or_not(gpu, rows, deg):
+    """`rows` vertices of equal degree, at and past the most that are shared,
+    in the WAVE, BLOCK and HUB bin, with room in the partial sums for many,
+    few and (16 edges a row) not all of them; sources on both sides."""
+    rng = np.random.default_rng(rows + deg)
+    pool = max(2 * deg, 400)
+    cols = np.concatenate([rng.choice(pool, deg, replace=False) for _ in range(rows)])
+    src = np.repeat(pool + np.arange(rows), deg)
+    # the pool hangs together by a ring (levels of several vertices each)
+    g = graphgen.from_edges(pool + rows, np.r_[src, np.arange(pool)], np.r_[cols, (np.arange(pool) + 1) % pool],
+                            symmetrize=True)
+    srcs = [0, pool // 3, pool, pool + rows - 1]
+    ref = oracle.bc(g.offsets, g.cols, srcs)
+    bins = {"g4_min_deg": 2, "g16_min_deg": 4, "wave_min_deg": 8, "block_min_deg": 50, "hub_min_deg": 200}
+    for f in (gpu.bc, gpu.bc_batched):
+        got = f(load(gpu, g, None, bins), srcs).cpu().numpy().astype(np.float64)
+        assert np.all(np.abs(got - ref) <= 1e-5 * np.abs(ref) + 1e-6 * max(ref.max(), 1.0))
