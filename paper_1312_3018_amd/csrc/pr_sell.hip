@@ -40,8 +40,9 @@
 // an iteration: 433 us in row blocks, 306 us in slices of 32-bit codes whose
 // classes lie interleaved in memory (4 of an XCD's 16 L2 channels serve all
 // its gathers), 209 us so; the 20-iteration call 9.48 -> 4.77 ms.  R-MAT with
-// 30,011 vertices, directed: 19.6 us per iteration in four launches, 8.9 us
-// in one.
+// 30,011 vertices, directed, dangling mass dropped: 19.6 us per iteration in
+// four launches, 7.8 us in one (8.9 with the sums of the dangling mass that
+// this mode has no use for).
 #include <string.h>
 
 #include <algorithm>
@@ -63,7 +64,10 @@ constexpr int WIN = 512;   // rows sorted together
 constexpr int LONG_CLS = 128, LONG_WHOLE = 32;
 constexpr int CHUNK = 1024;  // words of a piece of a longer row
 constexpr int ST = 1024;   // threads per workgroup of the gather
-constexpr int FLY_CLS = 16, FLY_WHOLE = 8;  // columns whose gathers a wave has in flight (codes: twice as many more)
+// Columns whose gathers a wave has in flight (codes: twice as many more).
+// Classes: 8 0.5 % slower, 24 spills; whole (waves have a few columns only):
+// 30,011 vertices, 20 iterations, 16 172 us, 8 166, 4 163.
+constexpr int FLY_CLS = 16, FLY_WHOLE = 4;
 constexpr int FLYG = 8;    // edges a lane has in flight in a giant
 constexpr int SHARES = 4;  // per wave (1: 5.23 ms, 2: 5.00, 4: 4.77, 8: 4.75)
 constexpr int PAD = LINE;  // floats before contribution 0 (the last is the zero slot)
@@ -450,14 +454,17 @@ __global__ __launch_bounds__(ST) void k_pr_sell(const SellArgs A) {
     for (int i = lane; i < WIN; i += 64) win[i] = __uint_as_float(NONE);
     __syncthreads();
   }
-  double add = 0.0, dang = 0.0;
-  if (!CLS) {
-    // the dangling mass of the last iteration, summed by every wave alike
+  double add = A.base, dang = 0.0;
+  // the dangling mass of the last iteration, summed by every wave alike; not
+  // before its first columns are on their way
+  bool have = CLS || A.drop;
+  const auto dangling = [&]() {
+    if (have) return;
+    have = true;
     double D = 0.0;
     for (int i = lane; i < A.np_in; i += 64) D += A.dang_in[i];
-    D = wave_sum(D);
-    add = A.base + A.d * (A.drop ? 0.0 : D) * A.inv_n;
-  }
+    add = A.base + A.d * wave_sum(D) * A.inv_n;
+  };
   // the sum s of row v, of out-degree od, is known
   const auto finish = [&](int32_t v, double s, int32_t od) {
     if (CLS) {
@@ -472,6 +479,7 @@ __global__ __launch_bounds__(ST) void k_pr_sell(const SellArgs A) {
   if (!CLS) {
     for (int32_t i = blockIdx.x; i < A.ngiants; i += gridDim.x) {
       const Giant G = A.giants[i];
+      dangling();
       double s = 0.0;
       for (int32_t e = t; e < G.len; e += FLYG * ST) {
         uint32_t c[FLYG];
@@ -512,6 +520,7 @@ __global__ __launch_bounds__(ST) void k_pr_sell(const SellArgs A) {
     };
     load(j, c0);
     load(j + FLY, c1);
+    dangling();
     uint32_t row = NONE;
     int32_t od = 0;
     double acc = 0.0;
@@ -582,16 +591,15 @@ __global__ __launch_bounds__(ST) void k_pr_sell(const SellArgs A) {
     flush();
     if (CLS) store_window();
   }
-  if (CLS) return;
-  // dangling partial of this workgroup, waves added in order
+  if (CLS || A.drop) return;
+  // dangling partial of this workgroup
   dang = wave_sum(dang);
   __syncthreads();
   if (lane == 0) red[wv] = dang;
   __syncthreads();
-  if (t == 0) {
-    double s = 0.0;
-    for (int q = 0; q < ST / 64; ++q) s += red[q];
-    A.dang_out[blockIdx.x] = s;
+  if (t < ST / 64) {
+    const double s = group_sum(red[t], ST / 64);
+    if (t == 0) A.dang_out[blockIdx.x] = s;
   }
 }
 
