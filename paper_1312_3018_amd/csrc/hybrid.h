@@ -105,6 +105,7 @@ struct HybridState {
   int32_t *h_stage = nullptr;
   long long *h_clock = nullptr;  // pinned: clocks around the small messages, [direction][parity][2]
   bool by_kernel[2][2] = {};     // whether the last one of [direction][parity] crossed so
+  bool waited[2] = {};           // [parity]: the last one needs no event of its own
   int clock_khz = 100000;
   Box out, in;                  // GPU-to-host and host-to-GPU messages
   hipStream_t cs_d2h = nullptr, cs_h2d = nullptr;  // copy streams (default priority)

@@ -466,6 +466,15 @@ __global__ __launch_bounds__(COPY_THREADS) void k_message(char *dst, const char 
   if (clock2 && blockIdx.x == 0 && threadIdx.x == 0) clock2[1] = wall_clock64();
 }
 
+// A search's device state at its start.
+__global__ __launch_bounds__(BLOCK) void k_hybrid_bfs_clear(uint32_t *visited, uint32_t *prev, int64_t nwords,
+                                                            int32_t *level, int64_t n, int32_t *sent, int64_t nslots) {
+  const int64_t i = (int64_t)blockIdx.x * BLOCK + threadIdx.x;
+  if (i < nwords) visited[i] = prev[i] = 0u;
+  if (i < n) level[i] = TG_INF;
+  if (i < nslots) sent[i] = 0;
+}
+
 inline unsigned nblk(int64_t n) { return (unsigned)std::max<int64_t>((n + BLOCK - 1) / BLOCK, 1); }
 inline unsigned select_grid(int64_t n) { return (unsigned)std::min<int64_t>(nblk(n), 8192); }
 
@@ -522,11 +531,13 @@ double clock_ms(const HybridState &h, const long long *clock2) {
 }
 
 // GPU -> host: once the GPU stream has produced box b, copy `bytes` of it.
-int post_d2h(HybridState &h, int b, size_t bytes, hipStream_t s) {
+// `stream_waited`: the caller waits for s before wait_d2h.
+int post_d2h(HybridState &h, int b, size_t bytes, hipStream_t s, bool stream_waited = false) {
   h.by_kernel[0][b] = bytes > 0 && bytes <= SMALL_MESSAGE;
+  h.waited[b] = stream_waited && h.by_kernel[0][b];
   if (h.by_kernel[0][b]) {
     TG_TRY(launch_message(h.out.h[b], h.out.d[b], bytes, h.h_clock + 2 * b, s));
-    TG_HIP(hipEventRecord(h.ev_d2h[b][1], s));
+    if (!h.waited[b]) TG_HIP(hipEventRecord(h.ev_d2h[b][1], s));
     return TG_OK;
   }
   TG_HIP(hipEventRecord(h.ev_ready[b], s));
@@ -539,7 +550,7 @@ int post_d2h(HybridState &h, int b, size_t bytes, hipStream_t s) {
 
 // Waits for it; adds the copy's time.
 int wait_d2h(HybridState &h, int b, double *ms) {
-  TG_HIP(hipEventSynchronize(h.ev_d2h[b][1]));
+  if (!h.waited[b]) TG_HIP(hipEventSynchronize(h.ev_d2h[b][1]));
   if (h.by_kernel[0][b]) {
     *ms += clock_ms(h, h.h_clock + 2 * b);
     return TG_OK;
@@ -715,10 +726,9 @@ int hybrid_bfs(tg_partition *p, const int32_t *roots, int32_t nr, int32_t *level
     const int32_t root = roots[r];
     const int32_t gl = p->h_l_of_g[root];
     uint32_t *visited = ws.bits_a;
-    TG_HIP(hipMemsetAsync(visited, 0, ws.nwords * sizeof(uint32_t), s));
-    TG_HIP(hipMemsetAsync(ws.bits_b, 0, ws.nwords * sizeof(uint32_t), s));
-    TG_TRY(fill_i32(ws.state, g.n, TG_INF, s));
-    if (no) TG_TRY(fill_i32(h.d_osent, no, 0, s));
+    hipLaunchKernelGGL(k_hybrid_bfs_clear, dim3(nblk(std::max<int64_t>({g.n, no, ws.nwords}))), dim3(BLOCK), 0, s,
+                       visited, ws.bits_b, ws.nwords, ws.state, g.n, h.d_osent, no);
+    TG_HIP(hipGetLastError());
     std::fill(cvis.begin(), cvis.end(), 0);
     std::fill(clev.begin(), clev.end(), TG_INF);
     cfront.clear();
@@ -748,7 +758,7 @@ int hybrid_bfs(tg_partition *p, const int32_t *roots, int32_t nr, int32_t *level
         TG_TRY(launch_gather(h.dout, s,
                              BfsOut{h.dout.rsrc, ws.state, L, h.d_osent, reinterpret_cast<uint32_t *>(h.out.d[b])},
                              reinterpret_cast<int32_t *>(h.dout.partials_i)));
-        TG_TRY(post_d2h(h, b, (size_t)nwo * 4, s));
+        TG_TRY(post_d2h(h, b, (size_t)nwo * 4, s, true));
       }
       // the host frontier to the GPU, which reduces the host-to-GPU channel
       if (host_front) {
@@ -771,7 +781,7 @@ int hybrid_bfs(tg_partition *p, const int32_t *roots, int32_t nr, int32_t *level
       TG_TRY(launch_message(ws.h_plan, ws.plan, sizeof(Plan), nullptr, s));
       // host: expand its frontier over its local edges while the GPU runs
       const auto tc = clk::now();
-#pragma omp parallel
+#pragma omp parallel if (host_front)
       {
         auto &mine = tl[omp_get_thread_num()];
 #pragma omp for schedule(dynamic, 64)
