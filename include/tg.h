@@ -131,7 +131,9 @@ int partition_by_degree(const tg_graph *g, int strategy, double cpu_edge_share,
  *                betweenness and hybrid searches; "bfs_batch_roots" (fewest
  *                roots of a call without parents that run in the 64-slot
  *                engine of bfs_batched; 0: never, -1: by the graph's size,
- *                the default unless another bfs_ key is given);
+ *                the default unless another bfs_ key is given; with
+ *                mapped_edges more than a root per 65536 vertices in any
+ *                case);
  *   SSSP         "sssp_delta" (0: plain frontier; > 0: near/far step),
  *                "sssp_lanes" (roots in flight, 1..8), "sssp_pull" (a
  *                superstep whose frontier holds more than this percentage
@@ -152,7 +154,9 @@ int partition_by_degree(const tg_graph *g, int strategy, double cpu_edge_share,
  *                is pulled by the vertices whose distance is not yet final
  *                when their out-degree sum times sssp_hpull / 100 is below
  *                the bucket's; 0: always pushed), "sssp_batch_roots" (as
- *                bfs_batch_roots, for sssp_batched's engine);
+ *                bfs_batch_roots, for sssp_batched's engine; unless it
+ *                is 0, fewer roots share the launches of the bucket
+ *                schedule where that schedule is on);
  *   layout       "mapped_edges" (1: the edge arrays -- neighbour ids, weights,
  *                in-edge ids -- stay in pinned host memory mapped into the
  *                GPU and kernels read them over the host link, for graphs

@@ -1063,9 +1063,13 @@ int check_roots(const tg_partition *p, const int32_t *roots, int32_t nr, const c
 // BFS (levels only).  2 roots: 2^13..2^20 vertices 0.49-0.72 / 0.25-0.67,
 // RMAT-22 0.63 / 1.01; 4 roots: RMAT-22 1.09 / 1.10, RMAT-23 1.61 / 2.61; 8:
 // RMAT-23 3.74 / 3.06, RMAT-24 3.78 / 3.29; 64: RMAT-22 22.5 / 3.84, RMAT-24
-// 28.1 / 10.9.
+// 28.1 / 10.9.  With the edges in host memory the single searches, which look
+// at few edges, hold out longer: 2^18, 8 roots 1.82 / 1.23; 2^20, 8: 1.98 /
+// 3.15, 64: 14.2 / 6.5; RMAT-22, 8: 4.61 / 9.69, 64: 30.4 / 28.9; RMAT-24, 64:
+// 120 / 129.
 bool bfs_in_engine(const tg_partition *p, int32_t nr) {
   const int64_t from = p->tune.bfs_batch_roots, n = p->gpu.n;
+  if (p->gpu.mapped_edges && nr <= (n >> 16)) return false;
   if (from >= 0) return from > 0 && nr >= from;
   return nr >= (n <= (1 << 20) ? 2 : n <= (1 << 22) ? 4 : 8);
 }
@@ -1112,10 +1116,12 @@ bool sssp_in_buckets(const tg_partition *p, int32_t nr) {
 // 1.95, 4: 2.58 / 2.32; 2^19, 1: 1.29 / 1.75, 2: 2.17 / 1.90; 2^20, 1: 1.88 /
 // 1.90, 2: 3.76 / 2.19.  Directed: 50,021 vertices, 1: 0.27 / 0.93, 32: 3.59 /
 // 5.35; 2^17, 12: 3.53 / 4.57; 2^18, 5: 2.51 / 2.52; 2^19, 3: 2.47 / 2.58; 2^20,
-// 1: 1.27 / 2.00, 2: 2.99 / 2.63.
+// 1: 1.27 / 2.00, 2: 2.99 / 2.63.  Edges in host memory, which a round reads
+// more often: 2^18, 1: 2.05 / 2.27; 2^20, 1: 7.40 / 3.98.
 bool sssp_in_rounds(const tg_partition *p, int32_t nr) {
   static const int sym[] = {32, 20, 16, 8, 6, 4, 3, 1, 1}, dir[] = {32, 32, 32, 32, 32, 12, 5, 3, 1};  // 2^12 .. 2^20
-  if (p->tune.sssp_batch_roots >= 0 || nr <= 0 || p->gpu.n <= 0 || p->gpu.n > (1 << 20)) return false;
+  if (p->tune.sssp_batch_roots >= 0 || nr <= 0 || p->gpu.n <= 0 || p->gpu.n > (1 << (p->gpu.mapped_edges ? 18 : 20)))
+    return false;
   int lg = 12;  // n <= 2^lg
   while (((int64_t)1 << lg) < p->gpu.n) ++lg;
   return nr <= (p->gpu.in_alias ? sym : dir)[lg - 12];

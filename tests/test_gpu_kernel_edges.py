@@ -525,3 +525,19 @@ def test_betweenness_rows_shared_or_not(gpu, rows, deg):
     for f in (gpu.bc, gpu.bc_batched):
         got = f(load(gpu, g, None, bins), srcs).cpu().numpy().astype(np.float64)
         assert np.all(np.abs(got - ref) <= 1e-5 * np.abs(ref) + 1e-6 * max(ref.max(), 1.0))
+
+
+@pytest.mark.parametrize("n,count", [(65535, 1), (65536, 2), (131072, 2), (131072, 3), (300000, 4), (300000, 5)])
+def test_routes_with_edges_in_host_memory(gpu, n, count):
+    """Roots on either side of one per 65,536 vertices, and SSSP on either
+    side of 2^18 vertices."""
+    rng = np.random.default_rng(n + count)
+    g = graphgen.from_edges(n, rng.integers(0, n, 3 * n), rng.integers(0, n, 3 * n), symmetrize=True)
+    w = graphgen.weights(g, seed=2)
+    P = load(gpu, g, w, {"mapped_edges": 1})
+    roots = rng.integers(0, n, count).tolist()
+    lev, dist = gpu.bfs(P, roots).cpu().numpy(), gpu.sssp(P, roots[:2]).cpu().numpy()
+    for i, r in enumerate(roots):
+        assert np.array_equal(lev[i], oracle.bfs(g.offsets, g.cols, r)), i
+        if i < 2:
+            assert np.array_equal(dist[i], oracle.sssp(g.offsets, g.cols, w, r)), i
