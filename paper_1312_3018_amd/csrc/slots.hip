@@ -195,6 +195,46 @@ __global__ __launch_bounds__(BLOCK) void k_ms_sssp_expand(const Plan *__restrict
   }
 }
 
+// The same for few slots: lanes by degree bin, a lane walks an edge's slots.
+// (Rows that leave most of a wave's lanes without a slot cost more than they
+// save, and so do the marks of minima that did not win: those return here.)
+__global__ __launch_bounds__(BLOCK) void k_ms_sssp_expand_few(const Plan *__restrict__ Pp,
+                                                              const int32_t *__restrict__ queue,
+                                                              const int64_t *__restrict__ hubpref,
+                                                              const int64_t *__restrict__ off,
+                                                              const int32_t *__restrict__ col,
+                                                              const int32_t *__restrict__ wgt, const u64 *frontier,
+                                                              SsspArgs A, int64_t hub_chunk) {
+  const Plan &P = load_plan(Pp);
+  const int64_t total = P.vb[NBIN];
+  for (int64_t vb = blockIdx.x; vb < total; vb += gridDim.x) {
+    const Assign a = assign_work(vb, P, queue, nullptr, hubpref, off, hub_chunk);
+    if (!a.ok) continue;
+    const u64 m = frontier[a.v];
+    if (m == 0) continue;
+    const int32_t *dv = A.dist + (int64_t)a.v * kSlots;
+    for (int64_t e = a.e_begin + a.lane; e < a.e_end; e += a.stride) {
+      const int32_t nb = stream_load(col + e);
+      const int32_t w = stream_load(wgt + e);
+      int32_t *dn = A.dist + (int64_t)nb * kSlots;
+      u64 gained = 0;
+      for (u64 bits = m; bits; bits &= bits - 1) {
+        const int s = __ffsll((long long)bits) - 1;
+        const int64_t nd = (int64_t)dv[s] + (int64_t)w;
+        if (nd >= (int64_t)TG_INF) {
+          if (dn[s] == TG_INF) {
+            atomicOr(A.ovf + nb, 1ull << s);
+            atomicOr(A.ovf_slots, 1ull << s);
+          }
+        } else if (nd < (int64_t)dn[s] && nd < (int64_t)atomicMin(dn + s, (int32_t)nd)) {
+          gained |= 1ull << s;
+        }
+      }
+      if (gained && atomicOr(A.next + nb, gained) == 0) atomicOr(A.touched + (nb >> 5), 1u << (nb & 31));
+    }
+  }
+}
+
 __global__ __launch_bounds__(BLOCK) void k_ms_clear(const Plan *__restrict__ Pp, const int32_t *__restrict__ queue,
                                                     u64 *frontier) {
   const int32_t count = Pp->count;
@@ -716,6 +756,11 @@ static void level_rows(const SlotEngine &E, LevelRow &lr, LevelRowWide &lw) {
 // every vertex's row of ids and masks, a push only the frontier's, but with
 // atomics.
 constexpr u64 SSSP_PULL_SHARE = 8;  // one in
+// Up to this many slots are pushed edge by edge and not pulled.  (ms a call,
+// edge by edge / rows and pulls: symmetric RMAT-20, 1 slot 1.65 / 3.90, 4 3.29
+// / 4.55; RMAT-22, 1 5.37 / 11.3, 4 12.5 / 15.6; uniform of 2^20, 4 4.58 / 5.71;
+// directed RMAT-20, 1 1.40 / 2.05, 8 4.14 / 7.60.)
+int sssp_few(const GpuPart &g) { return g.in_alias ? 4 : 16; }
 
 int SlotEngine::launch_step() {
   const GpuPart &g = p->gpu;
@@ -729,7 +774,7 @@ int SlotEngine::launch_step() {
       pulled = ms_pull_slots(mf, mu, alive, p->tune);
       all_pull = pulled == alive;
     } else {
-      all_pull = g.in_alias && pull_edges * SSSP_PULL_SHARE > (u64)g.m;
+      all_pull = g.in_alias && __builtin_popcountll(alive) > sssp_few(g) && pull_edges * SSSP_PULL_SHARE > (u64)g.m;
     }
     // a queue made from the masks would miss the slots that join
     if (dense && joined) all_pull = true;
@@ -814,6 +859,10 @@ int SlotEngine::launch_sparse(u64 pulled) {
     const int tk = ktimer_start(s);
     if (kind == kSlotBfs) {
       TG_TRY(ms_expand(g, ws, t, hp, ws.queue, frontier, visited, next, alive, pulled, s));
+    } else if (hp.vb[NBIN] > 0 && __builtin_popcountll(alive) <= sssp_few(g)) {
+      hipLaunchKernelGGL(k_ms_sssp_expand_few, dim3(launch_grid(hp.vb[NBIN])), dim3(BLOCK), 0, s, ws.plan, ws.queue,
+                         ws.hubpref, g.out.off, g.out.col, g.out.w, frontier,
+                         SsspArgs{dist, next, ws.bits_a, ovf, ovf_slots}, t.hub_chunk);
     } else if (hp.vb[NBIN] > 0) {
       const int64_t lists = (hp.pos[BIN_ZERO] - hp.pos[BIN_G16] + LIST_ROWS - 1) / LIST_ROWS;
       hipLaunchKernelGGL(k_ms_sssp_expand, dim3(launch_grid(hp.vb[BIN_G16] + (lists + 3) / 4)), dim3(BLOCK), 0, s,
