@@ -792,7 +792,8 @@ int build_slices(tg_partition *p, hipStream_t s) {
   }
   S.nlr = lrows;
   S.waves = (cls ? grid / NS : grid) * (ST / 64);
-  S.shares = S.waves * (cls ? SHARES : 1);
+  // (a share is not worth taking for less than 8 columns)
+  S.shares = cls ? (int32_t)std::max<int64_t>(1, std::min<int64_t>((int64_t)S.waves * SHARES, columns / (NS * 8))) : S.waves;
   const size_t nl = (size_t)std::max<int64_t>(lrows, 1);
   const size_t hwords = (size_t)(columns / 64) + 66;
   TG_TRY(dalloc(S.arena, &S.at.code, (size_t)std::max<int64_t>(columns, 1) * 64));
