@@ -241,15 +241,12 @@ __global__ __launch_bounds__(BLOCK) void k_bb_deepest(const int32_t *__restrict_
 // score[v] += the vertex's delta row: 16 lanes a row, four sources a lane.
 __global__ __launch_bounds__(BLOCK) void k_bb_score(const float4 *__restrict__ delta, int64_t n,
                                                     double *__restrict__ score) {
-  const int64_t t = (int64_t)blockIdx.x * BLOCK + threadIdx.x;
-  const int64_t v = t >> 4;
-  double x = 0.0;
-  if (v < n) {
+  // (a row's 16 lanes are in the loop together)
+  for (int64_t t = (int64_t)blockIdx.x * BLOCK + threadIdx.x; t < n * 16; t += (int64_t)gridDim.x * BLOCK) {
     const float4 d = delta[t];
-    x = ((double)d.x + (double)d.y) + ((double)d.z + (double)d.w);
+    const double x = group_sum(((double)d.x + (double)d.y) + ((double)d.z + (double)d.w), 16);
+    if ((t & 15) == 0 && x != 0.0) score[t >> 4] += x;
   }
-  x = group_sum(x, 16);
-  if (v < n && (t & 15) == 0 && x != 0.0) score[v] += x;
 }
 
 struct Sources {
@@ -498,7 +495,7 @@ int gpu_bc_batched(tg_partition *p, const int32_t *sources, int32_t ns, hipStrea
         TG_HIP(hipMemsetAsync(child, 0, (size_t)n * sizeof(u64), s));
         std::swap(child, own);
       }
-      hipLaunchKernelGGL(k_bb_score, dim3((unsigned)((g.n * 16 + BLOCK - 1) / BLOCK)), dim3(BLOCK), 0, s,
+      hipLaunchKernelGGL(k_bb_score, dim3((unsigned)std::min<int64_t>(nblk(g.n * 16), 16384)), dim3(BLOCK), 0, s,
                          reinterpret_cast<const float4 *>(B.delta), g.n, p->ws.bc_acc);
       TG_HIP(hipGetLastError());
     }

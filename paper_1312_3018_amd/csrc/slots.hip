@@ -572,9 +572,13 @@ __global__ __launch_bounds__(BLOCK) void k_ms_release(u64 *visited, u64 *ovf, in
     if (ovf) ovf[v] &= ~mask;
   }
 }
+// (a launch's threads are counted in 32 bits: 64 a vertex would wrap around,
+// unreported, from 2^26 vertices on)
+constexpr int64_t ROW_GRID = 16384;
 __global__ __launch_bounds__(BLOCK) void k_ms_release_dist(int32_t *dist, int64_t n, u64 mask) {
-  const int64_t i = (int64_t)blockIdx.x * BLOCK + threadIdx.x;
-  if (i < n * kSlots && ((mask >> (i & (kSlots - 1))) & 1ull)) dist[i] = TG_INF;
+  if (!((mask >> (threadIdx.x & (kSlots - 1))) & 1ull)) return;
+  for (int64_t i = (int64_t)blockIdx.x * BLOCK + threadIdx.x; i < n * kSlots; i += (int64_t)gridDim.x * BLOCK)
+    dist[i] = TG_INF;
 }
 
 // Levels of the slots in `mask` into their outputs, vertices in original id
@@ -611,25 +615,27 @@ __global__ __launch_bounds__(BLOCK) void k_ms_bfs_collect(const u64 *__restrict_
 }
 
 // Distances of the slots in `mask` into their outputs: a block takes 64
-// vertices in original id order, reads their rows (lane = slot) into LDS and
-// writes each slot's 64 values (lane = vertex).
+// vertices in original id order at a time, reads their rows (lane = slot)
+// into LDS and writes each slot's 64 values (lane = vertex).
 __global__ __launch_bounds__(BLOCK) void k_ms_sssp_collect(const int32_t *__restrict__ dist,
                                                            const int32_t *__restrict__ l_of_g, int64_t V, u64 mask,
                                                            SlotTable tab) {
   __shared__ int32_t tile[64][kSlots + 1];
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int64_t g0 = (int64_t)blockIdx.x * 64;
-  const int32_t l = g0 + lane < V ? l_of_g[g0 + lane] : 0;  // past the end: any row
-  int32_t x[16];
+  for (int64_t g0 = (int64_t)blockIdx.x * 64; g0 < V; g0 += (int64_t)gridDim.x * 64) {
+    const int32_t l = g0 + lane < V ? l_of_g[g0 + lane] : 0;  // past the end: any row
+    int32_t x[16];
 #pragma unroll
-  for (int j = 0; j < 16; ++j)
-    x[j] = dist[(int64_t)__builtin_amdgcn_readlane(l, w * 16 + j) * kSlots + lane];
+    for (int j = 0; j < 16; ++j)
+      x[j] = dist[(int64_t)__builtin_amdgcn_readlane(l, w * 16 + j) * kSlots + lane];
+    __syncthreads();
 #pragma unroll
-  for (int j = 0; j < 16; ++j) tile[w * 16 + j][lane] = x[j];
-  __syncthreads();
-  if (g0 + lane >= V) return;
-  for (int s = w * 16; s < w * 16 + 16; ++s)
-    if ((mask >> s) & 1ull) __builtin_nontemporal_store(tile[lane][s], tab.out[s] + g0 + lane);
+    for (int j = 0; j < 16; ++j) tile[w * 16 + j][lane] = x[j];
+    __syncthreads();
+    if (g0 + lane < V)
+      for (int s = w * 16; s < w * 16 + 16; ++s)
+        if ((mask >> s) & 1ull) __builtin_nontemporal_store(tile[lane][s], tab.out[s] + g0 + lane);
+  }
 }
 
 __global__ void k_clear_bits64(u64 *word, u64 mask) {
@@ -934,8 +940,8 @@ int SlotEngine::retire(u64 mask, u64 *overflow) {
     if (((mask >> k) & 1ull) && tab.out[k]) outs |= 1ull << k;
   if (kind == kSlotSssp) {
     if (outs)
-      hipLaunchKernelGGL(k_ms_sssp_collect, dim3((unsigned)((V + 63) / 64)), dim3(BLOCK), 0, s, dist, g.l_of_g, V,
-                         outs, tab);
+      hipLaunchKernelGGL(k_ms_sssp_collect, dim3((unsigned)std::min<int64_t>((V + 63) / 64, ROW_GRID)), dim3(BLOCK), 0,
+                         s, dist, g.l_of_g, V, outs, tab);
     // slots that saw an overflowing candidate get the exact verdict
     TG_HIP(hipMemcpyAsync(h_ovf, ovf_slots, sizeof(u64), hipMemcpyDeviceToHost, s));
     TG_HIP(hipStreamSynchronize(s));
@@ -947,8 +953,8 @@ int SlotEngine::retire(u64 mask, u64 *overflow) {
       hipLaunchKernelGGL(k_ms_release, dim3(grid), dim3(BLOCK), 0, s, nullptr, ovf, g.n, mask);
       TG_HIP(hipMemcpyAsync(h_ovf + 1, ovf_slots + 1, sizeof(u64), hipMemcpyDeviceToHost, s));
     }
-    hipLaunchKernelGGL(k_ms_release_dist, dim3((unsigned)((g.n * kSlots + BLOCK - 1) / BLOCK)), dim3(BLOCK), 0, s,
-                       dist, g.n, mask);
+    hipLaunchKernelGGL(k_ms_release_dist, dim3((unsigned)std::min<int64_t>(nblk(g.n * kSlots), ROW_GRID)), dim3(BLOCK),
+                       0, s, dist, g.n, mask);
     TG_HIP(hipGetLastError());
     TG_HIP(hipStreamSynchronize(s));
     if (flagged && overflow) *overflow = h_ovf[1] & flagged;

@@ -216,6 +216,26 @@ def test_batched_betweenness_deep_graph_grows_its_queue(gpu):
         assert np.all(np.abs(got - ref) <= 1e-5 * np.abs(ref) + 1e-6 * ref.max())
 
 
+def test_batched_distances_past_2_to_26_vertices(gpu):
+    """64 slots a vertex are more than 2^32 entries: a slot's distances are
+    cleared when it retires, so that the next search in it starts afresh."""
+    import torch
+    n, k = (1 << 26) + 5, 1000
+    i = np.arange(k)
+    col = np.stack([i - 1, i + 1], 1).ravel()
+    deg = np.zeros(n + 1, dtype=np.int64)
+    deg[1:k + 1] = 2
+    deg[1] = deg[k] = 1
+    G = gpu.graph_load_csr(n, np.cumsum(deg), col[(col >= 0) & (col < k)], np.full(2 * k - 2, 300),
+                           symmetric=True, validate=False)
+    P = gpu.partition_by_degree(G)
+    out = torch.empty((2, n), dtype=torch.int32, device="cuda")
+    for r in (0, k - 1, 500):
+        gpu.sssp_batched(P, [r, n - 1], out)
+        assert np.array_equal(out[0, :k].cpu().numpy(), 300 * np.abs(i - r)), r
+        assert int((out[0] != INF).sum()) == k and int((out[1] != INF).sum()) == 1
+
+
 # ------------------------------------- calls routed to the 64-slot engines
 
 @pytest.mark.parametrize("sym", [True, False])

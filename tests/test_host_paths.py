@@ -1,0 +1,106 @@
+"""Host code of libtg.so that only runs with a device (launch shapes, what
+follows a failed allocation), on the CPU: a process per test loads the library
+over the runtime of fake_hip.c, whose kernels do nothing."""
+import os
+import subprocess
+import sys
+
+import pytest
+
+import paper_1312_3018_amd as tg
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+
+PRELUDE = """
+import ctypes, sys
+import numpy as np
+fake = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)
+lib = ctypes.CDLL(sys.argv[2])
+OK, ENOMEM, ETIMEOUT, SYMMETRIC = 0, {enomem}, {etimeout}, {symmetric}
+for f, t in (("fake_thread_limit", ctypes.c_uint64), ("fake_malloc_limit", ctypes.c_size_t)):
+    getattr(fake, f).argtypes = [t]
+fake.fake_mark_copies.argtypes = [ctypes.c_size_t, ctypes.c_size_t]
+fake.fake_most_threads.restype = ctypes.c_uint64
+lib.tg_last_error.restype = ctypes.c_char_p
+p64, p32 = np.ctypeslib.ndpointer(np.int64), np.ctypeslib.ndpointer(np.int32)
+vp, i32, i64 = ctypes.c_void_p, ctypes.c_int32, ctypes.c_int64
+lib.graph_load_csr.argtypes = [i64, i64, p64, p32, vp, ctypes.c_uint32, vp, ctypes.POINTER(vp)]
+lib.partition_by_degree.argtypes = [vp, ctypes.c_int, ctypes.c_double, ctypes.c_uint64, ctypes.c_char_p,
+                                    ctypes.POINTER(vp)]
+lib.bfs.argtypes = [vp, p32, i32, vp, vp, vp]
+for f in (lib.sssp, lib.bfs_batched, lib.sssp_batched, lib.bc, lib.bc_batched):
+    f.argtypes = [vp, p32, i32, vp, vp]
+lib.cc.argtypes = [vp, vp, vp]
+lib.pagerank.argtypes = [vp, ctypes.c_float, i32, i32, vp, vp]
+lib.partition_free.argtypes = [vp]
+lib.server_create.argtypes = [ctypes.c_char_p, ctypes.POINTER(vp)]
+lib.server_add_graph.argtypes = [vp, vp, ctypes.POINTER(i32)]
+lib.server_submit.argtypes = [vp, i32, i32, i32, vp, ctypes.POINTER(ctypes.c_uint64)]
+lib.server_wait.argtypes = [vp, ctypes.c_uint64, i64, vp]
+lib.server_destroy.argtypes = [vp]
+BUF = 4096  # an address no kernel writes to
+
+
+def path(n, length, weight=300, tuning=b"{{}}", symmetric=True):
+    "A partition of n vertices, the first `length` of them a path."
+    deg = np.zeros(n + 1, dtype=np.int64)
+    deg[1:length + 1] = 2
+    deg[1] = deg[length] = 1
+    off = np.cumsum(deg)
+    i = np.arange(length)
+    col = np.sort(np.stack([i - 1, i + 1], 1), 1).ravel()
+    col = np.ascontiguousarray(col[(col >= 0) & (col < length)], dtype=np.int32)
+    w = np.full(col.size, weight, dtype=np.int32)
+    G, P = vp(), vp()
+    check(lib.graph_load_csr(n, col.size, off, col, w.ctypes.data, SYMMETRIC if symmetric else 0, None,
+                             ctypes.byref(G)))
+    check(lib.partition_by_degree(G, 0, 0.0, 0, tuning, ctypes.byref(P)))
+    return P
+
+
+def roots(k):
+    return np.arange(k, dtype=np.int32)
+
+
+def check(rc, want=OK):
+    assert rc == want, (rc, lib.tg_last_error())
+"""
+
+
+@pytest.fixture(scope="module")
+def run(tmp_path_factory):
+    tg.require_native()
+    so = str(tmp_path_factory.mktemp("fake") / "libfakehip.so")
+    subprocess.run(["gcc", "-O1", "-shared", "-fPIC", "-I/opt/rocm/include", "-o", so,
+                    os.path.join(HERE, "fake_hip.c")], check=True)
+    prelude = PRELUDE.format(enomem=tg.TG_ENOMEM, etimeout=tg.TG_ETIMEOUT, symmetric=tg.TG_SYMMETRIC)
+
+    def go(script):
+        r = subprocess.run([sys.executable, "-c", prelude + script, so, tg.LIB_PATH], capture_output=True, text=True,
+                           timeout=110)
+        assert r.returncode == 0, r.stdout + r.stderr
+    return go
+
+
+# ------------------------------------------------------------ launch shapes
+
+@pytest.mark.parametrize("symmetric", [True, False])
+def test_grids_fit_every_vertex_count(run, symmetric):
+    """A launch's threads are counted in 32 bits and V may be 2^31 - 1: past a
+    fixed number of blocks no launch takes more than two threads per vertex."""
+    run(f"""
+n = 1 << 23
+P = path(n, 100, symmetric={symmetric})
+fake.fake_thread_limit(2 * n + 1)
+for k in (1, 2, 64):
+    check(lib.bfs_batched(P, roots(k), k, BUF, None))
+    check(lib.sssp_batched(P, roots(k), k, BUF, None))
+    check(lib.bfs(P, roots(k), k, BUF, None, None))
+    check(lib.bfs(P, roots(k), k, BUF, BUF, None))
+    check(lib.sssp(P, roots(k), k, BUF, None))
+    check(lib.bc(P, roots(k), k, BUF, None))
+    check(lib.bc_batched(P, roots(k), k, BUF, None))
+check(lib.cc(P, BUF, None))
+check(lib.pagerank(P, 0.85, 2, 0, BUF, None))
+assert fake.fake_most_threads() >= n
+""")
