@@ -105,6 +105,7 @@ struct tg_server {
 
   void run();
   void solo_worker(Lane *L);
+  void fail_lane(Lane &L, int status, const std::string &err);
 };
 
 namespace {
@@ -183,13 +184,28 @@ void tg_server::solo_worker(Lane *L) {
   }
 }
 
+// A superstep of the lane failed (mu held): its running queries end with the
+// error, and its engine, whose state is unknown, is made anew when the next
+// one is admitted.
+void tg_server::fail_lane(Lane &L, int status, const std::string &err) {
+  for (Query *&q : L.slot_q)
+    if (q) {
+      finish(this, q, status, err);
+      q = nullptr;
+    }
+  TG_QUIET(hipStreamSynchronize(L.stream));  // what it enqueued reads its buffers
+  L.eng.reset();
+  cv_done.notify_all();
+  cv_work.notify_all();  // memory freed: other lanes may admit
+}
+
 void tg_server::run() {
   TG_QUIET(hipSetDevice(device));
   std::unique_lock<std::mutex> lk(mu);
   for (;;) {
     // 1. every idle lane: admit waiting queries into free slots (within the
     //    memory cap), then start its next superstep if it has running slots
-    bool in_flight = false;
+    bool in_flight = false, failed = false;
     for (auto &lp : lanes) {
       Lane &L = *lp;
       if (!L.p || L.solo) continue;
@@ -228,13 +244,18 @@ void tg_server::run() {
         }
       }
       if (L.eng && L.eng->busy) {
-        if (L.eng->launch_step() == TG_OK) {
+        const int rc = L.eng->launch_step();
+        if (rc == TG_OK) {
           L.launched = true;
           in_flight = true;
+        } else {
+          fail_lane(L, rc, tg_last_error());
+          failed = true;
         }
       }
     }
     if (!in_flight) {
+      if (failed) continue;  // queries may wait for the slots and the memory freed
       if (stop) break;
       cv_work.wait(lk);
       continue;
@@ -248,25 +269,33 @@ void tg_server::run() {
     for (auto &lp : lanes) snap.push_back(lp.get());
     lk.unlock();
     std::vector<std::pair<Lane *, unsigned long long>> fin;
+    struct Broken {
+      Lane *lane;
+      int status;
+      std::string err;
+    };
+    std::vector<Broken> broken;
     bool progressed = false;
     for (Lane *lp : snap) {
       Lane &L = *lp;
-      if (!L.launched || hipStreamQuery(L.stream) != hipSuccess) continue;
+      // (any other error is finish_step's)
+      if (!L.launched || hipStreamQuery(L.stream) == hipErrorNotReady) continue;
       (void)hipGetLastError();  // hipStreamQuery reports "not ready" through the error state
       L.launched = false;
       progressed = true;
-      unsigned long long f = 0;
-      if (L.eng->finish_step(&f) == TG_OK && f) {
+      unsigned long long f = 0, ovf = 0;
+      int rc = L.eng->finish_step(&f);
+      if (rc == TG_OK && f) {
         for (int k = 0; k < kSlots; ++k)
           if ((f >> k) & 1ull) L.eng->tab.out[k] = L.slot_q[k]->out;
-        unsigned long long ovf = 0;
-        const int rc = L.eng->retire(f, &ovf);
+        rc = L.eng->retire(f, &ovf);
+      }
+      if (rc != TG_OK) {
+        broken.push_back(Broken{&L, rc, tg_last_error()});
+      } else if (f) {
         fin.emplace_back(&L, f);
         for (int k = 0; k < kSlots; ++k)
-          if ((f >> k) & 1ull) {
-            if (rc != TG_OK) L.slot_q[k]->status = rc;
-            else if ((ovf >> k) & 1ull) L.slot_q[k]->status = TG_ERANGE;
-          }
+          if ((f & ovf) >> k & 1ull) L.slot_q[k]->status = TG_ERANGE;
       }
     }
     (void)hipGetLastError();
@@ -285,6 +314,7 @@ void tg_server::run() {
         }
     }
     if (!fin.empty()) cv_done.notify_all();
+    for (const Broken &x : broken) fail_lane(*x.lane, x.status, x.err);
   }
 }
 

@@ -20,7 +20,8 @@ enum { BIG = 1 << 20 };
 static uint64_t thread_limit = (uint64_t)1 << 32; /* a launch has fewer threads than this per dimension */
 static size_t malloc_limit = (size_t)-1;          /* device allocations of this many bytes and more fail */
 static int host_mallocs_left = -1;                /* pinned allocations until one fails (-1: none does) */
-static size_t marked_copy = 0, marked_from = 0;   /* device-to-host copies of this size: bytes from .. on become 1 */
+static size_t marked_copy = 0, marked_from = 0;   /* device-to-host copies of this size: bytes from .. on become 127 */
+static int failing_syncs = 0;                     /* stream synchronisations still to fail */
 static uint64_t launches, most_threads;
 static __thread hipError_t last_error;
 
@@ -28,6 +29,7 @@ void fake_thread_limit(uint64_t n) { thread_limit = n; }
 void fake_malloc_limit(size_t n) { malloc_limit = n; }
 void fake_host_mallocs(int n) { host_mallocs_left = n; }
 void fake_mark_copies(size_t bytes, size_t from) { marked_copy = bytes, marked_from = from; }
+void fake_failing_syncs(int n) { failing_syncs = n; }
 uint64_t fake_launches(void) { return launches; }
 uint64_t fake_most_threads(void) { return most_threads; }
 
@@ -67,7 +69,7 @@ hipError_t hipHostGetDevicePointer(void **d, void *h, unsigned flags) {
 }
 hipError_t hipMemcpy(void *d, const void *s, size_t n, hipMemcpyKind k) {
   if (n <= BIG) memmove(d, s, n);
-  if (k == hipMemcpyDeviceToHost && n == marked_copy) memset((char *)d + marked_from, 1, n - marked_from);
+  if (k == hipMemcpyDeviceToHost && n == marked_copy) memset((char *)d + marked_from, 127, n - marked_from);
   return hipSuccess;
 }
 hipError_t hipMemcpyAsync(void *d, const void *s, size_t n, hipMemcpyKind k, hipStream_t st) {
@@ -159,7 +161,10 @@ static hipError_t handle(void **p) {
 }
 hipError_t hipStreamCreateWithFlags(hipStream_t *s, unsigned f) { return (void)f, handle((void **)s); }
 hipError_t hipStreamDestroy(hipStream_t s) { return free(s), hipSuccess; }
-hipError_t hipStreamSynchronize(hipStream_t s) { return (void)s, hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t s) {
+  (void)s;
+  return failing_syncs > 0 && failing_syncs-- ? fail(hipErrorUnknown) : hipSuccess;
+}
 hipError_t hipStreamQuery(hipStream_t s) { return (void)s, hipSuccess; }
 hipError_t hipStreamWaitEvent(hipStream_t s, hipEvent_t e, unsigned f) { return (void)s, (void)e, (void)f, hipSuccess; }
 hipError_t hipEventCreate(hipEvent_t *e) { return handle((void **)e); }

@@ -12,11 +12,11 @@ import paper_1312_3018_amd as tg
 HERE = os.path.dirname(os.path.abspath(__file__))
 
 PRELUDE = """
-import ctypes, sys
+import ctypes, sys, time
 import numpy as np
 fake = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)
 lib = ctypes.CDLL(sys.argv[2])
-OK, ENOMEM, ETIMEOUT, SYMMETRIC = 0, {enomem}, {etimeout}, {symmetric}
+OK, ENOMEM, EDEVICE, SYMMETRIC = 0, {enomem}, {edevice}, {symmetric}
 for f, t in (("fake_thread_limit", ctypes.c_uint64), ("fake_malloc_limit", ctypes.c_size_t)):
     getattr(fake, f).argtypes = [t]
 fake.fake_mark_copies.argtypes = [ctypes.c_size_t, ctypes.c_size_t]
@@ -73,7 +73,7 @@ def run(tmp_path_factory):
     so = str(tmp_path_factory.mktemp("fake") / "libfakehip.so")
     subprocess.run(["gcc", "-O1", "-shared", "-fPIC", "-I/opt/rocm/include", "-o", so,
                     os.path.join(HERE, "fake_hip.c")], check=True)
-    prelude = PRELUDE.format(enomem=tg.TG_ENOMEM, etimeout=tg.TG_ETIMEOUT, symmetric=tg.TG_SYMMETRIC)
+    prelude = PRELUDE.format(enomem=tg.TG_ENOMEM, edevice=tg.TG_EDEVICE, symmetric=tg.TG_SYMMETRIC)
 
     def go(script):
         r = subprocess.run([sys.executable, "-c", prelude + script, so, tg.LIB_PATH], capture_output=True, text=True,
@@ -103,4 +103,58 @@ for k in (1, 2, 64):
 check(lib.cc(P, BUF, None))
 check(lib.pagerank(P, 0.85, 2, 0, BUF, None))
 assert fake.fake_most_threads() >= n
+""")
+
+
+# ---------------------------------------------------- errors while serving
+
+# Copies of the engine's control block (its plan, 104 bytes, then the
+# frontiers' sums) are marked, so that every slot has a frontier for ever.
+SERVE = """
+n = 1 << 16
+P = path(n, 100)
+S, gid, t = vp(), i32(), ctypes.c_uint64()
+check(lib.server_create(None, ctypes.byref(S)))
+check(lib.server_add_graph(S, P, ctypes.byref(gid)))
+
+
+def submit(kind, k):
+    out = []
+    for r in range(k):
+        check(lib.server_submit(S, gid, kind, r, BUF, ctypes.byref(t)))
+        out.append(t.value)
+    return out
+
+
+def results(tickets):
+    return [lib.server_wait(S, x, 10 * 1000 * 1000, None) for x in tickets]
+"""
+
+
+def test_server_query_ends_when_its_levels_find_no_room(run):
+    """The rows for levels past a byte are made when a search gets there; with
+    no memory for them the lane's queries end with TG_ENOMEM, and later ones
+    are served."""
+    run(SERVE + """
+fake.fake_malloc_limit(n * 256)
+fake.fake_mark_copies(104 + 2 * 8 * 64 * 8, 104)
+assert results(submit(0, 3)) == [ENOMEM] * 3
+fake.fake_mark_copies(0, 0)
+assert results(submit(0, 70)) == [OK] * 70
+lib.server_destroy(S)
+""")
+
+
+@pytest.mark.parametrize("kind", [0, 1])
+def test_server_query_ends_when_a_superstep_fails(run, kind):
+    run(SERVE + f"""
+assert results(submit({kind}, 2)) == [OK] * 2
+fake.fake_mark_copies(104 + 2 * 8 * 64 * 8, 104)
+tickets = submit({kind}, 3)
+time.sleep(0.3)  # all three in slots
+fake.fake_failing_syncs(1)
+assert results(tickets) == [EDEVICE] * 3
+fake.fake_mark_copies(0, 0)
+assert results(submit({kind}, 70)) == [OK] * 70
+lib.server_destroy(S)
 """)
