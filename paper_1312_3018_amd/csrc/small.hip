@@ -2,7 +2,7 @@
 // on small graphs, one workgroup per root in one launch, and shortest paths
 // for a few roots, one launch per round for all of them.
 #include <algorithm>
-#include <vector>
+#include <memory>
 
 #include "ms.h"
 
@@ -405,20 +405,28 @@ namespace {
 
 constexpr int64_t CHUNK = 64;  // roots per launch
 
+template <typename T>
+int pinned(T **p, size_t count) {
+  if (hipHostMalloc((void **)p, count * sizeof(T), hipHostMallocDefault) == hipSuccess) return TG_OK;
+  (void)hipGetLastError();
+  *p = nullptr;
+  return set_error(TG_ENOMEM, "hipHostMalloc(%zu bytes) failed", count * sizeof(T));
+}
+
 int small_state(tg_partition *p, int64_t rows, SmallState **out) {
   if (!p->small) {
-    p->small = new (std::nothrow) SmallState();
-    if (!p->small) return set_error(TG_ENOMEM, "out of host memory");
+    // (kept only when whole)
+    std::unique_ptr<SmallState> made(new (std::nothrow) SmallState());
+    if (!made) return set_error(TG_ENOMEM, "out of host memory");
+    TG_TRY(dalloc(made->arena, &made->roots, (size_t)CHUNK));
+    TG_TRY(dalloc(made->arena, &made->info, (size_t)CHUNK));
+    TG_TRY(dalloc(made->arena, &made->flags, (size_t)(2 + 2 * LIVE)));
+    TG_TRY(pinned(&made->h_flags, (size_t)(2 + 2 * LIVE)));
+    TG_TRY(pinned(&made->h_roots, (size_t)CHUNK));
+    TG_TRY(pinned(&made->h_info, (size_t)CHUNK));
+    p->small = made.release();
   }
   SmallState &S = *p->small;
-  if (!S.roots) {
-    TG_TRY(dalloc(S.arena, &S.roots, (size_t)CHUNK));
-    TG_TRY(dalloc(S.arena, &S.info, (size_t)CHUNK));
-    TG_TRY(dalloc(S.arena, &S.flags, (size_t)(2 + 2 * LIVE)));
-    TG_HIP(hipHostMalloc((void **)&S.h_flags, (2 + 2 * LIVE) * sizeof(uint32_t), hipHostMallocDefault));
-    TG_HIP(hipHostMalloc((void **)&S.h_roots, CHUNK * sizeof(int32_t), hipHostMallocDefault));
-    TG_HIP(hipHostMalloc((void **)&S.h_info, CHUNK * sizeof(int64_t), hipHostMallocDefault));
-  }
   if (S.rows < rows) {
     if (S.state) S.arena.release_one(S.state);
     S.state = nullptr;

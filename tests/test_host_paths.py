@@ -158,3 +158,20 @@ fake.fake_mark_copies(0, 0)
 assert results(submit({kind}, 70)) == [OK] * 70
 lib.server_destroy(S)
 """)
+
+
+# --------------------------------------------------- allocations that fail
+
+@pytest.mark.parametrize("call", ["lib.bfs(P, roots(1), 1, BUF, None, None)", "lib.sssp(P, roots(1), 1, BUF, None)"])
+def test_pinned_memory_that_fails_leaves_no_half_made_scratch(run, call):
+    """The few-launch searches without their pinned memory: the call takes the
+    next route, and the one after it finds no half-made scratch."""
+    run(f"""
+for k in range(3):
+    P = path(1000, 100)
+    fake.fake_host_mallocs(k)
+    check({call})
+    fake.fake_host_mallocs(-1)
+    check({call})
+    lib.partition_free(P)
+""")
