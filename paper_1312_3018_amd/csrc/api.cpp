@@ -135,6 +135,7 @@ int Workspace::ensure(const GpuPart &g, int64_t hub_chunks_needed) {
   if (cap_n == g.n && hub_chunks_needed <= hub_chunks_cap && hubs_needed <= hubs_cap) return TG_OK;
   drop_graphs();
   ++gen;
+  cap_n = -1;  // until every buffer is there again
   arena.release();
   fd = nullptr;
   pull_part = nullptr;

@@ -19,18 +19,21 @@ enum { BIG = 1 << 20 };
 
 static uint64_t thread_limit = (uint64_t)1 << 32; /* a launch has fewer threads than this per dimension */
 static size_t malloc_limit = (size_t)-1;          /* device allocations of this many bytes and more fail */
-static int host_mallocs_left = -1;                /* pinned allocations until one fails (-1: none does) */
+static int mallocs_left = -1;                     /* device allocations until one fails (-1: none does) */
+static int host_mallocs_left = -1;                /* the same for pinned ones */
 static size_t marked_copy = 0, marked_from = 0;   /* device-to-host copies of this size: bytes from .. on become 127 */
 static int failing_syncs = 0;                     /* stream synchronisations still to fail */
-static uint64_t launches, most_threads;
+static uint64_t launches, most_threads, live_mallocs;
 static __thread hipError_t last_error;
 
 void fake_thread_limit(uint64_t n) { thread_limit = n; }
 void fake_malloc_limit(size_t n) { malloc_limit = n; }
+void fake_mallocs(int n) { mallocs_left = n; }
 void fake_host_mallocs(int n) { host_mallocs_left = n; }
 void fake_mark_copies(size_t bytes, size_t from) { marked_copy = bytes, marked_from = from; }
 void fake_failing_syncs(int n) { failing_syncs = n; }
 uint64_t fake_launches(void) { return launches; }
+uint64_t fake_live_mallocs(void) { return live_mallocs; }
 uint64_t fake_most_threads(void) { return most_threads; }
 
 static hipError_t fail(hipError_t e) {
@@ -54,8 +57,15 @@ static hipError_t unmap(void *p) {
   }
   return hipSuccess;
 }
-hipError_t hipMalloc(void **p, size_t n) { return n >= malloc_limit ? fail(hipErrorOutOfMemory) : map(p, n); }
-hipError_t hipFree(void *p) { return unmap(p); }
+hipError_t hipMalloc(void **p, size_t n) {
+  if (n >= malloc_limit || (mallocs_left >= 0 && mallocs_left-- == 0)) return fail(hipErrorOutOfMemory);
+  ++live_mallocs;
+  return map(p, n);
+}
+hipError_t hipFree(void *p) {
+  if (p) --live_mallocs;
+  return unmap(p);
+}
 hipError_t hipHostMalloc(void **p, size_t n, unsigned flags) {
   (void)flags;
   if (host_mallocs_left >= 0 && host_mallocs_left-- == 0) return fail(hipErrorOutOfMemory);

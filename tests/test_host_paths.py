@@ -175,3 +175,24 @@ for k in range(3):
     check({call})
     lib.partition_free(P)
 """)
+
+
+def test_workspace_that_failed_to_grow_is_made_again(run):
+    """A retuned partition needs more room for hubs; wherever that fails, the
+    next call must not take the buffers given back."""
+    run("""
+lib.partition_retune.argtypes = [vp, ctypes.c_char_p]
+failed = 0
+for k in range(24):
+    P = path(1000, 1000)
+    check(lib.cc(P, BUF, None))
+    full = fake.fake_live_mallocs()
+    check(lib.partition_retune(P, b'{"hub_min_deg": 2, "block_min_deg": 2, "wave_min_deg": 2, "g16_min_deg": 2, "g4_min_deg": 2}'))
+    fake.fake_mallocs(k)
+    failed += lib.cc(P, BUF, None) == ENOMEM
+    fake.fake_mallocs(-1)
+    check(lib.cc(P, BUF, None))
+    assert fake.fake_live_mallocs() == full, k
+    lib.partition_free(P)
+assert failed > 15
+""")
