@@ -26,6 +26,9 @@ DEFAULTS = {
     "pr_rows": 512, "bfs_do": 1, "bfs_alpha": 14, "bfs_beta": 24, "sssp_xcd": 0,
     "bfs_lanes": 2, "bfs_td_grid": 1024, "bfs_bu_grid": 4096, "sssp_lanes": 4, "sssp_pull": 0, "sssp_packed": 1, "sssp_ring": 1, "sssp_split": 1, "sssp_hpull": 100,
     "bfs_graph": 0,
+    # not searched: which calls run in the shared schedules is left to the
+    # library's rules (named here, as the other keys alone would refuse them)
+    "bfs_batch_roots": -1, "sssp_batch_roots": -1,
 }
 
 SPACE = {

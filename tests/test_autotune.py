@@ -82,6 +82,24 @@ def test_search_keeps_only_gains_beyond_the_margin():
             assert autotune.FAMILY[changed[0]] == fam
 
 
+def test_tuned_config_leaves_the_routes_to_the_rules():
+    """A tuning that names bfs_ or sssp_ keys and no *_batch_roots asks for the
+    single searches; the tuned config must not: it names both, by rule unless
+    the start says otherwise, and the ones measured run single searches."""
+    f, _ = _cost({})
+    cfg = autotune.tune(None, [], None, start={}, measure_fn=f)["config"]
+    assert cfg["bfs_batch_roots"] == -1 and cfg["sssp_batch_roots"] == -1
+    cfg = autotune.tune(None, [], None, start={"bfs_batch_roots": 8}, measure_fn=f)["config"]
+    assert cfg["bfs_batch_roots"] == 8 and cfg["sssp_batch_roots"] == -1
+
+
+def test_measured_configs_run_single_searches(monkeypatch):
+    seen = []
+    monkeypatch.setattr(autotune, "partition_retune", lambda part, cfg: seen.append(cfg))
+    autotune.measure(None, autotune.DEFAULTS, [], None, 1, "none", (None,) * 3)
+    assert seen[0]["bfs_batch_roots"] == 0 and seen[0]["sssp_batch_roots"] == 0
+
+
 def test_search_skips_invalid_candidates():
     f, seen = _cost({})
     start = {"hub_min_deg": 8192, "block_min_deg": 4096}
