@@ -162,9 +162,13 @@ int partition_by_degree(const tg_graph *g, int strategy, double cpu_edge_share,
  *                GPU and kernels read them over the host link, for graphs
  *                beyond device memory; honoured by partition_by_degree only,
  *                and it keeps the per-XCD class layouts off);
- *   PageRank     "pr_xcd" (per-XCD source classes), "pr_rows" (256 or 512
- *                edges per row block), "pr_lds_verts" (hot-table entries,
- *                <= 40960), "pr_grid" (workgroups).
+ *   PageRank     "pr_xcd" (1: sliced columns of the in-edges; 0: row blocks,
+ *                as hybrid partitions and mapped edges have them), "pr_whole"
+ *                (how the sliced columns are walked: 0: by per-XCD source
+ *                classes, 1: whole, -1, the default: whole up to 12 * 2^20
+ *                edges), "pr_rows" (256 or 512 edges per row block),
+ *                "pr_lds_verts" (hot-table entries of the classes and the row
+ *                blocks, <= 40960), "pr_grid" (workgroups).
  * Results do not depend on the tuning.  Waits for the device to be idle
  * first.  Errors: TG_EINVAL (bad tuning), TG_ENOMEM, TG_EDEVICE. */
 int partition_retune(tg_partition *p, const char *tuning_json);

@@ -336,7 +336,7 @@ Tuning default_tuning() {
   t.bfs_graph = 0;  // replaying captured chunks measured 1-2% slower than direct launches
   t.mapped_edges = 0;
   t.bfs_batch_roots = t.sssp_batch_roots = -1;
-  t.pr_auto = true;
+  t.pr_whole = -1;
   return t;
 }
 
@@ -390,7 +390,8 @@ int parse_tuning(const char *json, Tuning *t) {
   if (json_int(json, "mapped_edges", &v)) t->mapped_edges = v;
   if (strstr(json, "\"bfs_")) t->bfs_batch_roots = 0;
   if (strstr(json, "\"sssp_")) t->sssp_batch_roots = 0;
-  if (strstr(json, "\"pr_")) t->pr_auto = false;
+  if (json_int(json, "pr_whole", &v)) t->pr_whole = v;
+  if (t->pr_whole < -1 || t->pr_whole > 1) return set_error(TG_EINVAL, "tuning: pr_whole must be -1, 0 or 1");
   if (json_int(json, "bfs_batch_roots", &v)) t->bfs_batch_roots = v;
   if (json_int(json, "sssp_batch_roots", &v)) t->sssp_batch_roots = v;
   if (t->bfs_batch_roots < -1 || t->sssp_batch_roots < -1)
@@ -1019,7 +1020,7 @@ extern "C" int partition_info(const tg_partition *p, char *json, size_t cap) {
            "\"sssp_delta\":%lld,\"sssp_lds_verts\":%lld,\"sssp_grid\":%lld,\"pr_xcd\":%lld,\"pr_rows\":%lld,"
            "\"bfs_do\":%lld,\"bfs_alpha\":%lld,\"bfs_beta\":%lld,\"sssp_xcd\":%lld,\"bfs_lanes\":%lld,"
            "\"bfs_td_grid\":%lld,\"bfs_bu_grid\":%lld,\"sssp_pull\":%lld,\"sssp_lanes\":%lld,\"bfs_graph\":%lld,\"mapped_edges\":%lld,\"sssp_packed\":%lld,\"sssp_ring\":%lld,\"sssp_split\":%lld,\"sssp_hpull\":%lld,"
-           "\"bfs_batch_roots\":%lld,\"sssp_batch_roots\":%lld}",
+           "\"bfs_batch_roots\":%lld,\"sssp_batch_roots\":%lld,\"pr_whole\":%lld}",
            (long long)p->tune.min_deg[0], (long long)p->tune.min_deg[1], (long long)p->tune.min_deg[2],
            (long long)p->tune.min_deg[3], (long long)p->tune.min_deg[4], (long long)p->tune.hub_chunk,
            (long long)p->tune.pr_lds_verts, (long long)p->tune.pr_grid, (long long)p->tune.bfs_lds_words,
@@ -1030,7 +1031,7 @@ extern "C" int partition_info(const tg_partition *p, char *json, size_t cap) {
            (long long)p->tune.bfs_td_grid, (long long)p->tune.bfs_bu_grid, (long long)p->tune.sssp_pull,
            (long long)p->tune.sssp_lanes, (long long)p->tune.bfs_graph, (long long)p->tune.mapped_edges,
            (long long)p->tune.sssp_packed, (long long)p->tune.sssp_ring, (long long)p->tune.sssp_split, (long long)p->tune.sssp_hpull,
-           (long long)p->tune.bfs_batch_roots, (long long)p->tune.sssp_batch_roots);
+           (long long)p->tune.bfs_batch_roots, (long long)p->tune.sssp_batch_roots, (long long)p->tune.pr_whole);
   s += buf;
   s += ",\"tuning_source\":\"" + p->tuning_source + "\"";
   s += hybrid_info_json(p);

@@ -696,11 +696,13 @@ void pr_slices_free(GpuPart &g) {
 
 namespace {
 
-// Small graphs are walked whole: the contribution vector is in every L2 and
-// launches are what counts; past this the eight copies of the vector no longer
-// fit the L2s beside the edges.  (us per iteration, whole / classes, R-MAT of
-// 2^16, 2^17, 2^18, 2^19, 2^20 vertices: 13/46, 23/44, 40/52, 68/59, 175/68;
-// uniform of 2^18 and 2^20, 2 and 8 M edges: 17/48, 52/71)
+// Small graphs are walked whole (unless "pr_whole" says otherwise): the
+// contribution vector is in every L2 and launches are what counts; past this
+// the eight copies of the vector no longer fit the L2s beside the edges.  (us
+// per iteration, whole / classes, symmetric R-MAT of 2^12, 2^14, 2^16, 2^18,
+// 2^19, 2^20 vertices: 9/18, 11/23, 12/28, 40/46, 68/59, 175/67; directed 2^14,
+// 2^16, 2^18: 9/19, 12/21, 24/37; uniform of 2^18 and 2^20, 2 and 8 M edges:
+// 17/48, 52/71)
 constexpr int64_t WHOLE_MAX_EDGES = (int64_t)12 << 20;
 
 template <typename T>
@@ -723,7 +725,7 @@ int build_slices(tg_partition *p, hipStream_t s) {
   GpuPart &g = p->gpu;
   const Tuning &t = p->tune;
   const int64_t n = g.n, m = g.in.m;
-  const bool cls = !(t.pr_auto && m <= WHOLE_MAX_EDGES);
+  const bool cls = t.pr_whole < 0 ? m > WHOLE_MAX_EDGES : t.pr_whole == 0;
   const int32_t lines = cls ? table_lines(t, n) : 0;
   const int32_t grid = (int32_t)(cls ? std::max<int64_t>(t.pr_grid / NS, 1) * NS : t.pr_grid);
   if (g.slices && g.slices->built && g.slices->classes == cls && g.slices->lines == lines && g.slices->grid == grid)

@@ -103,7 +103,7 @@ struct Tuning {
   // (-1: by the graph's size, 0: never; a tuning that names any other key of
   // the algorithm asks for that schedule, so there the default is 0)
   int64_t bfs_batch_roots, sssp_batch_roots;
-  bool pr_auto;  // PageRank: no key of it was given (small graphs may be walked whole)
+  int64_t pr_whole;  // PageRank sliced columns: 1 = rows walked whole, 0 = by source class, -1 = by the graph's size
 };
 Tuning default_tuning();
 int parse_tuning(const char *json, Tuning *t);

@@ -442,6 +442,61 @@ def test_pagerank_rows_of_one_class(gpu):
         check_pagerank(gpu, g, tuning)
 
 
+# The classes on graphs that are walked whole unless "pr_whole" says otherwise.
+PR_CLASSES = [{"pr_whole": 0}, {"pr_whole": 0, "pr_lds_verts": 0}, {"pr_whole": 0, "pr_lds_verts": 32},
+              {"pr_whole": 0, "pr_grid": 8}]
+
+
+def pagerank_kernels(tg, P):
+    tg.tg_set_timing(True)
+    try:
+        tg.pagerank(P, iterations=2)
+        return {k for k in tg.tg_last_stats() if k.endswith("_n")}
+    finally:
+        tg.tg_set_timing(False)
+
+
+def test_small_graphs_are_walked_whole_whatever_else_is_tuned(gpu):
+    """Naming a key of the classes does not cost a small graph its one launch
+    an iteration; "pr_whole" chooses."""
+    g = graphgen.rmat(10)
+    for tuning in PR_TUNINGS:
+        assert pagerank_kernels(gpu, load(gpu, g, tuning=tuning)) == {"pr_gather_n"}, tuning
+    assert pagerank_kernels(gpu, load(gpu, g, tuning={"pr_whole": 0})) == {"pr_slice_gather_n", "pr_combine_n"}
+    assert pagerank_kernels(gpu, load(gpu, g, tuning={"pr_whole": 1, "pr_grid": 8})) == {"pr_gather_n"}
+    with pytest.raises(gpu.TGError):
+        load(gpu, g, tuning={"pr_whole": 2})
+
+
+@pytest.mark.parametrize("n", [1, 2, 63, 64, 65, 255, 257, 511, 512, 513, 1025, 30011])
+@pytest.mark.parametrize("sym", [True, False])
+def test_pagerank_classes_of_ragged_sizes(gpu, monkeypatch, n, sym):
+    monkeypatch.setitem(globals(), "PR_TUNINGS", PR_CLASSES)
+    test_pagerank_slices_of_ragged_sizes(gpu, n, sym)
+
+
+@pytest.mark.parametrize("around", [32, 128, 1024, 2048, 9 * 1024])
+@pytest.mark.parametrize("sym", [True, False])
+def test_pagerank_class_rows_around_each_split(gpu, monkeypatch, around, sym):
+    monkeypatch.setitem(globals(), "PR_TUNINGS", PR_CLASSES)
+    test_pagerank_rows_around_each_split(gpu, around, sym)
+
+
+def test_pagerank_classes_left_empty(gpu, monkeypatch):
+    monkeypatch.setitem(globals(), "PR_TUNINGS", PR_CLASSES)
+    test_pagerank_rows_of_one_class(gpu)
+
+
+@pytest.mark.parametrize("lds", [0, 100, 40960])
+def test_pagerank_class_variants(gpu, lds):
+    """R-MAT hubs past a piece in every class, and runs that agree to the bit."""
+    for g in (graphgen.rmat(14), graphgen.rmat(12, symmetrize=False)):
+        check_pagerank(gpu, g, {"pr_whole": 0, "pr_lds_verts": lds, "pr_grid": 64}, iters=10)
+        P = load(gpu, g, tuning={"pr_whole": 0, "pr_lds_verts": lds, "pr_grid": 64})
+        a, b = (gpu.pagerank(P, iterations=10).cpu().numpy() for _ in range(2))
+        assert np.array_equal(a, b)
+
+
 # -------------------------- SSSP by buckets for several roots at once
 
 BUCKETS = {"sssp_batch_roots": 1 << 20}  # never the engine: the bucket schedule
