@@ -355,8 +355,18 @@ const char *tg_last_error(void);
  * the terminator) or a negative tg_status. */
 int partition_info(const tg_partition *p, char *json, size_t cap);
 
-/* JSON statistics of the last algorithm call on this thread: supersteps,
- * edges scanned or relaxations, and on hybrid partitions per-phase
+/* JSON statistics of the last algorithm call on this thread.  Always
+ * supersteps (those that several searches share counted once).  BFS:
+ * edges_scanned and vertices_expanded (top-down, the out-edges of the vertices
+ * expanded and those of them that have any, summed over the searches),
+ * bottom_up_edges_checked, bottom_up_vertices_examined and bottom_up_steps
+ * (in-edges looked at, vertices that looked, supersteps; once for all the
+ * searches of a 64-slot engine) and lanes (searches in flight together).
+ * SSSP: relaxations and activations (edges relaxed, vertices they went out
+ * from, summed over the searches), heavy_pull_edges_checked and
+ * heavy_pull_vertices (a bucket's heavy edges pulled), pull_supersteps, lanes,
+ * and from a 64-slot engine edges_read (once for all its searches).  CC:
+ * edges_pushed.  On hybrid partitions per-phase
  * milliseconds (gpu_ms: the GPU's kernels; cpu_ms: the host threads;
  * exchange_ms: the copies of both directions on their copy streams), bytes
  * exchanged (exchange_bytes, of which exchange_h2d_bytes host-to-GPU) and

@@ -1136,6 +1136,36 @@ bool bc_in_chain(const tg_partition *p, int32_t ns) { return ns >= 2 + (p->gpu.n
 
 }  // namespace
 
+namespace {
+
+void emit_bfs(int64_t roots, int64_t supersteps, const SearchWork &w) {
+  stats_add("roots", (double)roots);
+  stats_add("supersteps", (double)supersteps);
+  stats_add("edges_scanned", w.edges);
+  stats_add("vertices_expanded", w.vertices);
+  stats_add("bottom_up_edges_checked", w.checked);
+  stats_add("bottom_up_steps", w.steps);
+  stats_add("bottom_up_vertices_examined", w.examined);
+  stats_add("lanes", w.lanes);
+  ktimer_emit();
+}
+
+void emit_sssp(int64_t roots, int64_t supersteps, const SearchWork &w) {
+  stats_add("relaxations", w.edges);
+  stats_add("activations", w.vertices);
+  // (buckets of light and heavy edges are the single searches' and bucket_sssp's)
+  stats_add("heavy_pull_edges_checked", 0.0);
+  stats_add("heavy_pull_vertices", 0.0);
+  if (w.read > 0.0) stats_add("edges_read", w.read);
+  stats_add("lanes", w.lanes);
+  stats_add("roots", (double)roots);
+  stats_add("supersteps", (double)supersteps);
+  stats_add("pull_supersteps", w.pulls);
+  ktimer_emit();
+}
+
+}  // namespace
+
 extern "C" int bfs(const tg_partition *pc, const int32_t *roots, int32_t num_roots, int32_t *levels,
                    int32_t *parents, void *stream) {
   clear_error();
@@ -1149,26 +1179,24 @@ extern "C" int bfs(const tg_partition *pc, const int32_t *roots, int32_t num_roo
   int64_t supersteps = 0;
   if (bfs_in_workgroups(p, num_roots)) {
     bool deep = false;
-    const int rc = small_bfs(p, roots, num_roots, levels, parents, s, &supersteps, &deep);
+    SearchWork w;
+    const int rc = small_bfs(p, roots, num_roots, levels, parents, s, &supersteps, &w, &deep);
     if (rc != TG_OK && rc != TG_ENOMEM) return rc;
     if (rc == TG_ENOMEM) {
       small_free(p);
       clear_error();
     } else if (!deep) {
-      stats_add("roots", num_roots);
-      stats_add("supersteps", (double)supersteps);
-      ktimer_emit();
+      emit_bfs(num_roots, supersteps, w);
       return TG_OK;
     }
     supersteps = 0;
   }
   if (!parents && bfs_in_engine(p, num_roots)) {
-    const int rc = slots_run_batch(p, kSlotBfs, roots, num_roots, levels, s, &supersteps);
+    SearchWork w;
+    const int rc = slots_run_batch(p, kSlotBfs, roots, num_roots, levels, s, &supersteps, &w);
     if (rc == TG_OK) {
       TG_HIP(hipStreamSynchronize(s));
-      stats_add("roots", num_roots);
-      stats_add("supersteps", (double)supersteps);
-      ktimer_emit();
+      emit_bfs(num_roots, supersteps, w);
     }
     // no room for the engine's rows: the single searches need less
     if (rc != TG_ENOMEM) return rc;
@@ -1186,18 +1214,16 @@ extern "C" int bfs(const tg_partition *pc, const int32_t *roots, int32_t num_roo
   for (int l = 0; l < nl; ++l)
     for (int k = 0; k < 6; ++k) TG_TRY(stat_fetch(*lanes[l], k, s));
   TG_HIP(hipStreamSynchronize(s));
-  double sums[6] = {0, 0, 0, 0, 0, 0};
-  for (int l = 0; l < nl; ++l)
-    for (int k = 0; k < 6; ++k) sums[k] += (double)stat_sum(*lanes[l], k);
-  stats_add("roots", num_roots);
-  stats_add("supersteps", (double)supersteps);
-  stats_add("edges_scanned", sums[0]);
-  stats_add("vertices_expanded", sums[1]);
-  stats_add("bottom_up_edges_checked", sums[2]);
-  stats_add("bottom_up_steps", sums[3]);
-  stats_add("bottom_up_vertices_examined", sums[5]);
-  stats_add("lanes", nl);
-  ktimer_emit();
+  SearchWork w;
+  for (int l = 0; l < nl; ++l) {
+    w.edges += (double)stat_sum(*lanes[l], 0);
+    w.vertices += (double)stat_sum(*lanes[l], 1);
+    w.checked += (double)stat_sum(*lanes[l], 2);
+    w.steps += (double)stat_sum(*lanes[l], 3);
+    w.examined += (double)stat_sum(*lanes[l], 5);
+  }
+  w.lanes = nl;
+  emit_bfs(num_roots, supersteps, w);
   return TG_OK;
 }
 
@@ -1214,27 +1240,21 @@ extern "C" int sssp(const tg_partition *pc, const int32_t *roots, int32_t num_ro
   if (p->alpha > 0.0) return hybrid_sssp(p, roots, num_roots, dist, s);
   int64_t rounds_total = 0, pulls_total = 0;
   if (sssp_in_rounds(p, num_roots)) {
-    const int rc = round_sssp(p, roots, num_roots, dist, s, &rounds_total);
-    if (rc == TG_OK) {
-      stats_add("roots", num_roots);
-      stats_add("supersteps", (double)rounds_total);
-      stats_add("pull_supersteps", 0.0);
-      ktimer_emit();
-    }
+    SearchWork w;
+    const int rc = round_sssp(p, roots, num_roots, dist, s, &rounds_total, &w);
+    if (rc == TG_OK) emit_sssp(num_roots, rounds_total, w);
     if (rc != TG_ENOMEM) return rc;
     small_free(p);
     clear_error();
     rounds_total = 0;
   }
   if (sssp_in_engine(p, num_roots)) {
-    const int rc = slots_run_batch(p, kSlotSssp, roots, num_roots, dist, s, &rounds_total);
+    SearchWork w;
+    const int rc = slots_run_batch(p, kSlotSssp, roots, num_roots, dist, s, &rounds_total, &w);
     if (rc == TG_ERANGE) return set_error(rc, "sssp: a shortest-path distance does not fit below INT32_MAX");
     if (rc == TG_OK) {
       TG_HIP(hipStreamSynchronize(s));
-      stats_add("roots", num_roots);
-      stats_add("supersteps", (double)rounds_total);
-      stats_add("pull_supersteps", 0.0);
-      ktimer_emit();
+      emit_sssp(num_roots, rounds_total, w);
     }
     // no room for the engine's rows: the single searches need less
     if (rc != TG_ENOMEM) return rc;
@@ -1355,11 +1375,10 @@ extern "C" int bfs_batched(const tg_partition *pc, const int32_t *roots, int32_t
   stats_reset("bfs_batched");
   ktimer_reset();
   int64_t steps = 0;
-  TG_TRY(slots_run_batch(p, kSlotBfs, roots, num_roots, levels, s, &steps));
+  SearchWork w;
+  TG_TRY(slots_run_batch(p, kSlotBfs, roots, num_roots, levels, s, &steps, &w));
   TG_HIP(hipStreamSynchronize(s));
-  stats_add("roots", num_roots);
-  stats_add("supersteps", (double)steps);
-  ktimer_emit();
+  emit_bfs(num_roots, steps, w);
   return TG_OK;
 }
 
@@ -1375,11 +1394,10 @@ extern "C" int sssp_batched(const tg_partition *pc, const int32_t *roots, int32_
   stats_reset("sssp_batched");
   ktimer_reset();
   int64_t steps = 0;
-  TG_TRY(slots_run_batch(p, kSlotSssp, roots, num_roots, dist, s, &steps));
+  SearchWork w;
+  TG_TRY(slots_run_batch(p, kSlotSssp, roots, num_roots, dist, s, &steps, &w));
   TG_HIP(hipStreamSynchronize(s));
-  stats_add("roots", num_roots);
-  stats_add("supersteps", (double)steps);
-  ktimer_emit();
+  emit_sssp(num_roots, steps, w);
   return TG_OK;
 }
 

@@ -673,6 +673,7 @@ int bucket_sssp(tg_partition *p, const int32_t *roots_local, int32_t nr, int32_t
     for (int i = 0; i < STAT_SLOTS; ++i) sum += S->h_work[(size_t)c * STAT_SPAN + (size_t)i * STAT_STRIDE];
     stats_add(names[c], (double)sum);
   }
+  stats_add("lanes", cap < nr ? cap : nr);
   return TG_OK;
 }
 

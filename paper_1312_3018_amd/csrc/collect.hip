@@ -60,7 +60,7 @@ __global__ __launch_bounds__(BLOCK) void k_collect_f64_f32(const int32_t *__rest
 // as its parent and reads no row: those are the rows that hold one match in
 // no particular place.  RMAT-14, one root: 434 us with one thread per vertex
 // (a hub's row was one lane's serial walk), 13 us so.
-__global__ __launch_bounds__(BLOCK) void k_parents(const int32_t *__restrict__ g_of_l, int64_t n,
+__global__ __launch_bounds__(BLOCK) void k_parents(const int32_t *__restrict__ g_of_l, int64_t v0, int64_t n,
                                                    const int64_t *__restrict__ in_off,
                                                    const int32_t *__restrict__ in_col,
                                                    const uint32_t *__restrict__ visited,
@@ -70,51 +70,47 @@ __global__ __launch_bounds__(BLOCK) void k_parents(const int32_t *__restrict__ g
   // (without bits, unvisited vertices have level TG_INF)
   const auto seen = [&](int64_t u) { return visited ? ((visited[u >> 5] >> (u & 31)) & 1u) != 0u : level[u] != TG_INF; };
   const auto at = [&](int32_t u, int32_t want) { return (!visited || seen(u)) && level[u] == want; };
-  // (four threads a vertex would wrap a launch's 32-bit count from 2^30 vertices on)
-  const int64_t waves = ((int64_t)gridDim.x * BLOCK) >> 6;
-  for (int64_t w16 = ((int64_t)blockIdx.x * BLOCK + threadIdx.x) >> 6; w16 * 16 < n; w16 += waves) {
-    const int64_t v = w16 * 16 + (lane >> 2);
-    int32_t best = -1, want = 0;
-    int64_t e0 = 0, e1 = 0;
-    bool open = false;
-    if (v < n && seen(v)) {
-      want = level[v] - 1;
-      if (want <= 0) {
-        best = root;
-      } else {
-        e0 = in_off[v];
-        e1 = in_off[v + 1];
-        open = true;
-      }
+  const int64_t v = v0 + (((int64_t)blockIdx.x * BLOCK + threadIdx.x) >> 6) * 16 + (lane >> 2);
+  int32_t best = -1, want = 0;
+  int64_t e0 = 0, e1 = 0;
+  bool open = false;
+  if (v < n && seen(v)) {
+    want = level[v] - 1;
+    if (want <= 0) {
+      best = root;
+    } else {
+      e0 = in_off[v];
+      e1 = in_off[v + 1];
+      open = true;
     }
-    int32_t u = -1;
-    if (open && e0 + sub < e1) u = in_col[e0 + sub];
-    const uint64_t hits = __ballot(u >= 0 && at(u, want));
-    const uint32_t mine = (uint32_t)(hits >> (lane & ~3)) & 15u;
-    const int32_t first = __shfl(u, (lane & ~3) + (mine ? __ffs(mine) - 1 : 0), 64);
-    if (open && mine) {
-      best = first;
-      open = false;
-    }
-    for (uint64_t todo = __ballot(open && sub == 0); todo; todo &= todo - 1) {
-      const int src = __ffsll((long long)todo) - 1;
-      const int64_t a0 = __shfl((long long)e0, src, 64) + 4, a1 = __shfl((long long)e1, src, 64);
-      const int32_t w = __shfl(want, src, 64);
-      int32_t found = -1;
-      for (int64_t e = a0; e < a1; e += 128) {
-        const int64_t i0 = e + lane, i1 = i0 + 64;
-        const int32_t u0 = i0 < a1 ? in_col[i0] : -1, u1 = i1 < a1 ? in_col[i1] : -1;
-        const bool h0 = u0 >= 0 && at(u0, w), h1 = u1 >= 0 && at(u1, w);
-        const uint64_t m0 = __ballot(h0), m1 = __ballot(h1);
-        if (m0 | m1) {
-          found = m0 ? __shfl(u0, __ffsll((long long)m0) - 1, 64) : __shfl(u1, __ffsll((long long)m1) - 1, 64);
-          break;
-        }
-      }
-      if ((lane & ~3) == src) best = found;
-    }
-    if (v < n && sub == 0) out[g_of_l[v]] = best < 0 ? -1 : g_of_l[best];
   }
+  int32_t u = -1;
+  if (open && e0 + sub < e1) u = in_col[e0 + sub];
+  const uint64_t hits = __ballot(u >= 0 && at(u, want));
+  const uint32_t mine = (uint32_t)(hits >> (lane & ~3)) & 15u;
+  const int32_t first = __shfl(u, (lane & ~3) + (mine ? __ffs(mine) - 1 : 0), 64);
+  if (open && mine) {
+    best = first;
+    open = false;
+  }
+  for (uint64_t todo = __ballot(open && sub == 0); todo; todo &= todo - 1) {
+    const int src = __ffsll((long long)todo) - 1;
+    const int64_t a0 = __shfl((long long)e0, src, 64) + 4, a1 = __shfl((long long)e1, src, 64);
+    const int32_t w = __shfl(want, src, 64);
+    int32_t found = -1;
+    for (int64_t e = a0; e < a1; e += 128) {
+      const int64_t i0 = e + lane, i1 = i0 + 64;
+      const int32_t u0 = i0 < a1 ? in_col[i0] : -1, u1 = i1 < a1 ? in_col[i1] : -1;
+      const bool h0 = u0 >= 0 && at(u0, w), h1 = u1 >= 0 && at(u1, w);
+      const uint64_t m0 = __ballot(h0), m1 = __ballot(h1);
+      if (m0 | m1) {
+        found = m0 ? __shfl(u0, __ffsll((long long)m0) - 1, 64) : __shfl(u1, __ffsll((long long)m1) - 1, 64);
+        break;
+      }
+    }
+    if ((lane & ~3) == src) best = found;
+  }
+  if (v < n && sub == 0) out[g_of_l[v]] = best < 0 ? -1 : g_of_l[best];
 }
 
 }  // namespace
@@ -170,9 +166,11 @@ int collect_f64_to_f32(const GpuPart &g, const double *state, float *out, hipStr
 int bfs_parents(const GpuPart &g, const uint32_t *visited, const int32_t *level, int32_t root_local,
                 int32_t *out, hipStream_t s) {
   if (g.n <= 0) return TG_OK;
-  const int64_t blocks = std::min<int64_t>((g.n + BLOCK / 4 - 1) / (BLOCK / 4), 32768);
-  hipLaunchKernelGGL(k_parents, dim3((unsigned)blocks), dim3(BLOCK), 0, s, g.g_of_l, g.n, g.in.off, g.in.col, visited,
-                     level, root_local, out);
+  // four threads a vertex would wrap a launch's 32-bit count from 2^30 on
+  constexpr int64_t CHUNK = 1 << 22;
+  for (int64_t v0 = 0; v0 < g.n; v0 += CHUNK)
+    hipLaunchKernelGGL(k_parents, dim3((unsigned)((std::min(g.n - v0, CHUNK) + BLOCK / 4 - 1) / (BLOCK / 4))), dim3(BLOCK),
+                       0, s, g.g_of_l, v0, g.n, g.in.off, g.in.col, visited, level, root_local, out);
   TG_HIP(hipGetLastError());
   return TG_OK;
 }

@@ -188,6 +188,18 @@ __device__ __forceinline__ T wave_sum(T x) {
   return x;
 }
 
+// Sum over the wave in its vector registers, wave-uniform (all lanes active):
+// rows of 16 lanes by shifts, then the rows by broadcasts of their last lanes.
+__device__ __forceinline__ uint32_t wave_total(uint32_t x) {
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xf, 0xf, false);
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xf, 0xf, false);
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xf, 0xf, false);
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xf, 0xf, false);
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xa, 0xf, false);
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xc, 0xf, false);
+  return (uint32_t)__builtin_amdgcn_readlane((int)x, 63);
+}
+
 // Per-call counters that every block of a large grid adds to.  Atomics from
 // thousands of blocks on one address serialize (device-scope atomics are
 // resolved beyond the L2): a counter is STAT_SLOTS slots on separate

@@ -30,6 +30,10 @@ struct MsState {
   // other.
   u64 mf[2][MF_COPIES][kSlots];
 };
+// Counters of a workspace's `work`.  BFS: (vertex, slot) pairs pushed and their
+// edges; in-edges the pulls looked at and vertices that looked, each once for
+// all slots.  SSSP: (vertex, slot) pairs of the frontiers and their edges.
+enum { MS_PAIRS = 0, MS_EDGES = 1, MS_CHECKED = 2, MS_EXAMINED = 3, MS_COUNTERS = 4 };
 
 // Slots of `alive` to pull: mf, the edges of the slot's frontier, against mu,
 // those of the vertices it has not had on a frontier yet.
@@ -43,8 +47,8 @@ int ms_expand(const GpuPart &g, Workspace &ws, const Tuning &t, const Plan &hp, 
 // them: a symmetric graph's rows of 512 edges and more) into next and (unless
 // null) the bitmap `touched`, several waves a row.
 int64_t hub_rows(const GpuPart &g);
-int ms_pull_hubs(const GpuPart &g, uint32_t *touched, const u64 *front, const u64 *visited, u64 *next, u64 pulled,
-                 hipStream_t s);
+int ms_pull_hubs(const GpuPart &g, Workspace &ws, uint32_t *touched, const u64 *front, const u64 *visited, u64 *next,
+                 u64 pulled, hipStream_t s);
 
 }  // namespace tg
 
@@ -300,12 +304,14 @@ __device__ __forceinline__ void for_row_spans(const RowSpans &R, int64_t wave, i
 }
 
 // OR of the frontier masks of in-neighbours [b, a1) in tiles of 256 edges,
-// every `step`-th edge position a tile's first, until all of w is found.
+// every `step`-th edge position a tile's first, until all of w is found; the
+// edges looked at are added to `checked` (wave-uniform).
 __device__ __forceinline__ u64 pull_tiles(const int32_t *__restrict__ icol, const u64 *__restrict__ front, int64_t b,
-                                          int64_t a1, int64_t step, u64 w) {
+                                          int64_t a1, int64_t step, u64 w, u64 &checked) {
   const int lane = threadIdx.x & 63;
   u64 got = 0;
   for (; b < a1 && (w & ~got); b += step) {
+    checked += (u64)(a1 - b < 256 ? a1 - b : 256);
     u64 x[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
@@ -325,13 +331,15 @@ __device__ __forceinline__ u64 pull_tiles(const int32_t *__restrict__ icol, cons
 // on v's in-neighbours: the first four from the head array, sixteen more
 // from the row, then the rows still open by the whole wave.  Rows are sorted
 // by decreasing degree, so the hubs that most slots have just reached come
-// first and most rows close within the head.
+// first and most rows close within the head.  The edges looked at are added
+// to `checked` (wave-uniform; all lanes active).
 template <typename OffT>
 __device__ __forceinline__ u64 pull_vertices(const OffT *__restrict__ ioff, const int32_t *__restrict__ icol,
                                              const int4 *__restrict__ head, const u64 *__restrict__ front, int64_t v,
-                                             u64 want) {
+                                             u64 want, u64 &checked) {
   u64 acc = 0;
   int64_t e = 0, e1 = 0;
+  uint32_t seen = 0;
   if (want) {
     const int4 h = head[v];
     const int32_t hu[4] = {h.x, h.y, h.z, h.w};
@@ -339,6 +347,8 @@ __device__ __forceinline__ u64 pull_vertices(const OffT *__restrict__ ioff, cons
 #pragma unroll
     for (int k = 0; k < 4; ++k) x[k] = hu[k] >= 0 ? front[hu[k]] : 0ull;
     acc = (x[0] | x[1]) | (x[2] | x[3]);
+    // (ids of a short row end in -1)
+    seen = 4u - ((uint32_t)h.x >> 31) - ((uint32_t)h.y >> 31) - ((uint32_t)h.z >> 31) - ((uint32_t)h.w >> 31);
     if ((want & ~acc) && h.w >= 0) {
       e = (int64_t)ioff[v] + 4;
       e1 = (int64_t)ioff[v + 1];
@@ -347,11 +357,13 @@ __device__ __forceinline__ u64 pull_vertices(const OffT *__restrict__ ioff, cons
         for (int k = 0; k < 4; ++k) x[k] = front[icol[e + k < e1 ? e + k : e1 - 1]];
         acc |= (x[0] | x[1]) | (x[2] | x[3]);
       }
+      seen = (uint32_t)(min(e, e1) - (int64_t)ioff[v]);
     }
   }
+  checked += (u64)wave_total(seen);
   for (u64 todo = __ballot(e < e1 && (want & ~acc) != 0ull); todo; todo &= todo - 1) {
     const int src = __ffsll((long long)todo) - 1;
-    const u64 got = pull_tiles(icol, front, lane_i64(e, src), lane_i64(e1, src), 256, lane_mask(want & ~acc, src));
+    const u64 got = pull_tiles(icol, front, lane_i64(e, src), lane_i64(e1, src), 256, lane_mask(want & ~acc, src), checked);
     if ((int)(threadIdx.x & 63) == src) acc |= got;
   }
   return acc & want;

@@ -37,7 +37,7 @@ struct SlotEngine {
   // SSSP overflow: per vertex, the slots whose candidate for it did not fit
   // in int32; ovf_slots[0] = the slots with any such mark, [1] = scratch
   unsigned long long *ovf = nullptr, *ovf_slots = nullptr;
-  unsigned long long *h_ovf = nullptr;
+  unsigned long long *h_ovf = nullptr;  // pinned copies, then the counters' sums (MS_COUNTERS)
   SlotTable tab{};
   int64_t mu[kSlots] = {};      // BFS: edges of the vertices a slot has not had on a frontier
   unsigned long long busy = 0;  // slots in use
@@ -48,6 +48,8 @@ struct SlotEngine {
   bool dense = false;
   bool joined = false;          // slots joined since the last superstep
   unsigned long long pull_edges = 0;  // SSSP: edges of the frontier
+  SearchWork done;                    // since init
+  unsigned long long counted[MS_COUNTERS] = {};  // the counters when last read
   bool clean = false;           // buffers hold no trace of an earlier slot
   ~SlotEngine();
   // Empty engine on `part`; buffers of an earlier run on it are kept.
@@ -74,7 +76,7 @@ struct SlotEngine {
 };
 
 int slots_run_batch(tg_partition *p, int kind, const int32_t *roots, int32_t nr, int32_t *out, hipStream_t s,
-                    int64_t *supersteps_out);
+                    int64_t *supersteps_out, SearchWork *work);
 // Give the engine of `kind` and its buffers back.
 void slots_drop(tg_partition *p, int kind);
 

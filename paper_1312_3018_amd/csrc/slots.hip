@@ -328,12 +328,14 @@ __global__ __launch_bounds__(FT) void k_ms_bfs_dense(const OffT *__restrict__ io
                                                      int32_t *__restrict__ wide, LevelRow lr, LevelRowWide lw,
                                                      const int64_t *__restrict__ off, u64 take, int64_t hubs,
                                                      int64_t rows, int64_t n, u64 (*mf)[kSlots],
-                                                     u64 (*other)[kSlots]) {
-  u64 acc = 0;
+                                                     u64 (*other)[kSlots], unsigned long long *work) {
+  u64 acc = 0, checked = 0, examined = 0;
   for (int64_t vb = (int64_t)blockIdx.x * FT; vb < n; vb += (int64_t)gridDim.x * FT) {
     const int64_t v = vb + threadIdx.x;
     const u64 seen = v < n ? visited[v] : 0ull;
-    u64 nb = pull_vertices(ioff, icol, head, front, v, v >= hubs && v < rows ? take & ~seen : 0ull);
+    const u64 want = v >= hubs && v < rows ? take & ~seen : 0ull;
+    examined += (u64)__popcll(__ballot(want != 0ull));
+    u64 nb = pull_vertices(ioff, icol, head, front, v, want, checked);
     uint32_t edges = 0;
     if (v < n) {
       if (joins || v < hubs) {
@@ -352,7 +354,17 @@ __global__ __launch_bounds__(FT) void k_ms_bfs_dense(const OffT *__restrict__ io
     }
     add_by_slot(nb, edges, acc);
   }
-  publish_by_slot<FT>(acc, mf, other);
+  __shared__ u64 pulls[FT / 64][2];
+  if ((threadIdx.x & 63) == 0) {
+    pulls[threadIdx.x >> 6][0] = checked;
+    pulls[threadIdx.x >> 6][1] = examined;
+  }
+  publish_by_slot<FT>(acc, mf, other);  // (its barrier orders `pulls` too)
+  if (threadIdx.x >= 64 && threadIdx.x < 66) {
+    u64 x = 0;
+    for (int k = 0; k < FT / 64; ++k) x += pulls[k][threadIdx.x - 64];
+    if (x) stat_add(stat_counter(work, threadIdx.x == 64 ? MS_CHECKED : MS_EXAMINED), x);
+  }
 }
 
 // From masks to the bitmap a queue is compacted from.
@@ -371,28 +383,43 @@ __global__ __launch_bounds__(BLOCK) void k_ms_widen(const uint8_t *__restrict__ 
     wide[i] = lev[i];
 }
 
-// The block's part of an SSSP frontier: the OR of its masks and its edges
-// (per-thread values), see MsState.
+// An SSSP frontier, per thread or (the block's part) published: the OR of its
+// masks, its edges, its (vertex, slot) pairs and their edges (see MsState and
+// MS_PAIRS; the latter on 64 lines, as thousands of blocks add to them).
+struct FrontierSums {
+  u64 any, edges, pairs, relax;
+  __device__ __forceinline__ void add(u64 mask, u64 deg) {
+    any |= mask;
+    edges += deg;
+    const u64 k = deg ? (u64)__popcll(mask) : 0ull;
+    pairs += k;
+    relax += k * deg;
+  }
+};
 template <int THREADS>
-__device__ __forceinline__ void publish_frontier(u64 any, u64 edges, u64 (*mf)[kSlots], u64 (*other)[kSlots]) {
-  __shared__ u64 red[2][THREADS / 64];
+__device__ __forceinline__ void publish_frontier(FrontierSums F, u64 (*mf)[kSlots], u64 (*other)[kSlots],
+                                                 unsigned long long *work) {
+  __shared__ FrontierSums red[THREADS / 64];
   for (int o = 32; o > 0; o >>= 1) {
-    any |= __shfl_xor(any, o, 64);
-    edges += __shfl_xor(edges, o, 64);
+    F.any |= __shfl_xor(F.any, o, 64);
+    F.edges += __shfl_xor(F.edges, o, 64);
+    F.pairs += __shfl_xor(F.pairs, o, 64);
+    F.relax += __shfl_xor(F.relax, o, 64);
   }
-  if ((threadIdx.x & 63) == 0) {
-    red[0][threadIdx.x >> 6] = any;
-    red[1][threadIdx.x >> 6] = edges;
-  }
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = F;
   __syncthreads();
   if (threadIdx.x == 0) {
     for (int k = 1; k < THREADS / 64; ++k) {
-      any |= red[0][k];
-      edges += red[1][k];
+      F.any |= red[k].any;
+      F.edges += red[k].edges;
+      F.pairs += red[k].pairs;
+      F.relax += red[k].relax;
     }
     u64 *mine = mf[blockIdx.x % MF_COPIES];
-    if (any & ~__hip_atomic_load(mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicOr(mine, any);
-    if (edges) atomicAdd(mine + 1, edges);
+    if (F.any & ~__hip_atomic_load(mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicOr(mine, F.any);
+    if (F.edges) atomicAdd(mine + 1, F.edges);
+    if (F.pairs) stat_add(stat_counter(work, MS_PAIRS), F.pairs);
+    if (F.relax) stat_add(stat_counter(work, MS_EDGES), F.relax);
     if (blockIdx.x == 0)
       for (int c = 0; c < MF_COPIES; ++c) other[c][0] = other[c][1] = 0ull;
   }
@@ -402,18 +429,17 @@ __device__ __forceinline__ void publish_frontier(u64 any, u64 edges, u64 (*mf)[k
 __global__ __launch_bounds__(FT) void k_ms_sssp_finalize(const Plan *__restrict__ Pp,
                                                          const int32_t *__restrict__ queue, u64 *frontier, u64 *next,
                                                          const int64_t *__restrict__ off, u64 (*mf)[kSlots],
-                                                         u64 (*other)[kSlots]) {
+                                                         u64 (*other)[kSlots], unsigned long long *work) {
   const int32_t count = Pp->count;
-  u64 any = 0, edges = 0;
+  FrontierSums F{0, 0, 0, 0};
   for (int64_t i = (int64_t)blockIdx.x * FT + threadIdx.x; i < count; i += (int64_t)gridDim.x * FT) {
     const int32_t v = queue[i];
     const u64 nb = next[v];
     next[v] = 0;
     frontier[v] = nb;
-    any |= nb;
-    edges += (u64)(off[v + 1] - off[v]);
+    F.add(nb, (u64)(off[v + 1] - off[v]));
   }
-  publish_frontier<FT>(any, edges, mf, other);
+  publish_frontier<FT>(F, mf, other, work);
 }
 
 // SSSP, dense superstep on a symmetric graph: rows are distance rows, a
@@ -431,7 +457,7 @@ struct MinOp {
   int joins;
   u64 *ovf, *ovf_slots;
   int32_t deg;  // per lane: the entry's edges
-  u64 *any, *edges;
+  FrontierSums *sums;
 
   __device__ __forceinline__ A zero() const { return ~0u; }
   __device__ __forceinline__ P begin(int32_t v, u64) const { return dist[(int64_t)v * kSlots + (threadIdx.x & 63)]; }
@@ -462,10 +488,7 @@ struct MinOp {
     }
     if (lane == 0) {
       front_new[v] = g;
-      if (g) {
-        *any |= g;
-        *edges += (u64)(uint32_t)__builtin_amdgcn_readlane(deg, j);
-      }
+      if (g) sums->add(g, (u64)(uint32_t)__builtin_amdgcn_readlane(deg, j));
     }
   }
   __device__ __forceinline__ void idle(int32_t v, u64, u64 open) const {
@@ -477,8 +500,7 @@ struct MinOp {
       next[v] = 0;
     }
     front_new[v] = g;
-    *any |= g;
-    if (g) *edges += (u64)deg;
+    if (g) sums->add(g, (u64)deg);
   }
 };
 
@@ -505,18 +527,16 @@ __global__ __launch_bounds__(BLOCK) void k_ms_sssp_pull_hubs(const int64_t *__re
 __global__ __launch_bounds__(BLOCK) void k_ms_sssp_pull(const int64_t *__restrict__ off,
                                                         const int32_t *__restrict__ col, const u64 *front,
                                                         int64_t hubs, RowSpans R, MinOp op, u64 (*mf)[kSlots],
-                                                        u64 (*other)[kSlots]) {
-  u64 any = 0, edges = 0;
-  op.any = &any;
-  op.edges = &edges;
+                                                        u64 (*other)[kSlots], unsigned long long *work) {
+  FrontierSums F{0, 0, 0, 0};
+  op.sums = &F;
   for (int64_t v = (int64_t)blockIdx.x * BLOCK + threadIdx.x; v < hubs; v += (int64_t)gridDim.x * BLOCK) {
     const u64 g = op.next[v];
     if (g) {
       op.next[v] = 0;
-      edges += (u64)(off[v + 1] - off[v]);
+      F.add(g, (u64)(off[v + 1] - off[v]));
     }
     op.front_new[v] = g;
-    any |= g;
   }
   for_row_spans(R, ((int64_t)blockIdx.x * BLOCK + threadIdx.x) >> 6, ((int64_t)gridDim.x * BLOCK) >> 6,
                 [&](int64_t i, int k) {
@@ -525,7 +545,7 @@ __global__ __launch_bounds__(BLOCK) void k_ms_sssp_pull(const int64_t *__restric
                   op.deg = (int32_t)E.d;
                   walk_list(op, E, col, front);
                 });
-  publish_frontier<BLOCK>(any, edges, mf, other);
+  publish_frontier<BLOCK>(F, mf, other, work);
 }
 
 struct Roots {
@@ -566,7 +586,17 @@ __global__ __launch_bounds__(BLOCK) void k_ms_ovf_check(const u64 *__restrict__ 
 
 // Retiring slots: drop their bits / reset their distances and overflow
 // marks everywhere (distances a row at a time, lane = slot).
-__global__ __launch_bounds__(BLOCK) void k_ms_release(u64 *visited, u64 *ovf, int64_t n, u64 mask) {
+// Block 0 of the last launch of a retirement leaves the counters' sums in
+// pinned memory: 64 lines each are slow to read from the host.
+__device__ __forceinline__ void report_work(const unsigned long long *work, unsigned long long *sums) {
+  const int k = threadIdx.x >> 6;
+  if (blockIdx.x != 0 || k >= MS_COUNTERS) return;
+  const u64 x = wave_sum((u64)work[(size_t)k * STAT_SPAN + (threadIdx.x & 63) * STAT_STRIDE]);
+  if ((threadIdx.x & 63) == 0) sums[k] = x;
+}
+__global__ __launch_bounds__(BLOCK) void k_ms_release(u64 *visited, u64 *ovf, int64_t n, u64 mask,
+                                                      const unsigned long long *work, unsigned long long *sums) {
+  if (sums) report_work(work, sums);
   for (int64_t v = (int64_t)blockIdx.x * BLOCK + threadIdx.x; v < n; v += (int64_t)gridDim.x * BLOCK) {
     if (visited) visited[v] &= ~mask;
     if (ovf) ovf[v] &= ~mask;
@@ -575,7 +605,9 @@ __global__ __launch_bounds__(BLOCK) void k_ms_release(u64 *visited, u64 *ovf, in
 // (a launch's threads are counted in 32 bits: 64 a vertex would wrap around,
 // unreported, from 2^26 vertices on)
 constexpr int64_t ROW_GRID = 16384;
-__global__ __launch_bounds__(BLOCK) void k_ms_release_dist(int32_t *dist, int64_t n, u64 mask) {
+__global__ __launch_bounds__(BLOCK) void k_ms_release_dist(int32_t *dist, int64_t n, u64 mask,
+                                                           const unsigned long long *work, unsigned long long *sums) {
+  report_work(work, sums);
   if (!((mask >> (threadIdx.x & (kSlots - 1))) & 1ull)) return;
   for (int64_t i = (int64_t)blockIdx.x * BLOCK + threadIdx.x; i < n * kSlots; i += (int64_t)gridDim.x * BLOCK)
     dist[i] = TG_INF;
@@ -666,6 +698,8 @@ int SlotEngine::init(tg_partition *part, int kind_, hipStream_t stream) {
   busy = alive = 0;
   step = 0;
   have_queue = dense = joined = false;
+  done = SearchWork();
+  if (ws.gen != gen) memset(counted, 0, sizeof(counted));  // (new buffers, cleared)
   if (kept) {
     // every slot of the last run retired: the buffers are as after set-up
     if (ws.gen != gen) ws.plan = &state->plan;
@@ -700,9 +734,11 @@ int SlotEngine::init(tg_partition *part, int kind_, hipStream_t stream) {
     TG_HIP(hipGetLastError());
   }
   if (!h_state) TG_HIP(hipHostMalloc((void **)&h_state, sizeof(MsState), hipHostMallocDefault));
-  if (!h_ovf) TG_HIP(hipHostMalloc((void **)&h_ovf, 2 * sizeof(u64), hipHostMallocDefault));
+  if (!h_ovf) TG_HIP(hipHostMalloc((void **)&h_ovf, (2 + MS_COUNTERS) * sizeof(u64), hipHostMallocDefault));
   TG_HIP(hipMemset(ws.bits_a, 0, ws.nwords * sizeof(uint32_t)));
   TG_HIP(hipMemset(ws.counters, 0, 64 * sizeof(uint32_t)));
+  TG_HIP(hipMemset(ws.work, 0, (size_t)STAT_COUNTERS * STAT_SPAN * sizeof(unsigned long long)));
+  memset(counted, 0, sizeof(counted));
   // the clears above are on the null stream, not ordered before work on a
   // non-blocking stream such as a server lane's
   TG_HIP(hipDeviceSynchronize());
@@ -770,11 +806,10 @@ int sssp_few(const GpuPart &g) { return g.in_alias ? 4 : 16; }
 
 int SlotEngine::launch_step() {
   const GpuPart &g = p->gpu;
-  u64 pulled = 0;
+  u64 pulled = 0, mf[kSlots] = {};
   bool all_pull = false;
   if (have_queue && alive) {
     if (kind == kSlotBfs) {
-      u64 mf[kSlots] = {};
       for (int c = 0; c < MF_COPIES; ++c)
         for (int k = 0; k < kSlots; ++k) mf[k] += h_state->mf[step & 1][c][k];
       pulled = ms_pull_slots(mf, mu, alive, p->tune);
@@ -784,6 +819,14 @@ int SlotEngine::launch_step() {
     }
     // a queue made from the masks would miss the slots that join
     if (dense && joined) all_pull = true;
+    if (all_pull) pulled = alive;
+    // what this superstep does, for the call's statistics
+    if (kind == kSlotBfs) {
+      done.steps += pulled ? 1.0 : 0.0;
+    } else {
+      done.read += (double)(all_pull ? (u64)g.m : pull_edges);
+      done.pulls += all_pull ? 1.0 : 0.0;
+    }
   }
   if (kind == kSlotBfs && !is_wide) {
     const int64_t next_step = have_queue ? step + 1 : step;
@@ -811,7 +854,7 @@ int SlotEngine::launch_dense() {
   if (joined) TG_HIP(hipMemsetAsync(ws.bits_a, 0, ws.nwords * sizeof(uint32_t), s));  // the joins' marks
   const int tk = ktimer_start(s);
   if (kind == kSlotBfs) {
-    TG_TRY(ms_pull_hubs(g, nullptr, now, visited, next, alive, s));
+    TG_TRY(ms_pull_hubs(g, ws, nullptr, now, visited, next, alive, s));
     LevelRow lr;
     LevelRowWide lw;
     level_rows(*this, lr, lw);
@@ -821,24 +864,24 @@ int SlotEngine::launch_dense() {
     u64 *l8 = reinterpret_cast<u64 *>(lev);
     if (g.in_off32 && !is_wide)
       hipLaunchKernelGGL((k_ms_bfs_dense<int32_t, false>), grid, block, 0, s, g.in_off32, g.in.col, head, now, then,
-                         visited, next, joins, l8, wide, lr, lw, g.out.off, alive, hubs, rows, g.n, mf, other);
+                         visited, next, joins, l8, wide, lr, lw, g.out.off, alive, hubs, rows, g.n, mf, other, ws.work);
     else if (g.in_off32)
       hipLaunchKernelGGL((k_ms_bfs_dense<int32_t, true>), grid, block, 0, s, g.in_off32, g.in.col, head, now, then,
-                         visited, next, joins, l8, wide, lr, lw, g.out.off, alive, hubs, rows, g.n, mf, other);
+                         visited, next, joins, l8, wide, lr, lw, g.out.off, alive, hubs, rows, g.n, mf, other, ws.work);
     else if (!is_wide)
       hipLaunchKernelGGL((k_ms_bfs_dense<int64_t, false>), grid, block, 0, s, g.in.off, g.in.col, head, now, then,
-                         visited, next, joins, l8, wide, lr, lw, g.out.off, alive, hubs, rows, g.n, mf, other);
+                         visited, next, joins, l8, wide, lr, lw, g.out.off, alive, hubs, rows, g.n, mf, other, ws.work);
     else
       hipLaunchKernelGGL((k_ms_bfs_dense<int64_t, true>), grid, block, 0, s, g.in.off, g.in.col, head, now, then,
-                         visited, next, joins, l8, wide, lr, lw, g.out.off, alive, hubs, rows, g.n, mf, other);
+                         visited, next, joins, l8, wide, lr, lw, g.out.off, alive, hubs, rows, g.n, mf, other, ws.work);
   } else {
-    MinOp op{g.out.w, dist, then, next, joins, ovf, ovf_slots, 0, nullptr, nullptr};
+    MinOp op{g.out.w, dist, then, next, joins, ovf, ovf_slots, 0, nullptr};
     if (hubs > 0)
       hipLaunchKernelGGL(k_ms_sssp_pull_hubs, dim3((unsigned)std::min<int64_t>(hubs * SSSP_HUB_WAVES / 4, 16384)),
                          dim3(BLOCK), 0, s, g.out.off, g.out.col, now, hubs, op);
     const RowSpans R{hubs, g.out_bins.bstart[BIN_G16], g.out_bins.bstart[BIN_G4], g.n};
     hipLaunchKernelGGL(k_ms_sssp_pull, dim3((unsigned)std::max<int64_t>(1, std::min<int64_t>((R.waves() + 3) / 4, 8192))),
-                       dim3(BLOCK), 0, s, g.out.off, g.out.col, now, hubs, R, op, mf, other);
+                       dim3(BLOCK), 0, s, g.out.off, g.out.col, now, hubs, R, op, mf, other, ws.work);
   }
   ktimer_stop(tk, s, kind == kSlotBfs ? "msbfs_expand" : "mssssp_expand");
   TG_HIP(hipGetLastError());
@@ -899,7 +942,7 @@ int SlotEngine::launch_sparse(u64 pulled) {
                          frontier, next, l8, wide, lr, lw, g.out.off, mf, other);
   } else {
     hipLaunchKernelGGL(k_ms_sssp_finalize, dim3(fgrid(g.n)), dim3(FT), 0, s, ws.plan, ws.queue, frontier, next,
-                       g.out.off, mf, other);
+                       g.out.off, mf, other, ws.work);
   }
   TG_HIP(hipGetLastError());
   return TG_OK;
@@ -950,11 +993,12 @@ int SlotEngine::retire(u64 mask, u64 *overflow) {
       TG_HIP(hipMemsetAsync(ovf_slots + 1, 0, sizeof(u64), s));
       hipLaunchKernelGGL(k_ms_ovf_check, dim3(grid), dim3(BLOCK), 0, s, ovf, dist, g.n, flagged, ovf_slots + 1);
       hipLaunchKernelGGL(k_clear_bits64, dim3(1), dim3(64), 0, s, ovf_slots, flagged);
-      hipLaunchKernelGGL(k_ms_release, dim3(grid), dim3(BLOCK), 0, s, nullptr, ovf, g.n, mask);
+      hipLaunchKernelGGL(k_ms_release, dim3(grid), dim3(BLOCK), 0, s, nullptr, ovf, g.n, mask,
+                         nullptr, nullptr);
       TG_HIP(hipMemcpyAsync(h_ovf + 1, ovf_slots + 1, sizeof(u64), hipMemcpyDeviceToHost, s));
     }
     hipLaunchKernelGGL(k_ms_release_dist, dim3((unsigned)std::min<int64_t>(nblk(g.n * kSlots), ROW_GRID)), dim3(BLOCK),
-                       0, s, dist, g.n, mask);
+                       0, s, dist, g.n, mask, ws.work, h_ovf + 2);
     TG_HIP(hipGetLastError());
     TG_HIP(hipStreamSynchronize(s));
     if (flagged && overflow) *overflow = h_ovf[1] & flagged;
@@ -962,7 +1006,8 @@ int SlotEngine::retire(u64 mask, u64 *overflow) {
     if (outs)
       hipLaunchKernelGGL(k_ms_bfs_collect, dim3(nblk(V)), dim3(BLOCK), 0, s, visited,
                          reinterpret_cast<const uint4 *>(lev), is_wide ? wide : nullptr, g.l_of_g, V, outs, tab);
-    hipLaunchKernelGGL(k_ms_release, dim3(grid), dim3(BLOCK), 0, s, visited, nullptr, g.n, mask);
+    hipLaunchKernelGGL(k_ms_release, dim3(grid), dim3(BLOCK), 0, s, visited, nullptr, g.n, mask, ws.work,
+                       h_ovf + 2);
     TG_HIP(hipGetLastError());
     TG_HIP(hipStreamSynchronize(s));
   }
@@ -984,7 +1029,7 @@ void slots_drop(tg_partition *p, int kind) {
 // Batched BFS / SSSP from a fixed list of roots: chunks of 64 slots that all
 // join at superstep 0 and retire together.
 int slots_run_batch(tg_partition *p, int kind, const int32_t *roots, int32_t nr, int32_t *out, hipStream_t s,
-                    int64_t *supersteps_out) {
+                    int64_t *supersteps_out, SearchWork *work) {
   if (!p->slots[kind]) {
     p->slots[kind] = new (std::nothrow) SlotEngine();
     if (!p->slots[kind]) return set_error(TG_ENOMEM, "slot engine: out of host memory");
@@ -1009,6 +1054,15 @@ int slots_run_batch(tg_partition *p, int kind, const int32_t *roots, int32_t nr,
     }
     u64 ovf = 0;
     TG_TRY(E.retire(fin, &ovf));
+    double now[MS_COUNTERS];
+    for (int k = 0; k < MS_COUNTERS; ++k) {
+      now[k] = (double)(E.h_ovf[2 + k] - E.counted[k]);
+      E.counted[k] = E.h_ovf[2 + k];
+    }
+    E.done.vertices += now[MS_PAIRS];
+    E.done.edges += now[MS_EDGES];
+    E.done.checked += now[MS_CHECKED];
+    E.done.examined += now[MS_EXAMINED];
     total += E.step;
     E.step = 0;
     E.have_queue = E.dense = false;
@@ -1019,6 +1073,8 @@ int slots_run_batch(tg_partition *p, int kind, const int32_t *roots, int32_t nr,
     }
   }
   if (supersteps_out) *supersteps_out = total;
+  E.done.lanes = std::min<int>(nr, kSlots);
+  *work = E.done;
   return TG_OK;
 }
 

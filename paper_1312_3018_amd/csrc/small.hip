@@ -28,6 +28,13 @@ constexpr int64_t SMALL_BFS_MAX_N = 65536;
 constexpr int QMAX = 1024;      // largest frontier walked top-down
 constexpr int MAX_BYTE = 254;   // deepest level kept in a byte
 
+struct SmallBfsInfo {
+  int32_t root, supersteps;  // local; out: -1: deeper than a byte holds
+  u64 edges, vertices;       // expanded top-down
+  u64 checked, examined;     // bottom-up, `steps` times
+  int64_t steps;
+};
+
 struct SmallBfsArgs {
   const int64_t *off;
   const int32_t *col;
@@ -36,10 +43,9 @@ struct SmallBfsArgs {
   const int32_t *icol;
   const int4 *head;
   const int32_t *l_of_g;
-  const int32_t *roots;  // local
   int32_t *state;        // [roots][n] levels by local id
   int32_t *out;          // [roots][V] levels by original id
-  int64_t *info;         // [roots]: supersteps, or -1: deeper than a byte holds
+  SmallBfsInfo *info;    // [roots]
   int64_t n, V, m, n_in;
   int64_t alpha, beta;
   int do_switch;
@@ -65,22 +71,31 @@ __global__ __launch_bounds__(BT) void k_bfs_small(const SmallBfsArgs A) {
   uint8_t *lev = reinterpret_cast<uint8_t *>(qb + QMAX);
   __shared__ uint32_t count;            // vertices that joined this superstep
   __shared__ unsigned long long edges;  // their out-degrees
+  // of all levels, for the statistics: edges looked at bottom-up, vertices and
+  // edges expanded top-down
+  __shared__ unsigned long long looked, expanded, scanned;
   const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
-  const int32_t root = A.roots[blockIdx.x];
+  SmallBfsInfo *info = A.info + blockIdx.x;
+  const int32_t root = __builtin_amdgcn_readfirstlane(info->root);
   for (int i = t; i < W; i += BT) vis[i] = fr[i] = nx[i] = 0u;
   __syncthreads();
   if (t == 0) {
     vis[root >> 5] = fr[root >> 5] = 1u << (root & 31);
     lev[root] = 0;
     qa[0] = root;
+    looked = expanded = scanned = 0ull;
   }
   int64_t m_u = A.m, m_f = A.off[root + 1] - A.off[root];
   int64_t n_f = 1;
   int L = 0, bu = 0;
+  // vertices reached, and of the bottom-up levels the vertices that looked plus
+  // 2^24 each (scalar registers are scarce here)
+  int32_t reached = 1;
+  uint32_t ups = 0;
   bool queued = true;  // qa holds the frontier
   for (;; ++L) {
     if (L >= MAX_BYTE) {
-      if (t == 0) A.info[blockIdx.x] = -1;
+      if (t == 0) info->supersteps = -1;
       return;
     }
     m_u -= m_f;
@@ -91,10 +106,12 @@ __global__ __launch_bounds__(BT) void k_bfs_small(const SmallBfsArgs A) {
     // a frontier beyond the queue can only be looked for (every level of a
     // graph without in-edges beyond the bottom-up rows would be empty)
     const bool up = bu || n_f > QMAX;
+    if (up) ups += (1u << 24) + (uint32_t)max((int32_t)A.n_in - reached, 0);
     __syncthreads();
     if (t == 0) {
       count = 0u;
       edges = 0ull;
+      if (!up) atomicAdd(&scanned, (unsigned long long)m_f);
     }
     if (!up && !queued) {
       // the queue of a frontier that a bottom-up level found
@@ -112,9 +129,11 @@ __global__ __launch_bounds__(BT) void k_bfs_small(const SmallBfsArgs A) {
     __syncthreads();
     unsigned long long deg = 0;
     if (!up) {
+      uint32_t rows = 0;
       for (int i = wv; i < (int)n_f; i += BT / 64) {
         const int32_t v = qa[i];
         const int64_t e0 = A.off[v], e1 = A.off[v + 1];
+        rows += e1 > e0 ? 1u : 0u;
         for (int64_t e = e0; e < e1; e += 256) {
           int32_t nb[4];
 #pragma unroll
@@ -135,8 +154,10 @@ __global__ __launch_bounds__(BT) void k_bfs_small(const SmallBfsArgs A) {
           }
         }
       }
+      if (lane == 0 && rows) atomicAdd(&expanded, (unsigned long long)rows);
     } else {
-      uint32_t joined = 0;
+      uint32_t joined = 0, checked = 0;
+      int64_t walked = 0;
       const auto in = [&](int32_t u) { return u >= 0 && ((fr[u >> 5] >> (u & 31)) & 1u); };
       for (int64_t v0 = wv * 64; v0 < A.n_in; v0 += BT) {
         const int64_t v = v0 + lane;
@@ -146,6 +167,8 @@ __global__ __launch_bounds__(BT) void k_bfs_small(const SmallBfsArgs A) {
         if (open) {
           const int4 h = A.head[v];
           hit = in(h.x) || in(h.y) || in(h.z) || in(h.w);
+          // (ids of a short row end in -1)
+          checked += (uint32_t)(4 + (h.x >> 31) + (h.y >> 31) + (h.z >> 31) + (h.w >> 31));
           if (!hit && h.w >= 0) {
             e = (A.ioff32 ? (int64_t)A.ioff32[v] : A.ioff64[v]) + 4;
             e1 = A.ioff32 ? (int64_t)A.ioff32[v + 1] : A.ioff64[v + 1];
@@ -154,6 +177,7 @@ __global__ __launch_bounds__(BT) void k_bfs_small(const SmallBfsArgs A) {
 #pragma unroll
               for (int k = 0; k < 4; ++k) u[k] = A.icol[e + k < e1 ? e + k : e1 - 1];
               hit = in(u[0]) || in(u[1]) || in(u[2]) || in(u[3]);
+              checked += (uint32_t)min(e1 - e, (int64_t)4);
             }
           }
         }
@@ -166,6 +190,7 @@ __global__ __launch_bounds__(BT) void k_bfs_small(const SmallBfsArgs A) {
 #pragma unroll
             for (int k = 0; k < 4; ++k) u[k] = b + k * 64 + lane < a1 ? A.icol[b + k * 64 + lane] : -1;
             found = __ballot(in(u[0]) || in(u[1]) || in(u[2]) || in(u[3])) != 0ull;
+            walked += min(a1 - b, (int64_t)256);
           }
           if (lane == src) hit = found;
         }
@@ -181,13 +206,18 @@ __global__ __launch_bounds__(BT) void k_bfs_small(const SmallBfsArgs A) {
           }
         }
       }
-      if (lane == 0 && joined) atomicAdd(&count, joined);
+      const unsigned long long seen = (unsigned long long)wave_total(checked) + (unsigned long long)walked;
+      if (lane == 0) {
+        if (joined) atomicAdd(&count, joined);
+        if (seen) atomicAdd(&looked, seen);
+      }
     }
     deg = wave_sum(deg);
     if (lane == 0 && deg) atomicAdd(&edges, deg);
     __syncthreads();
-    n_f = count;
-    m_f = (int64_t)edges;
+    n_f = __builtin_amdgcn_readfirstlane((int)count);
+    m_f = lane_i64((int64_t)edges, 0);
+    reached += (int32_t)n_f;
     queued = !up;
     if (n_f == 0) break;
     for (int i = t; i < W; i += BT) {
@@ -204,11 +234,15 @@ __global__ __launch_bounds__(BT) void k_bfs_small(const SmallBfsArgs A) {
   int32_t *state = A.state + (int64_t)blockIdx.x * A.n;
   for (int64_t v = t; v < A.n; v += BT) state[v] = (vis[v >> 5] >> (v & 31)) & 1u ? (int32_t)lev[v] : TG_INF;
   int32_t *out = A.out + (int64_t)blockIdx.x * A.V;
-  for (int64_t gid = t; gid < A.V; gid += BT) {
-    const int32_t l = A.l_of_g[gid];
-    out[gid] = (vis[l >> 5] >> (l & 31)) & 1u ? (int32_t)lev[l] : TG_INF;
+  for (int32_t g0 = t; g0 < (int32_t)A.V; g0 += 8 * BT) {  // (eight ids in flight: 46.2 -> 44.9 us, RMAT-14)
+    int32_t l[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) l[k] = g0 + k * BT < (int32_t)A.V ? A.l_of_g[g0 + k * BT] : 0;
+#pragma unroll
+    for (int k = 0; k < 8; ++k)
+      if (g0 + k * BT < (int32_t)A.V) out[g0 + k * BT] = (vis[l[k] >> 5] >> (l[k] & 31)) & 1u ? (int32_t)lev[l[k]] : TG_INF;
   }
-  if (t == 0) A.info[blockIdx.x] = L + 1;
+  if (t == 0) *info = SmallBfsInfo{root, L + 1, scanned, expanded, looked, ups & 0xFFFFFFu, ups >> 24};
 }
 
 size_t small_bfs_lds(int64_t n) {
@@ -235,6 +269,7 @@ size_t small_bfs_lds(int64_t n) {
 // vertices in LDS tables did not help: what the blocks flush is as much.)
 constexpr int RT = 4;
 constexpr int LIVE = 64;  // rounds a chunk holds at most
+constexpr int ROUND_SLOTS = 256, ROUND_STRIDE = 16, ROUND_BITS = 36;
 
 struct RoundArgs {
   const int64_t *off;
@@ -245,6 +280,7 @@ struct RoundArgs {
   // [0]: some candidate did not fit; [1]: verdict; then two chunks of LIVE
   // flags, one per round
   uint32_t *flags;
+  u64 *work;  // on ROUND_SLOTS lines: edges relaxed, and above ROUND_BITS the vertices they went out from
   int64_t n, nwords, hubs;
   RowSpans spans;
 };
@@ -257,7 +293,15 @@ __global__ __launch_bounds__(BLOCK) void k_round_init(RoundArgs A, const int32_t
     A.settled[y * A.n + v] = TG_INF;
     if (v < A.nwords) A.ovf[y * A.nwords + v] = 0u;
   }
-  if (y == 0 && blockIdx.x == 0 && threadIdx.x < 3) A.flags[threadIdx.x] = 0u;
+  if (y == 0 && blockIdx.x == 0) {
+    if (threadIdx.x < 3) A.flags[threadIdx.x] = 0u;
+    for (int i = threadIdx.x; i < ROUND_SLOTS * ROUND_STRIDE; i += BLOCK) A.work[i] = 0ull;
+  }
+}
+
+// sum: edges + vertices << ROUND_BITS
+__device__ __forceinline__ void round_count(const RoundArgs &A, u64 sum) {
+  atomicAdd(A.work + (size_t)(blockIdx.x % ROUND_SLOTS) * ROUND_STRIDE, sum);
 }
 
 __device__ __forceinline__ void round_relax(const RoundArgs &A, int32_t *dist, uint32_t *ovf, int32_t dv, int32_t nb,
@@ -323,8 +367,10 @@ __global__ __launch_bounds__(RB) void k_round(const RoundArgs A, int live, int l
       for (int q = 0; q < RT; ++q)
         if (nb[q] >= 0) round_relax(A, dist, ovf, dv, nb[q], wt[q], cur[q]);
     }
+    if (t == 0) round_count(A, (u64)(e1 - A.off[v]) + (1ull << ROUND_BITS));
     return;
   }
+  u64 relaxed = 0;
   const int64_t wave = ((int64_t)blockIdx.x - A.hubs) * (RB / 64) + wv;
   const int64_t waves = ((int64_t)gridDim.x - A.hubs) * (RB / 64);
   for_row_spans(A.spans, wave, waves, [&](int64_t i, int k) {
@@ -338,7 +384,8 @@ __global__ __launch_bounds__(RB) void k_round(const RoundArgs A, int live, int l
              return (1ull << 32) | (u64)(uint32_t)d;
            },
            i, k, A.off);
-    if (!__ballot(E.m != 0ull)) return;
+    const u64 on = __ballot(E.m != 0ull);
+    if (!on) return;
     if (lane == 0) A.flags[live] = 1u;
     // (rows of these spans are below the BLOCK bin's degree: the list fits 32 bits)
     const int32_t len = (int32_t)E.total;
@@ -359,7 +406,10 @@ __global__ __launch_bounds__(RB) void k_round(const RoundArgs A, int live, int l
       for (int q = 0; q < RT; ++q)
         if (nb[q] >= 0) round_relax(A, dist, ovf, dv[q], nb[q], wt[q], cur[q]);
     }
+    relaxed += (u64)E.total + ((u64)__popcll(on) << ROUND_BITS);
   });
+  // (last: a later read would wait for the addition)
+  if (lane == 0 && relaxed) round_count(A, relaxed);
 }
 
 // flags[1] = 1 if some vertex with an overflowing candidate stayed unreached.
@@ -369,10 +419,21 @@ __global__ __launch_bounds__(BLOCK) void k_round_verdict(RoundArgs A) {
     A.flags[1] = 1u;
 }
 
+// (The first block leaves the counters' sums in pinned memory: their lines are
+// slow to read from the host.)
 __global__ __launch_bounds__(BLOCK) void k_round_collect(const int32_t *__restrict__ l_of_g,
                                                          const int32_t *__restrict__ dist, int64_t n, int64_t V,
-                                                         int32_t *__restrict__ out) {
+                                                         int32_t *__restrict__ out, const u64 *work, u64 *sums) {
+  static_assert(ROUND_SLOTS == BLOCK, "a counter a thread");
   const int64_t y = blockIdx.y, gid = (int64_t)blockIdx.x * BLOCK + threadIdx.x;
+  if (blockIdx.x == 0 && y == 0) {
+    const u64 x = work[(size_t)threadIdx.x * ROUND_STRIDE];
+    const u64 edges = block_sum(x & ((1ull << ROUND_BITS) - 1)), verts = block_sum(x >> ROUND_BITS);
+    if (threadIdx.x == 0) {
+      sums[0] = edges;
+      sums[1] = verts;
+    }
+  }
   if (gid < V) out[y * V + gid] = dist[y * n + l_of_g[gid]];
 }
 
@@ -385,14 +446,16 @@ struct SmallState {
   int64_t rows = 0;  // entries of `state`
   int32_t *state = nullptr;
   uint32_t *flags = nullptr, *h_flags = nullptr;
+  u64 *work = nullptr, *h_work = nullptr;  // the rounds' counters; their sums
   int32_t *roots = nullptr;
-  int64_t *info = nullptr;
+  SmallBfsInfo *info = nullptr;
   int32_t *h_roots = nullptr;
-  int64_t *h_info = nullptr;
+  SmallBfsInfo *h_info = nullptr;
   ~SmallState() {
     if (h_roots) TG_QUIET(hipHostFree(h_roots));
     if (h_info) TG_QUIET(hipHostFree(h_info));
     if (h_flags) TG_QUIET(hipHostFree(h_flags));
+    if (h_work) TG_QUIET(hipHostFree(h_work));
   }
 };
 
@@ -421,7 +484,9 @@ int small_state(tg_partition *p, int64_t rows, SmallState **out) {
     TG_TRY(dalloc(made->arena, &made->roots, (size_t)CHUNK));
     TG_TRY(dalloc(made->arena, &made->info, (size_t)CHUNK));
     TG_TRY(dalloc(made->arena, &made->flags, (size_t)(2 + 2 * LIVE)));
+    TG_TRY(dalloc(made->arena, &made->work, (size_t)ROUND_SLOTS * ROUND_STRIDE));
     TG_TRY(pinned(&made->h_flags, (size_t)(2 + 2 * LIVE)));
+    TG_TRY(pinned(&made->h_work, (size_t)2));
     TG_TRY(pinned(&made->h_roots, (size_t)CHUNK));
     TG_TRY(pinned(&made->h_info, (size_t)CHUNK));
     p->small = made.release();
@@ -452,7 +517,7 @@ bool small_bfs_supported(const GpuPart &g) {
 }
 
 int small_bfs(tg_partition *p, const int32_t *roots, int32_t nr, int32_t *levels, int32_t *parents, hipStream_t s,
-              int64_t *supersteps, bool *deep) {
+              int64_t *supersteps, SearchWork *work, bool *deep) {
   const GpuPart &g = p->gpu;
   const Tuning &t = p->tune;
   SmallState *S = nullptr;
@@ -460,10 +525,13 @@ int small_bfs(tg_partition *p, const int32_t *roots, int32_t nr, int32_t *levels
   *deep = false;
   for (int64_t c0 = 0; c0 < nr; c0 += CHUNK) {
     const int64_t cn = std::min<int64_t>(CHUNK, nr - c0);
-    for (int64_t k = 0; k < cn; ++k) S->h_roots[k] = p->h_l_of_g[roots[c0 + k]];
-    TG_HIP(hipMemcpyAsync(S->roots, S->h_roots, (size_t)cn * sizeof(int32_t), hipMemcpyHostToDevice, s));
+    for (int64_t k = 0; k < cn; ++k) {
+      S->h_roots[k] = p->h_l_of_g[roots[c0 + k]];
+      S->h_info[k] = SmallBfsInfo{S->h_roots[k], 0, 0, 0, 0, 0, 0};
+    }
+    TG_HIP(hipMemcpyAsync(S->info, S->h_info, (size_t)cn * sizeof(SmallBfsInfo), hipMemcpyHostToDevice, s));
     SmallBfsArgs A{g.out.off, g.out.col, g.in_off32, g.in.off, g.in.col, reinterpret_cast<const int4 *>(g.in_head),
-                   g.l_of_g, S->roots, S->state, levels + c0 * g.n_global, S->info, g.n, g.n_global, g.m,
+                   g.l_of_g, S->state, levels + c0 * g.n_global, S->info, g.n, g.n_global, g.m,
                    g.in_alias ? g.out_bins.bstart[BIN_ZERO] : g.n, t.bfs_alpha, t.bfs_beta, (int)t.bfs_do};
     const int tk = ktimer_start(s);
     hipLaunchKernelGGL(k_bfs_small, dim3((unsigned)cn), dim3(BT), small_bfs_lds(g.n), s, A);
@@ -472,19 +540,27 @@ int small_bfs(tg_partition *p, const int32_t *roots, int32_t nr, int32_t *levels
     if (parents)
       for (int64_t k = 0; k < cn; ++k)
         TG_TRY(bfs_parents(g, nullptr, S->state + k * g.n, S->h_roots[k], parents + (c0 + k) * g.n_global, s));
-    TG_HIP(hipMemcpyAsync(S->h_info, S->info, (size_t)cn * sizeof(int64_t), hipMemcpyDeviceToHost, s));
+    TG_HIP(hipMemcpyAsync(S->h_info, S->info, (size_t)cn * sizeof(SmallBfsInfo), hipMemcpyDeviceToHost, s));
     TG_HIP(hipStreamSynchronize(s));
     ktimer_flush();
     for (int64_t k = 0; k < cn; ++k) {
-      if (S->h_info[k] < 0) *deep = true;
-      else *supersteps += S->h_info[k];
+      const SmallBfsInfo &I = S->h_info[k];
+      if (I.supersteps < 0) *deep = true;
+      *supersteps += I.supersteps;
+      work->edges += (double)I.edges;
+      work->vertices += (double)I.vertices;
+      work->checked += (double)I.checked;
+      work->examined += (double)I.examined;
+      work->steps += (double)I.steps;
     }
     if (*deep) return TG_OK;
   }
+  work->lanes = (int)std::min<int64_t>(nr, CHUNK);
   return TG_OK;
 }
 
-int round_sssp(tg_partition *p, const int32_t *roots, int32_t nr, int32_t *dist, hipStream_t s, int64_t *rounds) {
+int round_sssp(tg_partition *p, const int32_t *roots, int32_t nr, int32_t *dist, hipStream_t s, int64_t *rounds,
+               SearchWork *work) {
   const GpuPart &g = p->gpu;
   const int64_t n = g.n, V = g.n_global, nwords = (n + 31) / 32;
   // roots per launch: as many as rows of 2^24 entries in all
@@ -496,7 +572,8 @@ int round_sssp(tg_partition *p, const int32_t *roots, int32_t nr, int32_t *dist,
     for (int64_t k = 0; k < cn; ++k) S->h_roots[k] = p->h_l_of_g[roots[c0 + k]];
     TG_HIP(hipMemcpyAsync(S->roots, S->h_roots, (size_t)cn * sizeof(int32_t), hipMemcpyHostToDevice, s));
     RoundArgs A{g.out.off, g.out.col, g.out.w, p->tune.sssp_packed ? g.out.cw : nullptr, S->state, S->state + per * n,
-                reinterpret_cast<uint32_t *>(S->state + 2 * per * n), S->flags, n, nwords,
+                reinterpret_cast<uint32_t *>(S->state + 2 * per * n), S->flags,
+                S->work, n, nwords,
                 // (rows past 2^31 / 1024 blocks would not fit the grid: the waves take any row)
                 std::min<int64_t>(g.out_bins.bstart[BIN_WAVE], 1 << 20), {}};
     A.spans = RowSpans{A.hubs, std::max(A.hubs, g.out_bins.bstart[BIN_G16]), std::max(A.hubs, g.out_bins.bstart[BIN_G4]),
@@ -532,10 +609,13 @@ int round_sssp(tg_partition *p, const int32_t *roots, int32_t nr, int32_t *dist,
       if (S->h_flags[1]) return set_error(TG_ERANGE, "sssp: a shortest-path distance does not fit below INT32_MAX");
     }
     hipLaunchKernelGGL(k_round_collect, dim3((unsigned)((V + BLOCK - 1) / BLOCK), y), dim3(BLOCK), 0, s, g.l_of_g,
-                       S->state, n, V, dist + c0 * V);
+                       S->state, n, V, dist + c0 * V, S->work, S->h_work);
     TG_HIP(hipGetLastError());
+    TG_HIP(hipStreamSynchronize(s));
+    work->edges += (double)S->h_work[0];
+    work->vertices += (double)S->h_work[1];
   }
-  TG_HIP(hipStreamSynchronize(s));
+  work->lanes = (int)per;
   return TG_OK;
 }
 

@@ -513,6 +513,16 @@ int gpu_pagerank_rows_step(tg_partition *p, double damping, int mode, int32_t k,
 void pr_rows_free(GpuPart &g);
 int pr_write_initial(const GpuPart &g, float *rank_out, double N, hipStream_t s);
 
+// What the searches of a call did (tg_last_stats).
+struct SearchWork {
+  // per search: out-edges of the vertices expanded (BFS: top-down) or relaxed
+  // from, and those of these vertices that have any
+  double edges = 0, vertices = 0;
+  double checked = 0, examined = 0, steps = 0;  // BFS, bottom-up: in-edges looked at, vertices that looked, supersteps
+  double pulls = 0, read = 0;  // SSSP engine: pulled supersteps, edges read (once for all searches)
+  int lanes = 1;               // searches in flight together
+};
+
 // algorithms (GPU partition only)
 // Lane i of a multi-search call: its workspace (lane 0: p->ws) and stream
 // (lane 0: the caller's s), created on first use.
@@ -552,9 +562,10 @@ int gpu_bc_source(tg_partition *p, int32_t src_local, hipStream_t s);
 // more levels than it can hold, the outputs are not complete.
 bool small_bfs_supported(const GpuPart &g);
 int small_bfs(tg_partition *p, const int32_t *roots, int32_t nr, int32_t *levels, int32_t *parents, hipStream_t s,
-              int64_t *supersteps, bool *deep);
+              int64_t *supersteps, SearchWork *work, bool *deep);
 // SSSP for a few roots (original ids), a launch per round for all of them.
-int round_sssp(tg_partition *p, const int32_t *roots, int32_t nr, int32_t *dist, hipStream_t s, int64_t *rounds);
+int round_sssp(tg_partition *p, const int32_t *roots, int32_t nr, int32_t *dist, hipStream_t s, int64_t *rounds,
+               SearchWork *work);
 void small_free(tg_partition *p);
 // SSSP by buckets for several roots at once (buckets.hip).
 bool buckets_supported(const tg_partition *p);

@@ -281,6 +281,99 @@ def test_overflow_verdict_is_the_same_on_both_routes(gpu):
         assert gpu.sssp(P, [1]).cpu().numpy().tolist() == [[2**31 - 10, 0, 2**31 - 10]]
 
 
+# -------------------------------------------- statistics of every route
+
+def stats_of(tg, call):
+    call()
+    return tg.tg_last_stats()
+
+
+@pytest.mark.parametrize("sym", [True, False])
+@pytest.mark.parametrize("count", [1, 3, 40, 70])
+def test_bfs_statistics_on_every_route(gpu, sym, count):
+    """Top-down throughout, the edges scanned are the out-edges of what each
+    search reached; with bottom-up steps every vertex that joined in one was
+    expanded in neither or one of them.  One workgroup per root, the 64-slot
+    engine and single searches."""
+    g = graphgen.rmat(10, symmetrize=sym, seed=4)
+    deg = np.diff(g.offsets)
+    roots = graphgen.sample_roots(g, count, seed=5).tolist()
+    reached = [oracle.bfs(g.offsets, g.cols, r) != INF for r in roots]
+    verts, edges = sum(int((m & (deg > 0)).sum()) for m in reached), sum(int(deg[m].sum()) for m in reached)
+    keys = {"roots", "supersteps", "edges_scanned", "vertices_expanded", "bottom_up_edges_checked", "bottom_up_steps",
+            "bottom_up_vertices_examined", "lanes"}
+    for route in ({"bfs_batch_roots": 1}, {"bfs_batch_roots": 0}):
+        P = load(gpu, g, None, {**route, "bfs_do": 0})
+        for call in (gpu.bfs, gpu.bfs_batched):
+            st = stats_of(gpu, lambda: call(P, roots))
+            assert keys <= set(st), route
+            assert (st["edges_scanned"], st["vertices_expanded"]) == (edges, verts), (route, call)
+            assert st["bottom_up_steps"] == st["bottom_up_edges_checked"] == st["bottom_up_vertices_examined"] == 0
+    # (workgroups: a frontier past the queue is looked for all the same)
+    for tuning in ({"bfs_do": 0, "bfs_batch_roots": -1}, {"bfs_batch_roots": -1, "bfs_do": 1}, {"bfs_batch_roots": 1},
+                   {"bfs_batch_roots": 0}):
+        st = stats_of(gpu, lambda: gpu.bfs(load(gpu, g, None, tuning), roots))
+        assert keys <= set(st) and st["roots"] == count and st["lanes"] >= min(count, 2), tuning
+        # (none where every superstep of the engine is pulled)
+        assert 0 <= st["edges_scanned"] <= edges and 0 <= st["vertices_expanded"] <= verts, tuning
+        if st["bottom_up_steps"] == 0:
+            assert (st["edges_scanned"], st["vertices_expanded"]) == (edges, verts), tuning
+        else:
+            assert st["edges_scanned"] < edges, tuning
+            assert 0 < st["bottom_up_vertices_examined"] <= g.n * st["bottom_up_steps"], tuning
+            assert st["bottom_up_vertices_examined"] <= st["bottom_up_edges_checked"] + g.n * st["bottom_up_steps"]
+            assert st["bottom_up_edges_checked"] <= g.nnz * st["bottom_up_steps"], tuning
+    assert stats_of(gpu, lambda: gpu.bfs(load(gpu, g), roots))["bottom_up_steps"] > 0
+
+
+def test_pulled_edges_are_counted(gpu):
+    """A star's leaves each look at their one in-neighbour, the hub, when it
+    is on the frontier, and the far hub's row is read to its end."""
+    leaves = 3000
+    g = graphgen.from_edges(leaves + 1, np.zeros(leaves, int), np.arange(1, leaves + 1), symmetrize=True)
+    for tuning in (None, {"bfs_batch_roots": 1}):
+        P = load(gpu, g, None, tuning)
+        # every leaf is unvisited but the root of the search; then none is
+        st = stats_of(gpu, lambda: gpu.bfs(P, [0, 0]))
+        assert st["supersteps"] in (2, 4)
+        if tuning is None:
+            assert st["bottom_up_edges_checked"] == st["bottom_up_vertices_examined"] == 2 * leaves
+        else:  # shared: a leaf looks once for both
+            assert st["bottom_up_edges_checked"] == st["bottom_up_vertices_examined"] == leaves
+
+
+@pytest.mark.parametrize("sym", [True, False])
+@pytest.mark.parametrize("count", [1, 4, 5, 20, 64, 70])
+def test_sssp_statistics_on_every_route(gpu, sym, count):
+    """Every reached vertex relaxes its out-edges at least once for each
+    search; on a path from its end exactly once."""
+    g = graphgen.rmat(10, symmetrize=sym, seed=4)
+    w = graphgen.weights(g, seed=1)
+    deg = np.diff(g.offsets)
+    roots = graphgen.sample_roots(g, count, seed=5).tolist()
+    reached = [oracle.bfs(g.offsets, g.cols, r) != INF for r in roots]
+    verts, edges = sum(int((m & (deg > 0)).sum()) for m in reached), sum(int(deg[m].sum()) for m in reached)
+    n = 300
+    path = graphgen.from_edges(n, np.arange(n - 1), np.arange(1, n), symmetrize=sym)
+    keys = {"roots", "supersteps", "relaxations", "activations", "pull_supersteps", "heavy_pull_edges_checked",
+            "heavy_pull_vertices", "lanes"}
+    for tuning in (None, {"sssp_batch_roots": 1}, BUCKETS, {"sssp_batch_roots": 0}):
+        st = stats_of(gpu, lambda: gpu.sssp(load(gpu, g, w, tuning), roots))
+        assert keys <= set(st) and st["roots"] == count and 1 <= st["lanes"] <= count, tuning
+        if not st["heavy_pull_edges_checked"]:  # (else a bucket's heavy edges are not relaxed from its members)
+            assert st["activations"] >= verts and st["relaxations"] >= edges, tuning
+        if tuning == {"sssp_batch_roots": 1}:
+            assert (st["pull_supersteps"] > 0) == (sym and count > 4)
+        st = stats_of(gpu, lambda: gpu.sssp(load(gpu, path, np.ones(path.nnz, np.int32), tuning), [0] * count))
+        if not st["heavy_pull_edges_checked"]:
+            has = int((np.diff(path.offsets) > 0).sum())
+            assert st["relaxations"] == count * path.nnz, tuning
+            # (the single searches count a vertex once per pass, light and heavy)
+            assert count * has <= st["activations"] <= count * has * (2 if tuning == {"sssp_batch_roots": 0} else 1)
+    st = stats_of(gpu, lambda: gpu.sssp_batched(load(gpu, g, w), roots))
+    assert keys <= set(st) and st["relaxations"] >= edges and st["edges_read"] >= edges / min(count, 64)
+
+
 # ------------------------------------------- one workgroup per BFS root
 
 @pytest.mark.parametrize("n", [1, 2, 31, 32, 33, 63, 64, 65, 1023, 1024, 1025, 32768, 65536, 65537])

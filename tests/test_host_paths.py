@@ -111,6 +111,8 @@ assert fake.fake_most_threads() >= n
 # Copies of the engine's control block (its plan, 104 bytes, then the
 # frontiers' sums) are marked, so that every slot has a frontier for ever.
 SERVE = """
+PLAN = 104
+CONTROL = PLAN + 2 * 8 * 64 * 8
 n = 1 << 16
 P = path(n, 100)
 S, gid, t = vp(), i32(), ctypes.c_uint64()
@@ -137,7 +139,7 @@ def test_server_query_ends_when_its_levels_find_no_room(run):
     are served."""
     run(SERVE + """
 fake.fake_malloc_limit(n * 256)
-fake.fake_mark_copies(104 + 2 * 8 * 64 * 8, 104)
+fake.fake_mark_copies(CONTROL, PLAN)
 assert results(submit(0, 3)) == [ENOMEM] * 3
 fake.fake_mark_copies(0, 0)
 assert results(submit(0, 70)) == [OK] * 70
@@ -149,7 +151,7 @@ lib.server_destroy(S)
 def test_server_query_ends_when_a_superstep_fails(run, kind):
     run(SERVE + f"""
 assert results(submit({kind}, 2)) == [OK] * 2
-fake.fake_mark_copies(104 + 2 * 8 * 64 * 8, 104)
+fake.fake_mark_copies(CONTROL, PLAN)
 tickets = submit({kind}, 3)
 time.sleep(0.3)  # all three in slots
 fake.fake_failing_syncs(1)
@@ -167,7 +169,7 @@ def test_pinned_memory_that_fails_leaves_no_half_made_scratch(run, call):
     """The few-launch searches without their pinned memory: the call takes the
     next route, and the one after it finds no half-made scratch."""
     run(f"""
-for k in range(3):
+for k in range(4):
     P = path(1000, 100)
     fake.fake_host_mallocs(k)
     check({call})
