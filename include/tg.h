@@ -368,7 +368,8 @@ int partition_info(const tg_partition *p, char *json, size_t cap);
  * and from a 64-slot engine edges_read (once for all its searches).  CC:
  * edges_pushed.  On hybrid partitions per-phase
  * milliseconds (gpu_ms: the GPU's kernels; cpu_ms: the host threads;
- * exchange_ms: the copies of both directions on their copy streams), bytes
+ * exchange_ms: the messages of both directions, on their copy streams or, up
+ * to 128 KB, in the kernel that moves them, without its launch), bytes
  * exchanged (exchange_bytes, of which exchange_h2d_bytes host-to-GPU) and
  * the local out-edges the host threads processed (cpu_edges; the boundary
  * edges of both sides are reduced on the GPU).  Same return convention as

@@ -71,6 +71,8 @@ struct Box {
   size_t cap = 0;                   // bytes of each buffer
 };
 
+constexpr int MESSAGE_BLOCKS = 8;  // of a message that crosses by a kernel, at most
+
 struct HybridState {
   CpuPart cpu;
   Channel g2c, c2g;
@@ -103,7 +105,8 @@ struct HybridState {
   int32_t *d_cpu_g_of_l = nullptr;
   int32_t *d_stage = nullptr;   // host-partition results on their way to the output
   int32_t *h_stage = nullptr;
-  long long *h_clock = nullptr;  // pinned: clocks around the small messages, [direction][parity][2]
+  long long *h_clock = nullptr;  // pinned: clocks of the small messages, [direction][parity][MESSAGE_BLOCKS][2]
+  int blocks[2][2] = {};         // blocks of the last one
   bool by_kernel[2][2] = {};     // whether the last one of [direction][parity] crossed so
   bool waited[2] = {};           // [parity]: the last one needs no event of its own
   int clock_khz = 100000;

@@ -409,7 +409,7 @@ int build_hybrid(tg_partition *p, uint64_t seed) {
   TG_TRY(up(A, &hy->d_cpu_g_of_l, C.g_of_l.data(), (size_t)C.n));
   TG_TRY(dalloc(A, &hy->d_stage, (size_t)C.n));
   TG_HIP(hipHostMalloc((void **)&hy->h_stage, (size_t)C.n * sizeof(int32_t), hipHostMallocDefault));
-  TG_HIP(hipHostMalloc((void **)&hy->h_clock, 8 * sizeof(long long), hipHostMallocDefault));
+  TG_HIP(hipHostMalloc((void **)&hy->h_clock, 2 * 2 * MESSAGE_BLOCKS * 2 * sizeof(long long), hipHostMallocDefault));
   TG_HIP(hipDeviceGetAttribute(&hy->clock_khz, hipDeviceAttributeWallClockRate, p->device));
   if (hy->clock_khz <= 0) hy->clock_khz = 100000;
   TG_HIP(hipStreamCreateWithFlags(&hy->cs_d2h, hipStreamNonBlocking));

@@ -450,12 +450,12 @@ __global__ void k_set_f64h(double *p, int64_t i, double v) {
 
 // Small messages cross by a kernel on the GPU's own stream, which reads or
 // writes the pinned host memory itself (16 bytes per lane, the tail in words).
-// Block 0 leaves its first and last clock.
+// Each block leaves its first and last clock.
 constexpr int COPY_THREADS = 1024;
 constexpr size_t COPY_BLOCK_BYTES = (size_t)COPY_THREADS * 16;
 __global__ __launch_bounds__(COPY_THREADS) void k_message(char *dst, const char *src, int64_t bytes,
-                                                          long long *clock2) {
-  if (clock2 && blockIdx.x == 0 && threadIdx.x == 0) clock2[0] = wall_clock64();
+                                                          long long *clocks) {
+  if (clocks && threadIdx.x == 0) clocks[2 * blockIdx.x] = wall_clock64();
   const int64_t n16 = bytes / 16, n4 = (bytes - n16 * 16) / 4;
   for (int64_t i = (int64_t)blockIdx.x * COPY_THREADS + threadIdx.x; i < n16; i += (int64_t)gridDim.x * COPY_THREADS)
     reinterpret_cast<uint4 *>(dst)[i] = reinterpret_cast<const uint4 *>(src)[i];
@@ -463,7 +463,7 @@ __global__ __launch_bounds__(COPY_THREADS) void k_message(char *dst, const char 
     reinterpret_cast<uint32_t *>(dst + n16 * 16)[threadIdx.x] =
         reinterpret_cast<const uint32_t *>(src + n16 * 16)[threadIdx.x];
   __syncthreads();
-  if (clock2 && blockIdx.x == 0 && threadIdx.x == 0) clock2[1] = wall_clock64();
+  if (clocks && threadIdx.x == 0) clocks[2 * blockIdx.x + 1] = wall_clock64();
 }
 
 // A search's device state at its start.
@@ -516,18 +516,31 @@ int clear_words(uint32_t *w, int64_t n, hipStream_t s) {
 // 10 PageRank iterations 1.82, 2.00, 4.00, 8.75 / 1.54, 1.62, 3.66, 8.33; four
 // searches 2.40, 2.90, 3.49 / 2.36, 2.60, 3.14.  Beyond, a copy engine moves
 // the bytes beside the kernels.
-constexpr size_t SMALL_MESSAGE = (size_t)1 << 17;
+constexpr size_t SMALL_MESSAGE = MESSAGE_BLOCKS * COPY_BLOCK_BYTES;  // 128 KB
 
-int launch_message(void *dst, const void *src, size_t bytes, long long *clock2, hipStream_t s) {
-  const unsigned grid = (unsigned)std::max<size_t>(1, (bytes + COPY_BLOCK_BYTES - 1) / COPY_BLOCK_BYTES);
+unsigned message_blocks(size_t bytes) {
+  return (unsigned)std::max<size_t>(1, (bytes + COPY_BLOCK_BYTES - 1) / COPY_BLOCK_BYTES);
+}
+
+int launch_message(void *dst, const void *src, size_t bytes, long long *clocks, hipStream_t s) {
+  const unsigned grid = message_blocks(bytes);
   hipLaunchKernelGGL(k_message, dim3(grid), dim3(COPY_THREADS), 0, s, static_cast<char *>(dst),
-                     static_cast<const char *>(src), (int64_t)bytes, clock2);
+                     static_cast<const char *>(src), (int64_t)bytes, clocks);
   TG_HIP(hipGetLastError());
   return TG_OK;
 }
 
-double clock_ms(const HybridState &h, const long long *clock2) {
-  return (double)(clock2[1] - clock2[0]) / (double)h.clock_khz;
+// Clocks of the message of direction d and parity b; and its time, from its
+// first block's start to its last block's end (the clock is the device's).
+long long *message_clocks(HybridState &h, int d, int b) { return h.h_clock + (2 * d + b) * 2 * MESSAGE_BLOCKS; }
+double message_ms(HybridState &h, int d, int b) {
+  const long long *c = message_clocks(h, d, b);
+  long long first = c[0], last = c[1];
+  for (int k = 1; k < h.blocks[d][b]; ++k) {
+    first = std::min(first, c[2 * k]);
+    last = std::max(last, c[2 * k + 1]);
+  }
+  return (double)(last - first) / (double)h.clock_khz;
 }
 
 // GPU -> host: once the GPU stream has produced box b, copy `bytes` of it.
@@ -536,7 +549,8 @@ int post_d2h(HybridState &h, int b, size_t bytes, hipStream_t s, bool stream_wai
   h.by_kernel[0][b] = bytes > 0 && bytes <= SMALL_MESSAGE;
   h.waited[b] = stream_waited && h.by_kernel[0][b];
   if (h.by_kernel[0][b]) {
-    TG_TRY(launch_message(h.out.h[b], h.out.d[b], bytes, h.h_clock + 2 * b, s));
+    h.blocks[0][b] = (int)message_blocks(bytes);
+    TG_TRY(launch_message(h.out.h[b], h.out.d[b], bytes, message_clocks(h, 0, b), s));
     if (!h.waited[b]) TG_HIP(hipEventRecord(h.ev_d2h[b][1], s));
     return TG_OK;
   }
@@ -552,7 +566,7 @@ int post_d2h(HybridState &h, int b, size_t bytes, hipStream_t s, bool stream_wai
 int wait_d2h(HybridState &h, int b, double *ms) {
   if (!h.waited[b]) TG_HIP(hipEventSynchronize(h.ev_d2h[b][1]));
   if (h.by_kernel[0][b]) {
-    *ms += clock_ms(h, h.h_clock + 2 * b);
+    *ms += message_ms(h, 0, b);
     return TG_OK;
   }
   float t = 0.0f;
@@ -591,8 +605,10 @@ size_t list_prefix_bytes(int64_t nslots) {
 // offset of the device box; the GPU stream waits for it.
 int post_h2d(HybridState &h, int b, size_t off, size_t bytes, hipStream_t s) {
   h.by_kernel[1][b] = bytes > 0 && bytes <= SMALL_MESSAGE;
-  if (h.by_kernel[1][b])
-    return launch_message(h.in.d[b] + off, h.in.h[b] + off, bytes, h.h_clock + 4 + 2 * b, s);
+  if (h.by_kernel[1][b]) {
+    h.blocks[1][b] = (int)message_blocks(bytes);
+    return launch_message(h.in.d[b] + off, h.in.h[b] + off, bytes, message_clocks(h, 1, b), s);
+  }
   TG_HIP(hipEventRecord(h.ev_h2d[b][0], h.cs_h2d));
   if (bytes) TG_HIP(hipMemcpyAsync(h.in.d[b] + off, h.in.h[b] + off, bytes, hipMemcpyHostToDevice, h.cs_h2d));
   TG_HIP(hipEventRecord(h.ev_h2d[b][1], h.cs_h2d));
@@ -603,7 +619,7 @@ int post_h2d(HybridState &h, int b, size_t off, size_t bytes, hipStream_t s) {
 // Time of the last host-to-GPU copy of parity b (complete once the GPU
 // stream has passed it).
 double h2d_ms(HybridState &h, int b) {
-  if (h.by_kernel[1][b]) return clock_ms(h, h.h_clock + 4 + 2 * b);
+  if (h.by_kernel[1][b]) return message_ms(h, 1, b);
   float t = 0.0f;
   TG_QUIET(hipEventElapsedTime(&t, h.ev_h2d[b][0], h.ev_h2d[b][1]));
   return t;
@@ -626,8 +642,9 @@ void concat(std::vector<std::vector<int32_t>> &parts, std::vector<int32_t> &out)
 }
 
 // Per-call accounting.  cpu_edges: the local out-edges the host threads
-// processed; exchange_ms: time of the copies in both directions (copy
-// stream events); exchange_bytes: what they moved, of which h2d_bytes went
+// processed; exchange_ms: time of the messages in both directions (copy
+// stream events, or of small ones the clocks of the kernel that moved them);
+// exchange_bytes: what they moved, of which h2d_bytes went
 // to the GPU.
 struct Phase {
   double gpu_ms = 0, cpu_ms = 0, exchange_ms = 0, bytes = 0, cpu_edges = 0, h2d_bytes = 0;

@@ -1,7 +1,7 @@
 /* A HIP runtime without a device, for tests of libtg.so's host code on the
- * CPU: "device" memory is ordinary zeroed memory, kernels do nothing, and
- * allocations and launches fail where a real device would refuse them or
- * where a test asks for it.  Loaded (RTLD_GLOBAL) before the library, its
+ * CPU: "device" memory is ordinary zeroed memory, kernels do nothing (but
+ * for the one that moves messages), and allocations and launches fail where a
+ * real device would refuse them or where a test asks for it.  Loaded (RTLD_GLOBAL) before the library, its
  * definitions take the place of the runtime's.
  *
  * Copies and fills of more than BIG bytes are left out: what they move is
@@ -24,6 +24,8 @@ static int host_mallocs_left = -1;                /* the same for pinned ones */
 static size_t marked_copy = 0, marked_from = 0;   /* device-to-host copies of this size: bytes from .. on become 127 */
 static int failing_syncs = 0;                     /* stream synchronisations still to fail */
 static uint64_t launches, most_threads, live_mallocs;
+static const void *message_kernel; /* k_message(dst, src, bytes, clocks) */
+static uint64_t message_ticks;     /* the time its launches took, each block 100 ticks longer than the one before */
 static __thread hipError_t last_error;
 
 void fake_thread_limit(uint64_t n) { thread_limit = n; }
@@ -33,6 +35,7 @@ void fake_host_mallocs(int n) { host_mallocs_left = n; }
 void fake_mark_copies(size_t bytes, size_t from) { marked_copy = bytes, marked_from = from; }
 void fake_failing_syncs(int n) { failing_syncs = n; }
 uint64_t fake_launches(void) { return launches; }
+uint64_t fake_message_ticks(void) { return message_ticks; }
 uint64_t fake_live_mallocs(void) { return live_mallocs; }
 uint64_t fake_most_threads(void) { return most_threads; }
 
@@ -120,13 +123,22 @@ hipError_t __hipPopCallConfiguration(dim3 *grid, dim3 *block, size_t *shared, hi
   return hipSuccess;
 }
 hipError_t hipLaunchKernel(const void *f, dim3 g, dim3 b, void **args, size_t shared, hipStream_t st) {
-  (void)f, (void)args, (void)st;
+  (void)st;
   const uint64_t x = (uint64_t)g.x * b.x, y = (uint64_t)g.y * b.y, z = (uint64_t)g.z * b.z;
   ++launches;
   if (x > most_threads) most_threads = x;
   if (!x || !y || !z || (uint64_t)b.x * b.y * b.z > 1024 || shared > 163840 || x >= thread_limit ||
       y >= thread_limit || z >= thread_limit)
     return fail(hipErrorInvalidConfiguration);
+  if (f == message_kernel) {
+    memmove(*(char **)args[0], *(char **)args[1], *(int64_t *)args[2]);
+    long long *clocks = *(long long **)args[3];
+    if (clocks) {
+      const uint64_t t0 = 1000 * launches;
+      for (unsigned k = 0; k < g.x; ++k) clocks[2 * k] = t0 + k, clocks[2 * k + 1] = t0 + 100 * (k + 1);
+      message_ticks += 100 * g.x;
+    }
+  }
   return hipSuccess;
 }
 void **__hipRegisterFatBinary(const void *data) {
@@ -137,7 +149,8 @@ void **__hipRegisterFatBinary(const void *data) {
 void __hipUnregisterFatBinary(void **h) { (void)h; }
 void __hipRegisterFunction(void **h, const void *f, char *a, const char *b, unsigned c, void *d, void *e, void *i,
                            void *j, int *k) {
-  (void)h, (void)f, (void)a, (void)b, (void)c, (void)d, (void)e, (void)i, (void)j, (void)k;
+  (void)h, (void)a, (void)c, (void)d, (void)e, (void)i, (void)j, (void)k;
+  if (strstr(b, "k_message")) message_kernel = f;
 }
 void __hipRegisterVar(void **h, void *v, char *a, char *b, int c, size_t d, int e, int f) {
   (void)h, (void)v, (void)a, (void)b, (void)c, (void)d, (void)e, (void)f;

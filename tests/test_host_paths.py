@@ -41,7 +41,7 @@ lib.server_destroy.argtypes = [vp]
 BUF = 4096  # an address no kernel writes to
 
 
-def path(n, length, weight=300, tuning=b"{{}}", symmetric=True):
+def path(n, length, weight=300, tuning=b"{{}}", symmetric=True, share=0.0):
     "A partition of n vertices, the first `length` of them a path."
     deg = np.zeros(n + 1, dtype=np.int64)
     deg[1:length + 1] = 2
@@ -54,7 +54,7 @@ def path(n, length, weight=300, tuning=b"{{}}", symmetric=True):
     G, P = vp(), vp()
     check(lib.graph_load_csr(n, col.size, off, col, w.ctypes.data, SYMMETRIC if symmetric else 0, None,
                              ctypes.byref(G)))
-    check(lib.partition_by_degree(G, 0, 0.0, 0, tuning, ctypes.byref(P)))
+    check(lib.partition_by_degree(G, 0, share, 0, tuning, ctypes.byref(P)))
     return P
 
 
@@ -103,6 +103,25 @@ for k in (1, 2, 64):
 check(lib.cc(P, BUF, None))
 check(lib.pagerank(P, 0.85, 2, 0, BUF, None))
 assert fake.fake_most_threads() >= n
+""")
+
+
+# ------------------------------------------------------------ hybrid split
+
+def test_exchange_time_is_that_of_whole_messages(run):
+    """exchange_ms of messages moved by a kernel: from the first block's start
+    to the last block's end, for messages of one block and of eight."""
+    run("""
+import json
+fake.fake_message_ticks.restype = ctypes.c_uint64
+n = 60000
+P = path(n, n, share=0.5)
+check(lib.pagerank(P, 0.85, 10, 0, BUF, None))
+buf = ctypes.create_string_buffer(4096)
+lib.tg_last_stats(buf, 4096)
+st = json.loads(buf.value)
+ticks = fake.fake_message_ticks()
+assert ticks > 10 * 800 and abs(st["exchange_ms"] - ticks / 1e5) < 1e-9, (st, ticks)
 """)
 
 
