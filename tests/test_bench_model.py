@@ -1,6 +1,7 @@
 """The performance model of section 3 as the bench evaluates it (host logic,
 no GPU): Equation 4's limits and the achieved-speedup definition on
 synthetic measurements with known answers."""
+import inspect
 import math
 
 import bench
@@ -67,3 +68,37 @@ def test_serve_solo_rule(monkeypatch):
     monkeypatch.setattr(bench, "SERVE_SOLO_MIN_VERTICES", 0)
     assert bench.serve_solo(star)  # skew about 1000
     assert not bench.serve_solo(ring)  # every degree 2: skew 1
+
+
+class FakeLibrary:
+    """Records the calls of the bench's timed helpers."""
+
+    def __init__(self):
+        self.calls = []
+
+    def bc(self, part, sources):
+        self.calls.append(list(sources))
+
+    def partition_info(self, part):
+        return {"tuning": {"bfs_alpha": 14, "bfs_batch_roots": -1, "sssp_batch_roots": 32}}
+
+    def partition_retune(self, part, tuning):
+        self.calls.append(tuning)
+
+
+def test_one_at_a_time_is_one_source_a_call():
+    """Several sources of one bc() call share the 64-source chain, which the
+    bench's one-at-a-time figure is compared with."""
+    tg = FakeLibrary()
+    bench.one_by_one(tg.bc, None, [5, 6, 7])
+    assert tg.calls == [[5], [6], [7]]
+    assert "one_by_one(tg.bc" in inspect.getsource(bench.bench_bc)
+    assert "tg.bc(P" not in inspect.getsource(bench.bench_bc)
+
+
+def test_single_searches_refuse_the_shared_schedules():
+    tg = FakeLibrary()
+    with bench.single_searches(tg, None):
+        assert tg.calls[-1]["bfs_batch_roots"] == 0 and tg.calls[-1]["sssp_batch_roots"] == 0
+    assert tg.calls[-1] == {"bfs_alpha": 14, "bfs_batch_roots": -1, "sssp_batch_roots": 32}
+    assert "single_searches(tg, P)" in inspect.getsource(bench.serve_capacity)
