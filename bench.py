@@ -44,7 +44,10 @@ def kernel_sources_digest(files):
 # Sources each timed kernel is built from, plus the tuning cache that sets its
 # launch shapes (a traffic figure is only reused while these are unchanged).
 KERNEL_FILES = {
-    "pr_gather": ["pagerank.hip", "pr_sell.hip", "pr_rows.hip", "kcommon.h", "../tuning_cache.json"],
+    "pr_gather": ["pagerank.hip", "pr_sell.hip", "pr_rows.hip", "ms.h", "kcommon.h", "../tuning_cache.json"],
+    "msbfs_expand": ["slots.hip", "slots.h", "ms.hip", "ms.h", "kcommon.h", "../tuning_cache.json"],
+    "mssssp_expand": ["slots.hip", "slots.h", "ms.h", "kcommon.h", "../tuning_cache.json"],
+    "bucket_relax": ["buckets.hip", "kcommon.h", "../tuning_cache.json"],
     "bfs_step": ["bfs.hip", "frontier.hip", "kcommon.h", "../tuning_cache.json"],
     "sssp_relax": ["sssp.hip", "kcommon.h", "../tuning_cache.json"],
     "sssp_pull": ["sssp.hip", "frontier.hip", "kcommon.h", "../tuning_cache.json"],
@@ -70,15 +73,20 @@ def load_traffic(kernel: str, workload: str):
 # Rows of profiles/traffic.json: the pass directories (<algo>_fetch,
 # <algo>_write, <algo>_hit) their counters come from, the kernels, and how
 # they make up one launch of the bench kernel: "sum" (each launch runs all of
-# them: their per-launch means add) or "pool" (each launch is one of them:
-# the mean over all their launches).
+# them: their per-launch means add), "pool" (each launch is one of them: the
+# mean over all their launches) or a number n (each launch is one of the first
+# n of them, the others run along: the sum of all over the first n's launches).
 TRAFFIC_ROWS = {
     "sssp_relax": ("sssp", ["k_sssp_relax<true, 1>", "k_sssp_relax<true, 2>"], "pool"),
     "sssp_pull": ("ssspp", ["k_sssp_pull_heavy"], "sum"),
-    # (sliced columns, then row blocks by class: a run has the kernels of one)
+    # (the last three are of a layout no longer built, for counters taken on it)
     "pr_gather": ("pr", ["k_pr_sell<true>", "k_pr_sell_long", "k_pr_combine", "k_pr_rows<true, int, 8>",
                          "k_pr_long<true>", "k_pr_dsum"], "sum"),
     "bfs_step": ("bfs", ["k_bfs_step<int>"], "sum"),
+    "msbfs_expand": ("msbfs", ["k_ms_push", "k_ms_pull<int>", "k_ms_bfs_dense<int, false>", "k_ms_pull_hubs<int>"], 3),
+    "mssssp_expand": ("mssssp", ["k_ms_sssp_pull", "k_ms_sssp_expand", "k_ms_sssp_expand_few", "k_ms_sssp_pull_hubs"],
+                      3),
+    "bucket_relax": ("bucket", ["k_bucket_relax"], "sum"),
 }
 # A 1 GiB device-to-device copy (--copy-calibration) reads FETCH_SIZE =
 # 524317 KiB and WRITE_SIZE = 1048576 KiB on MI355X.
@@ -110,6 +118,9 @@ def traffic_from(pmc_dir: str, workload: str = "rmat24") -> dict:
         if how == "pool":
             vals = [x for lst in lists for x in lst]
             return (sum(vals) / len(vals) if vals else 0.0), len(vals)
+        if isinstance(how, int):
+            n = sum(len(lst) for lst in lists[:how])
+            return sum(sum(lst) for lst in lists) / max(n, 1), n
         return sum(sum(lst) / len(lst) for lst in lists if lst), (len(lists[0]) if lists else 0)
 
     out = {}
@@ -972,8 +983,23 @@ def main():
         kernels["pr_gather"] = kern(sp, "pr_slice_gather", pr_bytes_iter * sp["pr_slice_gather_n"], ("pr_combine",))
     if "bfs_step_ms" in sb:
         kernels["bfs_step"] = kern(sb, "bfs_step", bfs_step_bytes)
+    if "msbfs_expand_ms" in sb:
+        # the 64-slot engine's pulls, per in-edge looked at its id and mask, per
+        # vertex that looked its offsets and visited mask (the pushes' edges are
+        # counted per search, not per read: left out)
+        kernels["msbfs_expand"] = kern(sb, "msbfs_expand", 12.0 * sb.get("bottom_up_edges_checked", 0) +
+                                       16.0 * sb.get("bottom_up_vertices_examined", 0))
+    if "mssssp_expand_ms" in ss:
+        # the 64-slot engine: per edge read its id and weight, per relaxation
+        # and per activation a distance
+        kernels["mssssp_expand"] = kern(ss, "mssssp_expand", 8.0 * ss.get("edges_read", 0) +
+                                        4.0 * ss.get("relaxations", 0) + 4.0 * ss.get("activations", 0))
     if "sssp_relax_ms" in ss:
         kernels["sssp_relax"] = kern(ss, "sssp_relax", sssp_bytes)
+    if "bucket_relax_ms" in ss:
+        # the shared bucket schedule: pushed and pulled edges in one launch
+        kernels["bucket_relax"] = kern(ss, "bucket_relax", sssp_bytes + 4.125 * ss.get("heavy_pull_edges_checked", 0) +
+                                       16.0 * ss.get("heavy_pull_vertices", 0))
     if "sssp_pull_ms" in ss:
         # a bucket's heavy edges pulled: per unsettled vertex its offsets,
         # light count and distance, per edge checked its packed word and the
@@ -998,9 +1024,9 @@ def main():
                     "traffic": tr, "algorithmic_bytes_per_launch": round(bytes_per_launch),
                     "avg_launch_ms": round(v["ms"] / n, 5), "busy_ms_per_launch": round(eff_ms, 5),
                     "launches": int(v["n"]), "share_of_step": round(v["busy"] / prof_ms_step, 4)}
+    bfs_kernel_bytes = sum(kernels[k]["bytes"] for k in ("bfs_step", "msbfs_expand") if k in kernels)
     dominant = max(kernels, key=lambda k: kernels[k]["busy"]) if kernels else None
     # every timed kernel of the step, also those whose bytes are not counted
-    # (the 64-slot engines read an edge once for all the roots on its source)
     busy = {k[:-len("_busy_ms")]: round(v, 3) for st in (sb, ss, sp) for k, v in st.items() if k.endswith("_busy_ms")}
 
     # per-root latency: each root alone (one search in flight)
@@ -1030,7 +1056,6 @@ def main():
     print("[bench] single-root latency pass done", file=sys.stderr, flush=True)
 
     def per_root(st, key):
-        # (the 64-slot engines do not count these)
         return round(st[key] / nr) if key in st else None
 
     out = {
@@ -1052,7 +1077,7 @@ def main():
                    "global_batch": nr, "parallelism": "none (1 GPU)"},
         "bfs": {"gteps": round(bfs_edges / (t_bfs / 1e3) / 1e9, 2), "ms_per_root": round(t_bfs / nr, 4),
                 "hbm_gbs_top_down_equivalent": round(bfs_bytes / (t_bfs / 1e3) / 1e9, 1),
-                "hbm_gbs_kernel_bytes": round(bfs_step_bytes / (t_bfs / 1e3) / 1e9, 1) if "edges_scanned" in sb else None,
+                "hbm_gbs_kernel_bytes": round(bfs_kernel_bytes / (t_bfs / 1e3) / 1e9, 1) if bfs_kernel_bytes else None,
                 "graph500_undirected_gteps": round(bfs_edges / 2 / (t_bfs / 1e3) / 1e9, 2),
                 "top_down_edges_per_root": per_root(sb, "edges_scanned"),
                 "bottom_up_edges_checked_per_root": per_root(sb, "bottom_up_edges_checked"),
@@ -1079,9 +1104,12 @@ def main():
         "tuning": {"source": tuning_used, "values": tg.partition_info(P)["tuning"]},
         "host_wall_s": round(wall, 3),
     }
-    if run_sssp and "sssp_relax_ms" in ss:
+    relax_ms = ss.get("sssp_relax_ms", ss.get("bucket_relax_ms"))
+    if run_sssp and relax_ms:
         gc = gather_reference(V, g.cols)
-        relax_rate = ss.get("relaxations", 0) / (ss["sssp_relax_ms"] / 1e3)
+        # (the bucket schedule's launches hold its pulled edges as well)
+        pulled = 0 if "sssp_relax_ms" in ss else ss.get("heavy_pull_edges_checked", 0)
+        relax_rate = (ss.get("relaxations", 0) + pulled) / (relax_ms / 1e3)
         gc["sssp_relaxations_per_s"] = round(relax_rate)
         gc["sssp_relax_vs_edge_order"] = round(relax_rate / gc["edge_order_gathers_per_s"], 3)
         out["gather_reference"] = gc

@@ -632,10 +632,10 @@ int bucket_sssp(tg_partition *p, const int32_t *roots_local, int32_t nr, int32_t
         const int tk = ktimer_start(s);
         hipLaunchKernelGGL(k_bucket_advance, dim3(1), dim3(64), 0, s, A);
         hipLaunchKernelGGL(k_bucket_collect, dim3(cgrid, y), dim3(CT), 0, s, A);
-        ktimer_stop(tk, s, "sssp_collect");
+        ktimer_stop(tk, s, "bucket_collect");
         const int tr = ktimer_start(s);
         hipLaunchKernelGGL(k_bucket_relax, dim3((unsigned)t.sssp_grid), dim3(BLOCK), 0, s, A);
-        ktimer_stop(tr, s, "sssp_relax");
+        ktimer_stop(tr, s, "bucket_relax");
       }
       TG_HIP(hipGetLastError());
       steps += STEPS;

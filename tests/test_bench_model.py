@@ -3,6 +3,8 @@ no GPU): Equation 4's limits and the achieved-speedup definition on
 synthetic measurements with known answers."""
 import inspect
 import math
+import os
+import re
 
 import bench
 
@@ -102,3 +104,33 @@ def test_single_searches_refuse_the_shared_schedules():
         assert tg.calls[-1]["bfs_batch_roots"] == 0 and tg.calls[-1]["sssp_batch_roots"] == 0
     assert tg.calls[-1] == {"bfs_alpha": 14, "bfs_batch_roots": -1, "sssp_batch_roots": 32}
     assert "single_searches(tg, P)" in inspect.getsource(bench.serve_capacity)
+
+
+def test_timed_kernels_are_tied_to_their_sources():
+    """Every kernel whose bytes the bench states has a digest over the files it
+    is built from, those it includes among them."""
+    src = os.path.join(bench.ROOT, "paper_1312_3018_amd", "csrc")
+    body = inspect.getsource(bench.main)
+    for kernel in re.findall(r'kernels\["(\w+)"\] = ', body):
+        files = bench.KERNEL_FILES[kernel]
+        names = [re.sub(r"<.*", "", k) for k in bench.TRAFFIC_ROWS[kernel][1]]
+        text = {f: open(os.path.join(src, f)).read() for f in files if not f.startswith("..")}
+        assert any(f"{k}(" in t for k in names for t in text.values()), kernel
+        for f, t in text.items():
+            for inc in re.findall(r'#include "(\w+\.h)"', t):
+                assert inc in files or inc == "tg_internal.h", (kernel, f, inc)
+
+
+def test_traffic_of_a_launch_that_is_one_of_several_kernels(tmp_path):
+    names = ["k_ms_sssp_pull(a)", "k_ms_sssp_expand(b)", "k_ms_sssp_pull_hubs(c)"]
+    for kind in ("fetch", "write", "hit"):
+        d = tmp_path / f"mssssp_{kind}"
+        d.mkdir()
+        lines = ["Kernel_Name,Counter_Name,Counter_Value"]
+        for k in names + names[:2]:
+            for c in {"fetch": ["FETCH_SIZE"], "write": ["WRITE_SIZE"], "hit": ["TCC_HIT_sum", "TCC_MISS_sum"]}[kind]:
+                lines.append(f'"{k}",{c},100')
+        (d / "run_counter_collection.csv").write_text("\n".join(lines) + "\n")
+    t = bench.traffic_from(str(tmp_path))["rmat24"]["mssssp_expand"]
+    assert t["launches_sampled"] == 4  # two pulls and two pushes; the hubs belong to the pulls
+    assert t["write_bytes"] == 5 * 100 * 1024 // 4 and t["l2_hit_rate"] == 0.5
