@@ -31,6 +31,7 @@ static __thread hipError_t last_error;
 void fake_thread_limit(uint64_t n) { thread_limit = n; }
 void fake_malloc_limit(size_t n) { malloc_limit = n; }
 void fake_mallocs(int n) { mallocs_left = n; }
+int fake_mallocs_left(void) { return mallocs_left; }
 void fake_host_mallocs(int n) { host_mallocs_left = n; }
 void fake_mark_copies(size_t bytes, size_t from) { marked_copy = bytes, marked_from = from; }
 void fake_failing_syncs(int n) { failing_syncs = n; }

@@ -217,3 +217,45 @@ for k in range(24):
     lib.partition_free(P)
 assert failed > 15
 """)
+
+
+@pytest.mark.parametrize("part,call", [
+    ("path(1000, 100)", "lib.bfs(P, roots(3), 3, BUF, BUF, None)"),  # a workgroup a root
+    ("path(70000, 100)", "lib.bfs(P, roots(2), 2, BUF, None, None)"),  # the engine
+    ("path(1000, 100)", "lib.sssp(P, roots(1), 1, BUF, None)"),  # rounds
+    ("path(70000, 100)", "lib.sssp(P, roots(40), 40, BUF, None)"),  # the engine
+    ("path(1000, 100)", "lib.bc(P, roots(2), 2, BUF, None)"),  # the chain
+    ("path(1000, 100)", "lib.pagerank(P, 0.85, 2, 0, BUF, None)"),  # slices, whole
+    ("path(1000, 100, tuning=b'{\"pr_whole\": 0}')", "lib.pagerank(P, 0.85, 2, 0, BUF, None)"),  # slices by class
+])
+def test_route_without_room_falls_back(run, part, call):
+    """Whichever allocation of a route's own scratch fails, the call takes the
+    route that needs less, and a later call can take the first one."""
+    run(f"""
+k, again = 0, []
+while True:
+    P = {part}
+    check(lib.cc(P, BUF, None))  # the workspace every route shares
+    fake.fake_mallocs(k)
+    check({call})
+    reached = fake.fake_mallocs_left() < 0
+    fake.fake_mallocs(-1)
+    check({call})
+    again.append(fake.fake_live_mallocs())
+    lib.partition_free(P)
+    if not reached:
+        break
+    k += 1
+assert k >= 3, k
+assert min(again) >= again[-1], again  # the first route's scratch was made after all
+""")
+
+
+def test_buckets_without_room_fall_back(run):
+    """Shared buckets (eight roots' rows at once) give way to single searches."""
+    run("""
+n = 100000
+P = path(n, 100, weight=200, tuning=b'{"sssp_batch_roots": 64}')
+fake.fake_malloc_limit(16 * n)
+check(lib.sssp(P, roots(8), 8, BUF, None))
+""")
