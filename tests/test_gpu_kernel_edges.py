@@ -184,6 +184,52 @@ def test_pulled_distances_that_do_not_fit(gpu, leaves):
         assert np.array_equal(got[i], oracle.sssp(g2.offsets, g2.cols, w2, r))
 
 
+@pytest.mark.parametrize("deg", [3, 15, 17, 100, 511, 512, 1500])
+@pytest.mark.parametrize("sym,roots", [(True, 5), (True, 6), (True, 64), (False, 16), (False, 17), (False, 64)])
+def test_distances_of_many_slots_that_do_not_fit(gpu, deg, sym, roots):
+    """Overflowing candidates with more slots in flight than are walked edge by
+    edge: pulled rows of each split and pushed ones, edges that many slots
+    share and edges with one; `far` hangs on `deg` vertices of a random core by
+    edges that only a search from one of them can take."""
+    big = 2**31 - 10
+    rng = np.random.default_rng(deg)
+    core = deg + 200
+    far, one, two = core, core + 1, core + 2  # and a path far from the core, for one slot
+    a, b = rng.integers(0, core, 10 * core), rng.integers(0, core, 10 * core)
+    ring = np.arange(core)
+    near = np.arange(deg)  # the vertices next to `far`
+    src = np.r_[a, ring, near, one, two]
+    dst = np.r_[b, (ring + 1) % core, np.full(deg, far), two, core + 3]
+    g = graphgen.from_edges(core + 4, src, dst, symmetrize=sym)
+    row = np.repeat(np.arange(g.n), np.diff(g.offsets))
+    w = np.where((row < core) & (g.cols < core), 1000, big).astype(np.int32)
+    P = load(gpu, g, w)
+    inside = rng.integers(0, deg, roots - 2).tolist()
+
+    def same(P, w, rs):
+        got = gpu.sssp_batched(P, rs).cpu().numpy()
+        pulls = gpu.tg_last_stats()["pull_supersteps"]
+        # (the search on the short path ends early: five leave four)
+        assert pulls > 0 if sym and roots > 5 else sym or pulls == 0
+        for i in sorted({0, 1, len(rs) // 2, len(rs) - 2, len(rs) - 1}):
+            assert np.array_equal(got[i], oracle.sssp(g.offsets, g.cols, w, rs[i])), i
+
+    good = inside + [two, near[0]]
+    same(P, w, good)  # `two` is the middle of its path
+    for bad, name in ((deg + 50, deg + 50), (one, one)):
+        with pytest.raises(gpu.TGError) as ei:
+            gpu.sssp_batched(P, inside[:3] + [bad] + inside[3:] + [two])
+        assert ei.value.code == gpu.TG_ERANGE and f"root {name}" in str(ei.value)
+    with pytest.raises(gpu.TGError) as ei:
+        gpu.sssp_batched(P, (deg + np.arange(roots)).tolist())
+    assert ei.value.code == gpu.TG_ERANGE
+    # one of the edges is light: candidates overflow, then the vertex is reached
+    light = ((row == 0) & (g.cols == far)) | ((row == far) & (g.cols == 0))
+    w2 = np.where(light, 1000, w).astype(np.int32)
+    same(load(gpu, g, w2), w2, (deg + np.arange(roots)).tolist())
+    same(P, w, good)  # nothing of the failed calls is left
+
+
 @pytest.mark.parametrize("deg", [1, 63, 64, 65, 511, 513, 2049])
 def test_batched_betweenness_rows_of_each_split(gpu, deg):
     """Two hubs sharing `deg` middle vertices (every row sum a multiple of the
@@ -693,6 +739,25 @@ def test_betweenness_rows_shared_or_not(gpu, rows, deg):
     for f in (gpu.bc, gpu.bc_batched):
         got = f(load(gpu, g, None, bins), srcs).cpu().numpy().astype(np.float64)
         assert np.all(np.abs(got - ref) <= 1e-5 * np.abs(ref) + 1e-6 * max(ref.max(), 1.0))
+
+
+@pytest.mark.parametrize("rows,deg", [(1, 16), (513, 16), (1, 300), (512, 64), (1025, 300)])
+def test_betweenness_of_one_source(gpu, rows, deg):
+    """The same rows for a source at a time: long ones of each bin and rows
+    past the most that are shared, added up over the calls."""
+    rng = np.random.default_rng(rows + deg)
+    pool = max(2 * deg, 400)
+    cols = np.concatenate([rng.choice(pool, deg, replace=False) for _ in range(rows)])
+    src = np.repeat(pool + np.arange(rows), deg)
+    g = graphgen.from_edges(pool + rows, np.r_[src, np.arange(pool)], np.r_[cols, (np.arange(pool) + 1) % pool],
+                            symmetrize=True)
+    bins = {"g4_min_deg": 2, "g16_min_deg": 4, "wave_min_deg": 8, "block_min_deg": 50, "hub_min_deg": 200,
+            "hub_chunk": 256}
+    P = load(gpu, g, None, bins)
+    for s in (0, pool // 3, pool, pool + rows - 1):
+        ref = oracle.bc(g.offsets, g.cols, [s])
+        got = gpu.bc(P, [s]).cpu().numpy().astype(np.float64)
+        assert np.all(np.abs(got - ref) <= 1e-5 * np.abs(ref) + 1e-6 * max(ref.max(), 1.0)), s
 
 
 @pytest.mark.parametrize("n,count", [(65535, 1), (65536, 2), (131072, 2), (131072, 3), (300000, 4), (300000, 5)])
