@@ -222,6 +222,41 @@ def test_overflowing_query_does_not_poison_its_lane(gpu, solo):
     assert ei.value.code == gpu.TG_ERANGE
 
 
+def test_queries_join_and_leave_pulled_supersteps(gpu):
+    """A path whose every superstep is pulled and whose levels go past a byte:
+    queries join and retire between two pulls, on both sides of that level."""
+    import torch
+    n = 440
+    g = graphgen.from_edges(n, np.arange(n - 1), np.arange(1, n), symmetrize=True)
+    w = np.full(g.nnz, 300, dtype=np.int32)
+    G = gpu.graph_load_csr(g.n, g.offsets, g.cols, w, symmetric=True)
+    P = gpu.partition_by_degree(G)
+    gpu.bfs_batched(P, [0, n - 1])
+    st = gpu.tg_last_stats()
+    assert st["supersteps"] >= n and st["bottom_up_steps"] >= n - 1
+    gpu.sssp_batched(P, list(range(0, n, 7))[:60])
+    assert gpu.tg_last_stats()["pull_supersteps"] > 200
+    S = gpu.Server(max_slots=64)
+    gid = S.add_graph(P)
+    rng = np.random.default_rng(1)
+    roots = np.r_[0, n - 1, rng.integers(0, n, 298)]
+    outs = torch.empty((2, len(roots), n), dtype=torch.int32, device="cuda")
+    tickets = []
+    for i, r in enumerate(roots.tolist()):
+        for kind in (0, 1):
+            tickets.append(S.submit(gid, kind, r, outs[kind, i]))
+        if i % 8 == 7:
+            S.wait(tickets.pop(0))
+    for t in tickets:
+        S.wait(t)
+    want = np.abs(roots[:, None] - np.arange(n)[None])
+    assert np.array_equal(outs[0].cpu().numpy(), want)
+    assert np.array_equal(outs[1].cpu().numpy(), 300 * want)
+    st = S.stats()
+    assert st["completed"] == 2 * len(roots) and st["max_concurrent"] > 1
+    S.close()
+
+
 def test_add_graph_while_queries_run(gpu, graphs):
     """Graphs registered while earlier queries are in flight (the worker walks
     its lanes meanwhile): every result, old and new, equals the oracle."""
