@@ -28,6 +28,16 @@
  *     the output buffer (host-blocking).
  *   - A partition holds per-call scratch memory; calls on one partition must
  *     not overlap (one host thread at a time per partition).
+ *   - That scratch is made by the first call that needs it and kept until
+ *     partition_free.  The largest, in device bytes: BFS with several roots
+ *     (the 64-slot engine, bfs_batched's) 96 per vertex, another 256 per
+ *     vertex once a search passes level 254; SSSP with many roots (its engine,
+ *     sssp_batched's) 288 per vertex; with up to eight roots in the bucket
+ *     schedule about 14 per vertex and root; bc with several sources and
+ *     bc_batched about 1130 per vertex and 2 per edge.  bfs, sssp, bc and
+ *     pagerank take a route that needs less where theirs finds no room;
+ *     "bfs_batch_roots": 0 and "sssp_batch_roots": 0 (partition_retune) keep
+ *     bfs and sssp to single searches from the start.
  */
 #ifndef TG_H
 #define TG_H
@@ -176,7 +186,9 @@ int partition_retune(tg_partition *p, const char *tuning_json);
 /* Level-synchronous breadth-first search (section 6.3.2, Figure 11).  With
  * "bfs_do" (the default) a superstep whose frontier holds many edges runs
  * bottom-up instead: every unvisited vertex looks for an in-neighbour on the
- * frontier.  Levels are the same either way.
+ * frontier.  Levels are the same either way.  Small graphs are searched by a
+ * workgroup per root, and several roots without parents share bfs_batched's
+ * engine ("bfs_batch_roots").
  *   roots     host array of num_roots original vertex ids.
  *   levels    device int32 [num_roots * V]; row r holds each vertex's hop
  *             count from roots[r] (TG_INF when unreachable).
@@ -204,7 +216,10 @@ int bfs_batched(const tg_partition *p, const int32_t *roots, int32_t num_roots,
  * ones once per bucket ("sssp_split"), pulled instead of pushed on
  * TG_SYMMETRIC graphs when that touches fewer edges ("sssp_hpull");
  * "sssp_ring": 0 and "sssp_delta": 0 give the paper's frontier
- * Bellman-Ford.  Up to "sssp_lanes" roots run at once on library streams
+ * Bellman-Ford.  Up to eight roots share that schedule's launches, and many
+ * share sssp_batched's engine; few roots on a graph of up to 2^20 vertices run
+ * a launch per round of relaxations.  Where none of these applies (see
+ * "sssp_batch_roots"), up to "sssp_lanes" roots run at once on library streams
  * and workspaces of their own.  The distances do not depend on any of
  * these.
  *   dist      device int32 [num_roots * V] (TG_INF when unreachable).
@@ -244,7 +259,8 @@ int pagerank(const tg_partition *p, float damping, int32_t iterations,
  * up (the first time a slot has any); the level and sigma of the vertices
  * each side's boundary edges reach then cross once; the backward sweep
  * sends, per level, the deltas of those vertices.  Host deltas are summed
- * in fp64.
+ * in fp64.  On a GPU-only partition several sources run as bc_batched's chain,
+ * one by one where that finds no room.
  * Errors: TG_EINVAL, TG_ENOMEM, TG_EDEVICE, TG_ERANGE (a path count reached
  * 2^53, beyond which fp64 counts are no longer exact). */
 int bc(const tg_partition *p, const int32_t *sources, int32_t num_sources,
@@ -278,8 +294,12 @@ typedef struct tg_server tg_server;
 enum { TG_QUERY_BFS = 0, TG_QUERY_SSSP = 1 };
 
 /* opts_json: NULL or {"max_slots": 1..64 (concurrent queries per graph and
- * kind; 1 = one query at a time), "memory_cap_bytes": N (device bytes that
- * running queries may hold; a query over the cap waits),
+ * kind; 1 = one query at a time), "memory_cap_bytes": N (bounds the sum over
+ * the running queries of a share each: 3 bits per vertex for BFS, 4 bytes and
+ * 2 bits for SSSP; a query over the cap waits.  What the server allocates does
+ * not follow that sum: a graph's engine is made whole, for 64 queries, when
+ * its first query is admitted -- 96 bytes per vertex for BFS, 352 once a search
+ * passes level 254, 288 for SSSP -- and kept until server_destroy),
  * "sssp_solo_min_vertices": N (default 2^22), "sssp_solo_min_skew": X
  * (default 16; both 0 = every graph's SSSP queries run as single searches)}.
  * Errors: TG_EINVAL, TG_ENOMEM, TG_EDEVICE. */
@@ -309,8 +329,9 @@ int server_wait(tg_server *s, uint64_t ticket, int64_t timeout_us, double *laten
 /* JSON counters: completed (queries finished, failed ones included),
  * supersteps (slot-engine supersteps), max_concurrent (most queries admitted
  * and not yet finished at once), waiting (queries not yet admitted),
- * memory_in_use (the device bytes the admitted queries hold, at most the
- * memory cap; 0 once every query has finished), max_slots; same return
+ * memory_in_use (the sum of the admitted queries' shares, see
+ * memory_cap_bytes, at most that cap; 0 once every query has finished),
+ * max_slots; same return
  * convention as partition_info. */
 int server_stats(tg_server *s, char *json, size_t cap);
 

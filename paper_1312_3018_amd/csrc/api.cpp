@@ -1060,7 +1060,12 @@ int check_roots(const tg_partition *p, const int32_t *roots, int32_t nr, const c
 
 // Calls with several roots: the 64-slot engine streams an edge once for all
 // of them, the single searches keep up to four in flight.  The lines below
-// are where the two met (ms, single / engine).
+// are where the two met (ms, single / engine).  They go by the vertex count
+// because it sets what the routes differ in: the engines' rows and passes grow
+// with it whatever the roots, the others' work with the roots.  They were taken
+// on R-MAT graphs of 16 generated edges per vertex, weights uniform in 1..255;
+// sparser, denser or deeper graphs cross elsewhere, and the results do not
+// depend on the route.
 //
 // BFS (levels only).  2 roots: 2^13..2^20 vertices 0.49-0.72 / 0.25-0.67,
 // RMAT-22 0.63 / 1.01; 4 roots: RMAT-22 1.09 / 1.10, RMAT-23 1.61 / 2.61; 8:
@@ -1111,8 +1116,10 @@ bool sssp_in_buckets(const tg_partition *p, int32_t nr) {
   return p->tune.sssp_batch_roots != 0 && nr > 0 && buckets_supported(p);
 }
 
-// Few roots on small graphs: a launch per round for all of them.  The most
-// roots by log2 of the vertex count (ms, rounds / the better of the others).
+// Few roots on small graphs: a launch per round for all of them.  A round looks
+// at every vertex of every root, which is free while it fits a launch's own
+// time and not beyond, hence fewer roots on more vertices.  The most roots by
+// log2 of the vertex count (ms, rounds / the better of the others).
 // Symmetric: 2^12, 32 roots 0.50 / 0.78; 2^14, 16: 0.68 / 1.00, 32: 1.16 / 1.03;
 // 2^15, 8: 1.07 / 1.21, 16: 1.81 / 1.14; 2^17, 4: 1.60 / 1.86; 2^18, 2: 1.29 /
 // 1.95, 4: 2.58 / 2.32; 2^19, 1: 1.29 / 1.75, 2: 2.17 / 1.90; 2^20, 1: 1.88 /

@@ -17,9 +17,10 @@
 // 4-byte distance; BC: an 8-byte path count, a 4-byte delta), or 4 bytes
 // per slot (PageRank).  The host sends its frontier as a bitmap (BFS), its
 // active set or frontier with values (SSSP, BC), or one 4-byte contribution
-// per vertex (PageRank).  Copies run on two copy streams of their own, one
-// per direction, into buffers double-buffered by superstep parity and
-// ordered by events (section 4.3.4 (iv)); sending only what changed is the
+// per vertex (PageRank).  Messages of up to 128 KB are moved by a kernel on
+// the GPU's stream; larger ones run on two copy streams of their own, one
+// per direction, ordered by events (section 4.3.4 (iv)).  Buffers are
+// double-buffered by superstep parity.  Sending only what changed is the
 // compression that section 4.4 points to.  The host's part of a superstep
 // is sent before it computes, so the GPU's reduction never waits for the
 // host's expansion, and PageRank's host gather runs beside the GPU step.

@@ -10,6 +10,10 @@
 // column of row ids (the header) goes before each slice, and a bit array
 // tells headers from codes: a wave reads its whole share as one stream, two
 // groups of columns ahead of the gathers, whatever the lengths of the slices.
+// (Sorting rows in windows and storing slices of them by columns is SELL-C-sigma,
+// Kreutzer, Hager, Wellein, Fehske and Bishop, SIAM J. Sci. Comput. 36(5), 2014,
+// with C = 64 and sigma = WIN; the stream of shares, its headers, the codes and
+// the classes below are not part of it.)
 // What a lane does per column is one load of the source's code, one gather
 // and one or two additions: no row offsets, no staging in LDS, no reduction
 // across lanes (the row-block kernel of pr_rows.hip spends 77 vector
