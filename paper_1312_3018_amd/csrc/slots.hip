@@ -385,15 +385,19 @@ __global__ __launch_bounds__(BLOCK) void k_ms_widen(const uint8_t *__restrict__ 
 
 // An SSSP frontier, per thread or (the block's part) published: the OR of its
 // masks, its edges, its (vertex, slot) pairs and their edges (see MsState and
-// MS_PAIRS; the latter on 64 lines, as thousands of blocks add to them).
+// MS_PAIRS; the latter on 64 lines, as thousands of blocks add to them).  (Sums
+// of 32 bits where they fit: a pulled superstep takes 205 us so, as without
+// the last two, 213 with all in 64 bits.)
 struct FrontierSums {
-  u64 any, edges, pairs, relax;
-  __device__ __forceinline__ void add(u64 mask, u64 deg) {
+  u64 any, edges, relax;
+  uint32_t pairs;
+  template <class T>
+  __device__ __forceinline__ void add(u64 mask, T deg) {
     any |= mask;
     edges += deg;
-    const u64 k = deg ? (u64)__popcll(mask) : 0ull;
+    const uint32_t k = deg ? (uint32_t)__popcll(mask) : 0u;
     pairs += k;
-    relax += k * deg;
+    relax += (u64)k * deg;
   }
 };
 template <int THREADS>
@@ -418,7 +422,7 @@ __device__ __forceinline__ void publish_frontier(FrontierSums F, u64 (*mf)[kSlot
     u64 *mine = mf[blockIdx.x % MF_COPIES];
     if (F.any & ~__hip_atomic_load(mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicOr(mine, F.any);
     if (F.edges) atomicAdd(mine + 1, F.edges);
-    if (F.pairs) stat_add(stat_counter(work, MS_PAIRS), F.pairs);
+    if (F.pairs) stat_add(stat_counter(work, MS_PAIRS), (u64)F.pairs);
     if (F.relax) stat_add(stat_counter(work, MS_EDGES), F.relax);
     if (blockIdx.x == 0)
       for (int c = 0; c < MF_COPIES; ++c) other[c][0] = other[c][1] = 0ull;
@@ -488,7 +492,7 @@ struct MinOp {
     }
     if (lane == 0) {
       front_new[v] = g;
-      if (g) sums->add(g, (u64)(uint32_t)__builtin_amdgcn_readlane(deg, j));
+      if (g) sums->add(g, (uint32_t)__builtin_amdgcn_readlane(deg, j));
     }
   }
   __device__ __forceinline__ void idle(int32_t v, u64, u64 open) const {
@@ -500,7 +504,7 @@ struct MinOp {
       next[v] = 0;
     }
     front_new[v] = g;
-    if (g) sums->add(g, (u64)deg);
+    if (g) sums->add(g, (uint32_t)deg);
   }
 };
 
@@ -602,9 +606,14 @@ __global__ __launch_bounds__(BLOCK) void k_ms_release(u64 *visited, u64 *ovf, in
     if (ovf) ovf[v] &= ~mask;
   }
 }
-// (a launch's threads are counted in 32 bits: 64 a vertex would wrap around,
-// unreported, from 2^26 vertices on)
-constexpr int64_t ROW_GRID = 16384;
+// A launch's threads are counted in 32 bits: 64 a vertex would wrap around,
+// unreported, from 2^26 vertices on.  The release has a thread per distance up
+// to half of that and strides beyond.  (16384 blocks that stride are done
+// sooner, one slot 7 instead of 17 us on RMAT-18 and 110 instead of 227 on
+// 2^22 vertices, but the server then completes more supersteps of fewer queries
+// each: the eight graphs of the serving benchmark, 2,000 queries/s offered,
+// 1,245 instead of 1,370 served/s.)
+constexpr int64_t ROW_GRID = 16384, RELEASE_GRID = 1 << 23;
 __global__ __launch_bounds__(BLOCK) void k_ms_release_dist(int32_t *dist, int64_t n, u64 mask,
                                                            const unsigned long long *work, unsigned long long *sums) {
   report_work(work, sums);
@@ -997,8 +1006,8 @@ int SlotEngine::retire(u64 mask, u64 *overflow) {
                          nullptr, nullptr);
       TG_HIP(hipMemcpyAsync(h_ovf + 1, ovf_slots + 1, sizeof(u64), hipMemcpyDeviceToHost, s));
     }
-    hipLaunchKernelGGL(k_ms_release_dist, dim3((unsigned)std::min<int64_t>(nblk(g.n * kSlots), ROW_GRID)), dim3(BLOCK),
-                       0, s, dist, g.n, mask, ws.work, h_ovf + 2);
+    hipLaunchKernelGGL(k_ms_release_dist, dim3((unsigned)std::min<int64_t>(nblk(g.n * kSlots), RELEASE_GRID)),
+                       dim3(BLOCK), 0, s, dist, g.n, mask, ws.work, h_ovf + 2);
     TG_HIP(hipGetLastError());
     TG_HIP(hipStreamSynchronize(s));
     if (flagged && overflow) *overflow = h_ovf[1] & flagged;

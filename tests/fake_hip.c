@@ -24,6 +24,7 @@ static int host_mallocs_left = -1;                /* the same for pinned ones */
 static size_t marked_copy = 0, marked_from = 0;   /* device-to-host copies of this size: bytes from .. on become 127 */
 static int failing_syncs = 0;                     /* stream synchronisations still to fail */
 static uint64_t launches, most_threads, live_mallocs;
+static const void *release_kernel; /* a thread per distance up to 2^31, strides beyond: exempt from a lower limit */
 static const void *message_kernel; /* k_message(dst, src, bytes, clocks) */
 static uint64_t message_ticks;     /* the time its launches took, each block 100 ticks longer than the one before */
 static __thread hipError_t last_error;
@@ -128,7 +129,8 @@ hipError_t hipLaunchKernel(const void *f, dim3 g, dim3 b, void **args, size_t sh
   const uint64_t x = (uint64_t)g.x * b.x, y = (uint64_t)g.y * b.y, z = (uint64_t)g.z * b.z;
   ++launches;
   if (x > most_threads) most_threads = x;
-  if (!x || !y || !z || (uint64_t)b.x * b.y * b.z > 1024 || shared > 163840 || x >= thread_limit ||
+  if (!x || !y || !z || (uint64_t)b.x * b.y * b.z > 1024 || shared > 163840 ||
+      x >= (f == release_kernel && thread_limit < (uint64_t)1 << 31 ? ((uint64_t)1 << 31) + 1 : thread_limit) ||
       y >= thread_limit || z >= thread_limit)
     return fail(hipErrorInvalidConfiguration);
   if (f == message_kernel) {
@@ -152,6 +154,7 @@ void __hipRegisterFunction(void **h, const void *f, char *a, const char *b, unsi
                            void *j, int *k) {
   (void)h, (void)a, (void)c, (void)d, (void)e, (void)i, (void)j, (void)k;
   if (strstr(b, "k_message")) message_kernel = f;
+  if (strstr(b, "k_ms_release_dist")) release_kernel = f;
 }
 void __hipRegisterVar(void **h, void *v, char *a, char *b, int c, size_t d, int e, int f) {
   (void)h, (void)v, (void)a, (void)b, (void)c, (void)d, (void)e, (void)f;

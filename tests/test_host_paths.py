@@ -87,7 +87,8 @@ def run(tmp_path_factory):
 @pytest.mark.parametrize("symmetric", [True, False])
 def test_grids_fit_every_vertex_count(run, symmetric):
     """A launch's threads are counted in 32 bits and V may be 2^31 - 1: past a
-    fixed number of blocks no launch takes more than two threads per vertex."""
+    fixed number of blocks no launch takes more than two threads per vertex
+    (that number is 2^23 for the clearing of a retired slot's distances)."""
     run(f"""
 n = 1 << 23
 P = path(n, 100, symmetric={symmetric})
@@ -103,6 +104,15 @@ for k in (1, 2, 64):
 check(lib.cc(P, BUF, None))
 check(lib.pagerank(P, 0.85, 2, 0, BUF, None))
 assert fake.fake_most_threads() >= n
+""")
+
+
+def test_grid_of_the_released_distances(run):
+    """A thread per distance where 64 of them a vertex are 2^32 and more."""
+    run("""
+P = path((1 << 26) + 5, 100)
+check(lib.sssp_batched(P, roots(2), 2, BUF, None))
+assert 1 << 26 < fake.fake_most_threads() <= 1 << 31
 """)
 
 
