@@ -83,7 +83,7 @@ TRAFFIC_ROWS = {
     "pr_gather": ("pr", ["k_pr_sell<true>", "k_pr_sell_long", "k_pr_combine", "k_pr_rows<true, int, 8>",
                          "k_pr_long<true>", "k_pr_dsum"], "sum"),
     "bfs_step": ("bfs", ["k_bfs_step<int>"], "sum"),
-    "msbfs_expand": ("msbfs", ["k_ms_push", "k_ms_pull<int>", "k_ms_bfs_dense<int, false>", "k_ms_pull_hubs<int>"], 3),
+    "msbfs_expand": ("msbfs", ["k_ms_push", "k_ms_bfs_dense<int, false>", "k_ms_pull<int>", "k_ms_pull_hubs<int>"], 2),
     "mssssp_expand": ("mssssp", ["k_ms_sssp_pull", "k_ms_sssp_expand", "k_ms_sssp_expand_few", "k_ms_sssp_pull_hubs"],
                       3),
     "bucket_relax": ("bucket", ["k_bucket_relax"], "sum"),
